@@ -10,7 +10,7 @@
 // gathers each galaxy's inputs into a 128-byte record in that order, so the
 // kernel reads them coalesced; each lane writes its results at its galaxy's
 // index in the caller's arrays.
-#include "sps_eval.h"
+#include "sps_pair.h"
 
 namespace sps {
 
@@ -315,6 +315,73 @@ __global__ void __launch_bounds__(WAVE, 2) k_approx(DevConsts k, ApproxArgs a) {
     for (int p = 0; p < NP; ++p) a.grad[(size_t)p * a.n + dst_g] = gr[p] + bad;
 }
 
+// One galaxy per workgroup of two waves (sps_pair.h): batches up to PAIR_MAX_GAL.  The caller's
+// arrays are read in place and each galaxy's results written at its own index.
+struct PairArgs {
+    int n, sfh;
+    const float *params, *z, *obs, *sigma;   // obs: the adjoints with MODE_VJP
+    const uint8_t *mask;
+    const float *bounds, *prior;
+    const uint16_t *qf, *qa;
+    float *mag, *val, *grad;
+    int *status;
+};
+
+template <int MODE>
+__global__ void __launch_bounds__(PAIR_T, 2) k_approx_pair(DevConsts k, PairArgs a) {
+    __shared__ PairLds S;
+    const int g = blockIdx.x, tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & (WAVE - 1), nb = k.n_band;
+    const float zf = a.z[g];
+    float f;
+    const int kk = z_bucket(k, zf, &f);
+    PairTab q;
+    const int kb = max(kk, 0);
+    pair_load(q, k, a.qf, kb, w, lane, row_blocks(nb));
+    const PairBin bin = pair_bin(k);
+    const int bl = min(lane, nb - 1);
+    float ob = 0.0f, sg = 1.0f, mine = 0.0f;   // mine: lane p holds parameter p
+    uint32_t mask = 0xffu;
+    mine = a.params[(size_t)min(lane, NP - 1) * a.n + g];
+    if (MODE != MODE_MAGS) ob = a.obs[(size_t)g * nb + bl];
+    if (MODE != MODE_MAGS && MODE != MODE_VJP) {
+        sg = a.sigma[(size_t)g * nb + bl];
+        mask = a.mask[g];
+    }
+    const float x = mine;
+    float dth = 1.0f;
+    if (MODE == MODE_LOGPOST_GRAD) bound_param(a.bounds + 4 * min(lane, NP - 1), x, mine, dth);
+    float th[NP], gr[NP], mag;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) th[p] = lane_value(mine, p);
+    double t_obs, m0, logl;
+    cosmo_at(k, (double)zf, t_obs, m0);
+    m0 -= 2.5 * (double)th[0];
+    constexpr int EM = (MODE == MODE_LOGPOST_GRAD || MODE == MODE_VJP) ? MODE_LOGL_GRAD : MODE;
+    pair_eval<EM, true, 1, MODE == MODE_VJP>(k, bin, q, a.qa, kb, S, a.sfh, th, zf, f, t_obs, m0, ob, sg, mask, mag, logl, gr);
+    if (w != 0) return;
+    // a redshift outside the table: NaN results, flagged as by the sort
+    const float bad = (kk >= 0) ? 0.0f : __int_as_float(0x7fc00000);
+    if (kk < 0 && lane == 0) atomicOr(a.status, STATUS_Z_RANGE);
+    if (MODE == MODE_MAGS) {
+        if (lane < nb) a.mag[(size_t)g * nb + lane] = mag + bad;
+        return;
+    }
+    float gp = 0.0f;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) gp = (lane == p) ? gr[p] : gp;
+    double lp = logl;
+    if (MODE == MODE_LOGPOST_GRAD) {
+        float dlp;
+        const double l = log_prior_skewnorm(a.prior + 3 * min(lane, NP - 1), x, dlp);
+        gp = fmaf(gp, dth, dlp);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) lp += lane_value(l, p);
+    }
+    if (a.val && lane == 0) a.val[g] = (float)lp + bad;
+    if (MODE == MODE_LOGL || !a.grad) return;
+    if (lane < NP) a.grad[(size_t)lane * a.n + g] = gp + bad;
+}
+
 // ------------------------------------------------------------------ SSP weights output
 __global__ void __launch_bounds__(WAVE) k_weights(DevConsts k, int n, int sfh, const float *__restrict__ params,
                                                   const float *__restrict__ z, float *__restrict__ w) {
@@ -376,9 +443,38 @@ int launch_bucket_sort(sps_ctx *c, hipStream_t s, int n, const float *z, const G
     return launch_bucket_sort_ws(c, s, ctx_ws(c), n, z, ga, grid);
 }
 
+// Up to PAIR_MAX_GAL galaxies a pair of waves takes each galaxy (k_approx_pair); the chip holds 1024
+// such pairs at a time, 9.6 us each round (value+gradient).  Above it a lane takes each galaxy, whose
+// serial chain of 94 bins, twice, costs the same ~130 us from a few thousand to 65,536 galaxies.
+// Pair / lane kernels, us per call: value+gradient 52 / 139 at 4096, 111 / 133 at 10,240, 131 / 135
+// at 12,288; magnitudes 25 / 69, 53 / 64, 62 / 64; and at 64 galaxies 16 / 770, where a wave of the lane
+// kernel spans all redshift buckets and contracts once for each.
+constexpr int PAIR_MAX_GAL = 10240;
+
 int launch_approx_ws(sps_ctx *c, hipStream_t s, const ApproxWs &ws, int n, int sfh, int mode, const float *params,
                      const float *z, const float *obs, const float *sigma, const uint8_t *mask, const float *bounds,
                      const float *prior, float *out_mag, float *out_val, float *out_grad) {
+    if (n <= PAIR_MAX_GAL) {
+        const PairArgs a{n, sfh, params, z, obs, sigma, mask, bounds, prior, c->d_qf, c->d_qa, out_mag,
+                         mode == MODE_VJP ? nullptr : out_val, out_grad, c->d_status};
+        hipEvent_t *tev = timing_pair(c);
+        if (tev) (void)hipEventRecord(tev[0], s);
+        switch (mode) {
+            case MODE_MAGS: hipLaunchKernelGGL(k_approx_pair<MODE_MAGS>, dim3(n), dim3(PAIR_T), 0, s, c->k, a); break;
+            case MODE_LOGL: hipLaunchKernelGGL(k_approx_pair<MODE_LOGL>, dim3(n), dim3(PAIR_T), 0, s, c->k, a); break;
+            case MODE_LOGL_GRAD:
+                hipLaunchKernelGGL(k_approx_pair<MODE_LOGL_GRAD>, dim3(n), dim3(PAIR_T), 0, s, c->k, a);
+                break;
+            case MODE_VJP: hipLaunchKernelGGL(k_approx_pair<MODE_VJP>, dim3(n), dim3(PAIR_T), 0, s, c->k, a); break;
+            case MODE_LOGPOST_GRAD:
+                hipLaunchKernelGGL(k_approx_pair<MODE_LOGPOST_GRAD>, dim3(n), dim3(PAIR_T), 0, s, c->k, a);
+                break;
+            default: return set_error(SPS_E_INVAL, "bad approx mode");
+        }
+        if (tev) (void)hipEventRecord(tev[1], s);
+        SPS_HIP(hipGetLastError());
+        return SPS_OK;
+    }
     const GatherArgs ga{params, mode == MODE_MAGS ? nullptr : obs, mode == MODE_MAGS ? nullptr : sigma,
                         mode == MODE_MAGS ? nullptr : mask, ws.rec, c->d_status};
     int rc = launch_bucket_sort_ws(c, s, ws, n, z, &ga, nullptr);

@@ -1,0 +1,78 @@
+"""The small-batch kernels (one galaxy per pair of waves) against the batched ones, which the FP64
+oracle pins: the same galaxies in one call above the small-batch limit and in slices below it.
+
+Both take every FP32 sum in the same order; only the FP64 total of the smooth mass differs in its
+order (1e-16), which can move the rounding of FP32 values derived from it by one unit (6e-8).  Through
+the near-cancelling sums of the gradient that stays within 2e-6 of a galaxy's largest component, and
+within 2e-5 of log L's scale at the residuals used here."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from gpu_common import bounds_prior, dev, f32, gal_inputs, soa
+
+pytestmark = pytest.mark.gpu
+
+PAIR_MAX = 10240            # the batched kernels take over above it
+N = PAIR_MAX + 1
+SLICES = [(0, 1), (1, 64), (64, N)]     # a single galaxy, a ragged few, the rest
+
+
+@pytest.fixture(scope="module", params=[1, 6, 8])
+def ctx(request, ssp2000):
+    import paper_2506_19919_amd as sps
+    c = sps.Context(ssp2000, synth.filters(request.param), precisions=(sps.SPS_F64, sps.SPS_F32), max_gal=N)
+    c.build_ztable(64, 0.1, 3.0)
+    yield c
+    c.close()
+
+
+def batch(kind, nb):
+    sfh, th, z = gal_inputs(kind, N, 811)
+    z[[5, 70, 9000]] = [0.05, 3.5, 3.2]           # outside the table: NaN on both paths
+    z[[6, 71]] = [0.1, 3.0]                       # its first and last node
+    th[7, 4], th[72, 4] = 1.0, 0.0                # all burst, no burst
+    th[8, 5], th[73, 5] = 11.5, 3.0               # a burst past every bin (empty window), below the grid
+    rng = np.random.default_rng(812)
+    obs, sig = f32(rng.uniform(20, 26, (N, nb))), f32(rng.uniform(0.3, 1.0, (N, nb)))
+    mask = rng.integers(0, 1 << nb, N).astype(np.uint8)
+    return sfh, f32(th), f32(z), obs, sig, mask
+
+
+def close(a, b, rel):
+    assert np.array_equal(np.isnan(a), np.isnan(b))
+    scale = np.nanmax(np.abs(b), axis=1, keepdims=True)
+    assert np.all((np.abs(a - b) <= rel * np.maximum(scale, 1e-30)) | np.isnan(b))
+
+
+@pytest.mark.parametrize("kind", ["dpl", "lognormal_burst"])
+@pytest.mark.parametrize("op", ["mags", "loglike", "logl", "logpost", "vjp"])
+def test_small_batches_match_the_batched_kernels(ctx, kind, op):
+    nb = ctx.n_band
+    sfh, th, z, obs, sig, mask = batch(kind, nb)
+    if op == "logpost":
+        bnd, pri = bounds_prior()
+        th = f32((th - th.mean(0)) / (th.std(0) + 1e-3))      # unbounded values of order one
+        bp = (dev(bnd), dev(pri))
+
+    def call(lo, hi):
+        t = lambda a: dev(np.ascontiguousarray(a[lo:hi]))
+        p, zz, o, s, m = soa(th[lo:hi]), t(z), t(obs), t(sig), dev(mask[lo:hi], torch.uint8)
+        if op == "mags":
+            return [ctx.phot_approx(sfh, p, zz)]
+        if op == "vjp":
+            return [ctx.phot_vjp(sfh, p, zz, o).T]
+        if op == "logl":
+            return [ctx.loglike_grad(sfh, p, zz, o, s, m, grad=False)[:, None]]
+        v, g = (ctx.logpost_grad(sfh, p, zz, o, s, m, *bp) if op == "logpost" else
+                ctx.loglike_grad(sfh, p, zz, o, s, m))
+        return [v[:, None], g.T]
+
+    whole = [x.cpu().numpy().astype(np.float64) for x in call(0, N)]
+    parts = [np.concatenate(x) for x in zip(*[[y.cpu().numpy().astype(np.float64) for y in call(*s)] for s in SLICES])]
+    assert np.isnan(whole[0][[5, 70, 9000]]).all()
+    for a, b in zip(parts, whole):
+        close(a, b, 2e-5 if b.shape[1] == 1 else 2e-6)
+    with pytest.raises(Exception):
+        ctx.status()                              # the redshifts outside the table were flagged
