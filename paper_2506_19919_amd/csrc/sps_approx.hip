@@ -328,7 +328,7 @@ struct PairArgs {
 };
 
 template <int MODE>
-__global__ void __launch_bounds__(PAIR_T, 2) k_approx_pair(DevConsts k, PairArgs a) {
+__global__ void __launch_bounds__(PAIR_T, 4) k_approx_pair(DevConsts k, PairArgs a) {
     __shared__ PairLds S;
     const int g = blockIdx.x, tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & (WAVE - 1), nb = k.n_band;
     const float zf = a.z[g];
@@ -336,7 +336,7 @@ __global__ void __launch_bounds__(PAIR_T, 2) k_approx_pair(DevConsts k, PairArgs
     const int kk = z_bucket(k, zf, &f);
     PairTab q;
     const int kb = max(kk, 0);
-    pair_load(q, k, a.qf, kb, w, lane, row_blocks(nb));
+    pair_load(q, k, a.qf, kb, w, lane);
     const PairBin bin = pair_bin(k);
     const int bl = min(lane, nb - 1);
     float ob = 0.0f, sg = 1.0f, mine = 0.0f;   // mine: lane p holds parameter p
@@ -350,14 +350,15 @@ __global__ void __launch_bounds__(PAIR_T, 2) k_approx_pair(DevConsts k, PairArgs
     const float x = mine;
     float dth = 1.0f;
     if (MODE == MODE_LOGPOST_GRAD) bound_param(a.bounds + 4 * min(lane, NP - 1), x, mine, dth);
-    float th[NP], gr[NP], mag;
+    float th[NP], gp, mag;
 #pragma unroll
     for (int p = 0; p < NP; ++p) th[p] = lane_value(mine, p);
     double t_obs, m0, logl;
     cosmo_at(k, (double)zf, t_obs, m0);
     m0 -= 2.5 * (double)th[0];
     constexpr int EM = (MODE == MODE_LOGPOST_GRAD || MODE == MODE_VJP) ? MODE_LOGL_GRAD : MODE;
-    pair_eval<EM, true, 1, MODE == MODE_VJP>(k, bin, q, a.qa, kb, S, a.sfh, th, zf, f, t_obs, m0, ob, sg, mask, mag, logl, gr);
+    pair_eval<EM, true, 1, MODE == MODE_VJP>(k, bin, q, a.qa, a.qf, kb, S, a.sfh, th, zf, kk < 0 ? 0.0f : 1.0f - f,
+                                             f, t_obs, m0, ob, sg, mask, mag, logl, gp);
     if (w != 0) return;
     // a redshift outside the table: NaN results, flagged as by the sort
     const float bad = (kk >= 0) ? 0.0f : __int_as_float(0x7fc00000);
@@ -366,9 +367,6 @@ __global__ void __launch_bounds__(PAIR_T, 2) k_approx_pair(DevConsts k, PairArgs
         if (lane < nb) a.mag[(size_t)g * nb + lane] = mag + bad;
         return;
     }
-    float gp = 0.0f;
-#pragma unroll
-    for (int p = 0; p < NP; ++p) gp = (lane == p) ? gr[p] : gp;
     double lp = logl;
     if (MODE == MODE_LOGPOST_GRAD) {
         float dlp;

@@ -14,7 +14,7 @@
 // 1e-3 * 5/(n+5) and dual averaging restarts at mu = log(10 eps).
 // Sampling: Welford mean / M2 of the physical parameters per chain (FP64); the same
 // state arrays hold the window statistics during warm-up.
-#include "sps_eval.h"
+#include "sps_pair.h"
 
 namespace sps {
 
@@ -196,6 +196,7 @@ struct HmcArgs {
     // evaluation runs with these in memory instead of registers
     float *pm, *xt;
     int ntmp;
+    int *status;
 };
 
 struct LaneCtx {
@@ -505,6 +506,196 @@ __global__ void __launch_bounds__(64, 2) k_hmc(DevConsts k, HmcArgs a) {
     a.da0[sl] = da0;
 }
 #undef ST
+
+// Out of line for the same reason as log_prior_all: one parameter's log prior and its momentum.
+struct LanePrior {
+    double lp;
+    float dlp;
+};
+__device__ __noinline__ LanePrior log_prior_lane(PriorC c, float x) {
+    LanePrior r;
+    r.lp = log_prior_pc(c, x, r.dlp);
+    return r;
+}
+// parameter pp's momentum: words 2t and 2t + 1 (t = pp / 2) of the iteration's blocks 0 .. 2
+__device__ __noinline__ float momentum_lane(uint32_t key0, uint32_t key1, uint32_t it, uint32_t chain_id, int pp,
+                                            float minv) {
+    const int t2 = pp & ~1;
+    uint32_t c4[4] = {(uint32_t)(t2 >> 2), it, chain_id, 0u};
+    philox4x32_10(c4, key0, key1);
+    const float r = sqrtf(-2.0f * logf(u01f((t2 & 2) ? c4[2] : c4[0])));
+    float sn, cs;
+    sincosf(6.283185307179586f * u01f((t2 & 2) ? c4[3] : c4[1]), &sn, &cs);
+    return r * ((pp & 1) ? sn : cs) / sqrtf(minv);
+}
+// The same iterations for few chains: one chain per workgroup of two waves (sps_pair.h), galaxies in
+// the caller's order (slot = galaxy * C + chain), the draws and the arithmetic of k_hmc_init and
+// k_hmc.  Wave 0 carries the chain, lane p < NP parameter p, so the per-parameter work of a step is one
+// lane's and the state stays in registers for the whole launch; wave 1 takes its share of the model.  With `start` the launch
+// evaluates the starting point first.
+template <int SFH>
+__global__ void __launch_bounds__(PAIR_T, 2) k_hmc_pair(DevConsts k, HmcArgs a, int start) {
+    __shared__ PairLds S;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & (WAVE - 1);
+    const int sl = blockIdx.x, nslot = a.n_gal * a.C, g = sl / a.C, ch = sl % a.C, pp = min(lane, NP - 1);
+    const uint32_t chain_id = (uint32_t)(ch * a.n_gal + g);
+    const bool mine = lane < NP;   // (in wave 0) the lanes that write a parameter's state
+    const size_t at = (size_t)pp * nslot + sl;
+    const float zf = a.z[g];
+    float f;
+    const int kk = z_bucket(k, zf, &f), kb = max(kk, 0);
+    if (kk < 0 && tid == 0) atomicOr(a.status, STATUS_Z_RANGE);
+    const float wz0 = kk < 0 ? 0.0f : 1.0f - f;
+    const PairBin bin = pair_bin(k);
+    const int bl = min(lane, k.n_band - 1);
+    const float ob = a.obs[(size_t)g * k.n_band + bl], sg = a.sigma[(size_t)g * k.n_band + bl];
+    const uint32_t mask = a.mask[g];
+    const double t_obs = age_universe_gyr(k, (double)zf), m0base = mag_offset(k, (double)zf);
+    float bnd[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) bnd[t] = a.bounds[4 * pp + t];
+    const PriorC pc = prior_const(a.prior + 3 * pp);
+
+    float x, gx = 0.0f, minv = 1.0f, eps = a.init_step, mu = logf(10.0f * a.init_step), hbar = 0.0f, lebar = 0.0f;
+    double lp = 0.0, wmean = 0.0, wm2 = 0.0;
+    int nacc = 0, da0 = 0;
+    if (start) {
+        if (a.theta0) {
+            x = a.theta0[((size_t)ch * NP + pp) * a.n_gal + g];
+        } else {
+            float x0[NP];
+            prior_draw(a.prior, a.key0, a.key1, chain_id, x0);
+            x = x0[0];
+#pragma unroll
+            for (int t = 1; t < NP; ++t) x = (pp == t) ? x0[t] : x;
+        }
+    } else {
+        x = a.x[at];
+        gx = a.gr[at];
+        minv = a.minv[at];
+        wmean = a.wmean[at];
+        wm2 = a.wm2[at];
+        lp = a.lp[sl];
+        eps = a.eps[sl];
+        mu = a.mu[sl];
+        hbar = a.hbar[sl];
+        lebar = a.lebar[sl];
+        nacc = a.nacc[sl];
+        da0 = a.da0[sl];
+    }
+
+    for (int it = a.it0 - (start ? 1 : 0); it < a.it1; ++it) {
+        const bool first = it < a.it0;   // the starting point's evaluation
+        float p = 0.0f, xt = x, gn = gx;
+        double H0 = -lp, lpn = lp;
+        if (!first && w == 0) {
+            p = momentum_lane(a.key0, a.key1, (uint32_t)it, chain_id, pp, minv);
+            const double hp = 0.5 * (double)minv * (double)p;
+#pragma unroll
+            for (int t = 0; t < NP; ++t) H0 = fma(lane_value(hp, t), (double)lane_value(p, t), H0);
+        }
+        for (int l = first ? a.L - 1 : 0; l < a.L; ++l) {
+            float thp, dth = 0.0f, th[NP], mag;
+            if (w == 0) {
+                if (!first) {
+                    p = fmaf(0.5f * eps, gn, p);
+                    xt = fmaf(eps * minv, p, xt);
+                }
+                bound_param(bnd, xt, thp, dth);
+                if (lane < NP) S.th[lane] = thp;
+            }
+            __syncthreads();
+            thp = S.th[pp];
+            PairTab q;
+            pair_load(q, k, a.qf, opaque(kb), w, lane);
+#pragma unroll
+            for (int t = 0; t < NP; ++t) th[t] = lane_value(thp, t);
+            double logl;
+            // opaque: nothing derived from the galaxy's constants is formed outside the loop (registers;
+            // and a product hoisted away from its sum would no longer be fused with it)
+            pair_eval<MODE_LOGL_GRAD, false, HG, false>(k, bin, q, a.qa, a.qf, kb, S, SFH, th, opaque(zf), opaque(wz0),
+                                                        opaque(f), opaque(t_obs),
+                                                        opaque(m0base) - 2.5 * (double)th[0], ob, sg, mask, mag, logl,
+                                                        gn, !first);
+            if (w != 0) continue;
+            const LanePrior lpr = log_prior_lane(pc, xt);
+            gn = fmaf(gn, dth, lpr.dlp);
+            lpn = 0.0;
+#pragma unroll
+            for (int t = 0; t < NP; ++t) lpn += lane_value(lpr.lp, t);
+            lpn = logl + lpn;
+            if (!first) p = fmaf(0.5f * eps, gn, p);
+        }
+        if (w != 0) continue;
+        if (first) {
+            lp = lpn;
+            gx = gn;
+            continue;
+        }
+        double H1 = -lpn;
+        const double hp = 0.5 * (double)minv * (double)p;
+#pragma unroll
+        for (int t = 0; t < NP; ++t) H1 = fma(lane_value(hp, t), (double)lane_value(p, t), H1);
+        uint32_t c4[4] = {2u, (uint32_t)it, chain_id, 0u};   // the accept draw: word 2 of block 2
+        philox4x32_10(c4, a.key0, a.key1);
+        float alpha;
+        const bool acc = metropolis(H1, H1 - H0, c4[2], alpha);
+        if (acc) {
+            lp = lpn;
+            x = xt;
+            gx = gn;
+        }
+        if (it < a.NW) {
+            const float m = (float)(it - da0 + 1), eta = 1.0f / (m + 10.0f);
+            hbar = (1.0f - eta) * hbar + eta * (a.target - alpha);
+            const float leps = mu - sqrtf(m) / 0.05f * hbar, wk = powf(m, -0.75f);
+            lebar = wk * leps + (1.0f - wk) * lebar;
+            eps = expf(it == a.NW - 1 ? lebar : leps);
+            int wi = -1;
+            for (int t = 0; t < a.n_win; ++t)
+                if (it >= a.win_s[t] && it < a.win_e[t]) wi = t;
+            if (wi >= 0) {
+                const double nn = (double)(it - a.win_s[wi] + 1);
+                const double d = (double)x - wmean;
+                wmean += d / nn;
+                wm2 += d * ((double)x - wmean);
+                if (it == a.win_e[wi] - 1) {
+                    minv = (float)(nn / (nn + 5.0) * (wm2 / (nn - 1.0)) + 1e-3 * 5.0 / (nn + 5.0));
+                    wmean = wm2 = 0.0;
+                    mu = logf(10.0f * eps);
+                    hbar = lebar = 0.0f;
+                    da0 = it + 1;
+                }
+            }
+        } else {
+            nacc += acc ? 1 : 0;
+            const double nrec = (double)(it - a.NW + 1);
+            float th, dth;
+            bound_param(bnd, x, th, dth);
+            const double d = (double)th - wmean;
+            wmean += d / nrec;
+            wm2 += d * ((double)th - wmean);
+            if (mine && a.samples) a.samples[(((size_t)(it - a.NW) * a.C + ch) * NP + pp) * a.n_gal + g] = th;
+        }
+    }
+    if (w != 0) return;
+    if (mine) {
+        a.x[at] = x;
+        a.gr[at] = gx;
+        a.minv[at] = minv;
+        a.wmean[at] = wmean;
+        a.wm2[at] = wm2;
+    }
+    if (tid == 0) {
+        a.lp[sl] = lp;
+        a.eps[sl] = eps;
+        a.mu[sl] = mu;
+        a.hbar[sl] = hbar;
+        a.lebar[sl] = lebar;
+        a.nacc[sl] = nacc;
+        a.da0[sl] = da0;
+    }
+}
 
 // pooled posterior mean / sd, classic Gelman-Rubin R-hat and acceptance per galaxy; slot
 // r * C + c holds chain c of galaxy perm[r] (of galaxy r if perm is null).  Acceptance: the
@@ -1452,6 +1643,12 @@ static int launch_hmc_exact(sps_ctx *c, hipStream_t s, const sps_hmc_cfg *cfg, i
     return SPS_OK;
 }
 
+// Up to HMC_PAIR_MAX chains a pair of waves takes each chain (k_hmc_pair), above it a pair of lanes
+// (k_hmc), whose waves span ever fewer redshift buckets as the batch grows.  Pair of waves / lanes, us
+// per leapfrog step: 13 / 101 at 512 chains, 28 / 84 at 2048, 46 / 80 at 4096, 84 / 90 at 8192, 103 / 91
+// at 10,240.
+constexpr int HMC_PAIR_MAX = 8192;
+
 int launch_hmc(sps_ctx *c, hipStream_t s, const sps_hmc_cfg *cfg, int n_gal, int sfh, const float *z,
                const float *obs, const float *sigma, const uint8_t *mask, const float *bounds, const float *prior,
                const float *theta0, float *samples, float *post_mean, float *post_sd, float *rhat, float *accept,
@@ -1470,8 +1667,10 @@ int launch_hmc(sps_ctx *c, hipStream_t s, const sps_hmc_cfg *cfg, int n_gal, int
     const int it0 = cfg->it_begin, it1 = cfg->it_end > 0 ? cfg->it_end : nit;
     if (c->hstate_bytes < hmc_state_bytes(nslot))
         return set_error(SPS_E_STATE, "the HMC chain state needs n_gal * n_chain reserved galaxies (call sps_reserve)");
-    int rc = launch_bucket_sort(c, s, n_gal, z);
+    const bool pair = nslot <= HMC_PAIR_MAX;   // those kernels keep the caller's order: no sort
+    int rc = pair ? SPS_OK : launch_bucket_sort(c, s, n_gal, z);
     if (rc) return rc;
+    const int *perm = pair ? nullptr : c->d_perm;
     const ChainState cs = chain_state_at(c->d_hstate, nslot);
     a.n_gal = n_gal;
     a.C = C;
@@ -1490,7 +1689,8 @@ int launch_hmc(sps_ctx *c, hipStream_t s, const sps_hmc_cfg *cfg, int n_gal, int
     a.bounds = bounds;
     a.prior = prior;
     a.theta0 = theta0;
-    a.perm = c->d_perm;
+    a.perm = perm;
+    a.status = c->d_status;
     a.qf = c->d_qf;
     a.qa = c->d_qa;
     a.samples = samples;
@@ -1514,22 +1714,30 @@ int launch_hmc(sps_ctx *c, hipStream_t s, const sps_hmc_cfg *cfg, int n_gal, int
     dim3 grid((nslot * HG + 63) / 64), block(64);
     const bool dpl = (sfh == SPS_SFH_DPL);
     const size_t lds_bytes = approx_lds_bytes(c->n_band, false, HG);
-    if (it0 == 0) {
+    if (it0 == 0 && pair) {
+        // the first launch below evaluates the starting points
+    } else if (it0 == 0) {
         if (dpl) hipLaunchKernelGGL(k_hmc_init<SPS_SFH_DPL>, grid, block, lds_bytes, s, c->k, a);
         else hipLaunchKernelGGL(k_hmc_init<SPS_SFH_LOGNORMAL>, grid, block, lds_bytes, s, c->k, a);
-    } else if ((rc = move_state(c, s, cs, state, cfg, n_gal, c->d_perm, 0, it0))) {
+    } else if ((rc = move_state(c, s, cs, state, cfg, n_gal, perm, 0, it0))) {
         return rc;
     }
     for (int b0 = it0; b0 < it1; b0 += blk_it) {
         a.it0 = b0;
         a.it1 = b0 + blk_it < it1 ? b0 + blk_it : it1;
+        if (pair) {
+            const int start = b0 == 0;
+            if (dpl) hipLaunchKernelGGL(k_hmc_pair<SPS_SFH_DPL>, dim3(nslot), dim3(PAIR_T), 0, s, c->k, a, start);
+            else hipLaunchKernelGGL(k_hmc_pair<SPS_SFH_LOGNORMAL>, dim3(nslot), dim3(PAIR_T), 0, s, c->k, a, start);
+            continue;
+        }
         if (dpl) hipLaunchKernelGGL(k_hmc<SPS_SFH_DPL>, grid, block, lds_bytes, s, c->k, a);
         else hipLaunchKernelGGL(k_hmc<SPS_SFH_LOGNORMAL>, grid, block, lds_bytes, s, c->k, a);
     }
-    if (state && (rc = move_state(c, s, cs, state, cfg, n_gal, c->d_perm, 1, it1))) return rc;
+    if (state && (rc = move_state(c, s, cs, state, cfg, n_gal, perm, 1, it1))) return rc;
     if (it1 == nit)
         hipLaunchKernelGGL(k_hmc_summary, dim3((n_gal + 255) / 256), dim3(256), 0, s, n_gal, C, cfg->n_sample,
-                           c->d_perm, a.wmean, a.wm2, a.nacc, nullptr, a.eps, a.minv, post_mean, post_sd, rhat, accept, step,
+                           perm, a.wmean, a.wm2, a.nacc, nullptr, a.eps, a.minv, post_mean, post_sd, rhat, accept, step,
                            inv_metric);
     SPS_HIP(hipGetLastError());
     return SPS_OK;

@@ -19,7 +19,7 @@
 namespace sps {
 
 constexpr int PAIR_T = 2 * WAVE;
-constexpr int PAIR_NB = 3;   // blocks of 16 table rows or ages per wave, at most
+constexpr int PAIR_NB = AGE_BLK / 2;   // blocks of 16 table rows or ages per wave (rows past the bands are zero)
 
 // ------------------------------------------------------------------ sums over a wave
 template <int CTRL, int ROWS = 0xf>
@@ -50,16 +50,20 @@ __device__ inline double wave_sum(double v) {
 
 // ------------------------------------------------------------------ per-workgroup state
 // factors of the adjoint's sums over bins (see pair_sums)
-enum { PX_NGBAR, PX_PSBAR, PX_BURST, PX_ONE, PX_COUNT };
-enum { PY_PS, PY_D1, PY_D2, PY_D3, PY_PB, PY_DPB, PY_COUNT };
-enum { PS_CBAR, PS_A0, PS_A1, PS_A2, PS_B0, PS_B1, PS_B2, PS_E1, PS_E2, PS_E3, PS_FBAR, PS_COUNT };
+enum { PX_NGBAR, PX_PSBAR, PX_BURST, PX_ONE, PX_INVS3, PX_COUNT };
+enum { PY_PS, PY_D1, PY_D2, PY_D3, PY_PB, PY_DPB, PY_DD, PY_COUNT };
+enum { PS_CBAR, PS_A0, PS_A1, PS_A2, PS_B0, PS_B1, PS_B2, PS_E1, PS_E2, PS_E3, PS_FBAR, PS_MET, PS_COUNT };
 
+// rows of 100 floats: 16-byte aligned, and the sums' lanes, each on its own row, on different banks
+constexpr int PAIR_ROW = SLOT_W + 4;
 struct __attribute__((aligned(16))) PairLds {
     uint16_t hi[2][SLOT_W], lo[2][SLOT_W];   // contraction operands of the two nodes, BF16 hi and lo
     float t[SLOT_W];                         // T, then dP_age
-    float px[PX_COUNT][SLOT_W], py[PY_COUNT][SLOT_W];
-    float pz[NZ + 4], sum[PS_COUNT + 1];
-    double S[2], d[2][4];
+    float px[PX_COUNT][PAIR_ROW], py[PY_COUNT][PAIR_ROW];
+    float met[2][16];                        // dlogL/dP_Z and dP_Z/dmu, zero from NZ on
+    float pz[16], th[12];
+    float sbar[NB_MAX], bx[4][NB_MAX], by[4][NB_MAX];   // per band: dlogL/d(sum), and factors of gr 0, 7, 8, 9
+    double ll[NB_MAX], S[2], d[2][4];
 };
 
 // a thread's age bin: fixed over a run
@@ -81,25 +85,31 @@ __device__ inline float pair_edge(const PairBin &b, int e) {
     return (e <= WAVE) ? lane_value(b.up0, e - 1) : lane_value(b.up1, e - 1 - WAVE);
 }
 
-// wave w's fragments (qf or qa of sps_internal.h) of nodes kb and kb + 1: blocks 2 t + w, BF16 hi and lo
+// wave w's fragments (qf or qa of sps_internal.h) of nodes kb and kb + 1: blocks 2 t + w, BF16 hi and
+// lo.  The first PAIR_KRES k-steps are loaded ahead, the rest inside the contraction: one leaves 128
+// registers, four waves per SIMD (value+gradient at 4096 galaxies, us: 41; two ahead, three waves, 43;
+// all three ahead, two waves, 50; at one galaxy the same within 1 us).
+constexpr int PAIR_KRES = 1;
 struct PairTab {
-    b8v h[2][PAIR_NB][KSTEPS], l[2][PAIR_NB][KSTEPS];
+    b8v h[PAIR_KRES][2][PAIR_NB], l[PAIR_KRES][2][PAIR_NB];
 };
-__device__ inline void pair_load(PairTab &t, const DevConsts &k, const uint16_t *q, int kb, int w, int lane, int nbk) {
-    const uint16_t *b = q + (size_t)kb * QB_NODE + lane * 8;
+__device__ inline void pair_load_step(const DevConsts &k, const uint16_t *b, int ks, int w, b8v (&h)[2][PAIR_NB],
+                                      b8v (&l)[2][PAIR_NB]) {
     const size_t lo_off = (size_t)k.n_z * QB_NODE;
 #pragma unroll
     for (int nb = 0; nb < PAIR_NB; ++nb) {
-        if (2 * nb + w >= nbk) break;
 #pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks)
-#pragma unroll
-            for (int nd = 0; nd < 2; ++nd) {
-                const size_t o = (size_t)((2 * nb + w) * KSTEPS + ks) * 512 + (size_t)nd * QB_NODE;
-                t.h[nd][nb][ks] = *(const b8v *)(b + o);
-                t.l[nd][nb][ks] = *(const b8v *)(b + lo_off + o);
-            }
+        for (int nd = 0; nd < 2; ++nd) {
+            const size_t o = (size_t)((2 * nb + w) * KSTEPS + ks) * 512 + (size_t)nd * QB_NODE;
+            h[nd][nb] = *(const b8v *)(b + o);
+            l[nd][nb] = *(const b8v *)(b + lo_off + o);
+        }
     }
+}
+__device__ inline void pair_load(PairTab &t, const DevConsts &k, const uint16_t *q, int kb, int w, int lane) {
+    const uint16_t *b = q + (size_t)kb * QB_NODE + lane * 8;
+#pragma unroll
+    for (int ks = 0; ks < PAIR_KRES; ++ks) pair_load_step(k, b, ks, w, t.h[ks], t.l[ks]);
 }
 
 __device__ inline void split_store(float x, uint16_t *hi, uint16_t *lo) {
@@ -110,8 +120,13 @@ __device__ inline void split_store(float x, uint16_t *hi, uint16_t *lo) {
 
 // S.t[n] = sum over both nodes and k of operand[k] table[k][n], the wave's blocks of n (each
 // accumulator takes its products in contract()'s order)
-__device__ inline void pair_contract(const PairTab &t, PairLds &S, int w, int lane, int nbk) {
+__device__ inline void pair_contract(const PairTab &t, const DevConsts &k, const uint16_t *q, int kb, PairLds &S, int w,
+                                     int lane) {
     const int x = lane & 15, lk = lane >> 4;
+    const uint16_t *qb = q + (size_t)kb * QB_NODE + lane * 8;
+    b8v th[KSTEPS - PAIR_KRES + 1][2][PAIR_NB], tl[KSTEPS - PAIR_KRES + 1][2][PAIR_NB];
+#pragma unroll
+    for (int ks = PAIR_KRES; ks < KSTEPS; ++ks) pair_load_step(k, qb, ks, w, th[ks - PAIR_KRES], tl[ks - PAIR_KRES]);
     v4f acc[PAIR_NB];
 #pragma unroll
     for (int nb = 0; nb < PAIR_NB; ++nb) acc[nb] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -120,73 +135,101 @@ __device__ inline void pair_contract(const PairTab &t, PairLds &S, int w, int la
         const int o = 32 * ks + 8 * lk;
         const b8v a0h = *(const b8v *)(S.hi[0] + o), a0l = *(const b8v *)(S.lo[0] + o);
         const b8v a1h = *(const b8v *)(S.hi[1] + o), a1l = *(const b8v *)(S.lo[1] + o);
+        const auto &h = ks < PAIR_KRES ? t.h[ks < PAIR_KRES ? ks : 0] : th[ks < PAIR_KRES ? 0 : ks - PAIR_KRES];
+        const auto &l = ks < PAIR_KRES ? t.l[ks < PAIR_KRES ? ks : 0] : tl[ks < PAIR_KRES ? 0 : ks - PAIR_KRES];
 #pragma unroll
         for (int nb = 0; nb < PAIR_NB; ++nb) {
-            if (2 * nb + w >= nbk) break;
-            acc[nb] = mfma3(a0h, a0l, t.h[0][nb][ks], t.l[0][nb][ks], acc[nb]);
-            acc[nb] = mfma3(a1h, a1l, t.h[1][nb][ks], t.l[1][nb][ks], acc[nb]);
+                acc[nb] = mfma3(a0h, a0l, h[0][nb], l[0][nb], acc[nb]);
+            acc[nb] = mfma3(a1h, a1l, h[1][nb], l[1][nb], acc[nb]);
         }
     }
 #pragma unroll
     for (int nb = 0; nb < PAIR_NB; ++nb) {
-        if (2 * nb + w >= nbk) break;
         if (lk == 0) S.t[16 * (2 * nb + w) + x] = acc[nb][0];
     }
 }
 
-// The adjoint's sums over the age bins, each in the batched kernels' order: with PG lanes per galaxy
-// there, bins q, q + PG, ... in turn for each q, then the PG sums added.  Lane PG s + q of wave 0
-// takes part q of sum s.
+// The adjoint's sums, each in the batched kernels' order with one fused multiply-add per term, as their
+// loops compile to: with PG lanes per galaxy there, bins q, q + PG, ... in turn for each q, then the
+// PG sums added.  Lane PG s + q of the wave takes part q of sum s; the sum is returned in lane PG s.
+// Bin i's factors lie at pair_at(i): each part's bins are consecutive.
 template <int PG>
-__device__ inline void pair_sums(PairLds &S, int lane) {
+__device__ inline int pair_at(int i) {
+    return PG == 1 ? i : (i & 1) * (SLOT_W / 2) + (i >> 1);
+}
+template <int PG>
+__device__ inline float pair_sums(const PairLds &S, int lane, int i0, int i_end) {
     static_assert(PG * PS_COUNT <= WAVE, "a lane per partial sum");
+    constexpr int LEN = SLOT_W / PG, CH = 16 / PG;
     const int s = min(lane / PG, PS_COUNT - 1), q = lane % PG;
-    const int xi = s == PS_FBAR ? PX_NGBAR : s <= PS_A2 ? PX_PSBAR : (s == PS_E1 || s == PS_E2) ? PX_BURST : PX_ONE;
+    const int xi = s == PS_FBAR ? PX_NGBAR : s <= PS_A2 ? PX_PSBAR : s <= PS_B2 ? PX_ONE : s == PS_E3 ? PX_INVS3 : PX_BURST;
     const int yi = (s == PS_CBAR || s == PS_FBAR) ? PY_PS : s <= PS_A2 ? PY_D1 + s - PS_A0
-                   : s <= PS_B2 ? PY_D1 + s - PS_B0 : s == PS_E2 ? PY_PB : PY_DPB;
-    const float *xp = S.px[xi], *yp = S.py[yi];
+                   : s <= PS_B2 ? PY_D1 + s - PS_B0 : s == PS_E2 ? PY_PB : s == PS_E3 ? PY_DD : PY_DPB;
+    const float *xp = S.px[xi] + q * LEN, *yp = S.py[yi] + q * LEN;
     float v = 0.0f;
-    constexpr int STEP = 4;
-#pragma unroll 4
-    for (int i = 0; i < SLOT_W; i += STEP) {
-        const v4f a = *(const v4f *)(xp + i), b = *(const v4f *)(yp + i);
 #pragma unroll
-        for (int e = 0; e < STEP; e += PG)
-            v = (PG == 1) ? fmaf(a[e], b[e], v) : fmaf(q ? a[e + PG - 1] : a[e], q ? b[e + PG - 1] : b[e], v);
+    for (int c = 0; c < LEN; c += 24) {
+        v4f a[6], b[6];
+#pragma unroll
+        for (int e = 0; e < 6; ++e) {
+            a[e] = *(const v4f *)(xp + c + 4 * e);
+            b[e] = *(const v4f *)(yp + c + 4 * e);
+        }
+#pragma unroll
+        for (int e = 0; e < 24; ++e) v = fmaf(a[e / 4][e % 4], b[e / 4][e % 4], v);
     }
-    // the burst part of fbar follows its smooth part
-    if (s == PS_FBAR) {
-#pragma unroll 2
-        for (int i = 0; i < SLOT_W; i += STEP) {
-            const v4f a = *(const v4f *)(xp + i), b = *(const v4f *)(S.py[PY_PB] + i);
+    // the burst part of fbar follows its smooth part, over the window's bins (zero around them); the
+    // metallicity sum, in order
+    if (s == PS_MET) v = 0.0f;
+    const float *x2 = s == PS_MET ? S.met[0] : S.px[PX_NGBAR] + q * LEN;
+    const float *y2 = s == PS_MET ? S.met[1] : S.py[PY_PB] + q * LEN;
+    const int c0 = i0 / PG & ~(CH - 1), c1 = (i_end + PG - 1) / PG;
+    if (s >= PS_FBAR) {
+        for (int c = c0; c < c1; c += CH) {
+            const bool met = s == PS_MET;
+            if (met && c > c0) break;
+            const int at = met ? 0 : c;
+            v4f a[4], b[4];
 #pragma unroll
-            for (int e = 0; e < STEP; e += PG)
-                v = (PG == 1) ? fmaf(a[e], -b[e], v) : fmaf(q ? a[e + PG - 1] : a[e], q ? -b[e + PG - 1] : -b[e], v);
+            for (int e = 0; e < 4; ++e) {
+                const int o = (PG == 2 && !met && e >= 2) ? 0 : 4 * e;
+                a[e] = *(const v4f *)(x2 + at + o);
+                b[e] = *(const v4f *)(y2 + at + o);
+            }
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                if (met ? e < NZ : e < CH) v = fmaf(met ? a[e / 4][e % 4] : -a[e / 4][e % 4], b[e / 4][e % 4], v);
+            }
         }
     }
-    if (PG == 2) v += __shfl_xor(v, 1, WAVE);
-    if (q == 0 && lane < PG * PS_COUNT) S.sum[s] = v;
+    if (PG == 2) {
+        if (s == PS_MET && q != 0) v = 0.0f;   // one part holds the whole of it
+        v += __shfl_xor(v, 1, WAVE);
+    }
+    return v;
 }
 
 // ------------------------------------------------------------------ one evaluation
 // Every thread of the workgroup calls it with the same galaxy.  q: the wave's forward fragments of
-// nodes kb and kb + 1 on entry; the adjoint's are loaded into it (qa).  PK and PG: the columns'
+// nodes kb and kb + 1 on entry; the adjoint's are loaded into it.  wz0, wz1: the nodes' z weights (1 - f and f, or 0 outside the table:
+// T = 0, as in the batched kernels).  PK and PG: the columns'
 // 24-bit rounding and the lanes per galaxy of the batched kernel that it stands in for (the one-shot
-// kernels: true, 1; the samplers: false, 2).  ob, sg_f: lane b of each wave holds band b's
-// observation and sigma (VJP: ob its adjoint).  MODE_MAGS: lane b gets band b's magnitude in
-// `mag`.  Else: logl, and with MODE_LOGL_GRAD the gradient, in every thread.
+// kernels: true, 1; the samplers: false, 2).  ob, sg_f: lane b of wave 0 holds band b's
+// observation and sigma (VJP: ob its adjoint).  Results in wave 0: MODE_MAGS: lane b gets band b's
+// magnitude in `mag`.  Else: logl in every lane, and with MODE_LOGL_GRAD lane p gets gradient component p.
 template <int MODE, bool PK, int PG, bool VJP>
 __device__ __forceinline__ void pair_eval(const DevConsts &k, const PairBin &bin, PairTab &q, const uint16_t *qa,
-                                          int kb, PairLds &S, int sfh, const float (&th)[NP], float zf, float f,
-                                          double t_obs, double m0, float ob, float sg_f, uint32_t mask, float &mag,
-                                          double &logl, float (&gr)[NP]) {
+                                          const uint16_t *qf, int kb, PairLds &S, int sfh, const float (&th)[NP],
+                                          float zf, float wz0, float wz1, double t_obs, double m0, float ob, float sg_f, uint32_t mask, float &mag,
+                                          double &logl, float &gp, bool fuse_odd = true) {
     constexpr bool GRAD = (MODE == MODE_LOGL_GRAD);
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & (WAVE - 1);
     const int nb = k.n_band;
     const float t_obs_f = (float)t_obs;
     const bool dpl = (sfh == SPS_SFH_DPL);
 
-    // ---- weights: the thread's bin
+    // ---- weights: the thread's bin.  Wave 1 holds the oldest bins, whose panels take longest: wave 0
+    // does the per-galaxy work (metallicity, dust) meanwhile, and the bands later
     float m = 0.0f, d1 = 0.0f, d2 = 0.0f, d3 = 0.0f;
     if (bin.own) {
         if (dpl) {
@@ -201,27 +244,28 @@ __device__ __forceinline__ void pair_eval(const DevConsts &k, const PairBin &bin
         const double s = wave_sum((double)m);
         if (lane == 0) S.S[w] = s;
     }
-    // metallicity bin `lane` (both waves alike): its upper edge, the lower one from the lane before
-    const float inv_sz = 1.0f / k.sigma_logz;
-    float pz = 0.0f, dpz = 0.0f;
-    {
+    DustVal dust{};
+    if (w == 0) {
+        // metallicity bin `lane`: its upper edge, the lower one from the lane before
+        const float inv_sz = 1.0f / k.sigma_logz;
         const bool top = lane >= NZ - 1;
         const float xe = top ? INFINITY : (bin.met_hi - th[6]) * inv_sz;
         const float te = top ? 0.0f : 0.5f * erfcf(0.7071067811865475f * fabsf(xe));
-        const float de = top ? 0.0f : phi_f(xe);
-        float xp = __shfl_up(xe, 1, WAVE), tp = __shfl_up(te, 1, WAVE), dp = __shfl_up(de, 1, WAVE);
+        constexpr float C = 0.3989422804014327f;
+        const float ee = top ? 0.0f : expf(-0.5f * xe * xe), de = C * ee;
+        float xp = __shfl_up(xe, 1, WAVE), tp = __shfl_up(te, 1, WAVE), ep = __shfl_up(ee, 1, WAVE);
         if (lane == 0) {
             xp = -INFINITY;
-            tp = dp = 0.0f;
+            tp = ep = 0.0f;
         }
         if (lane < NZ) {
-            pz = (xp > 0.0f) ? tp - te : ((xe <= 0.0f) ? te - tp : 1.0f - tp - te);
-            dpz = (dp - de) * inv_sz;
-            if (w == 0) S.pz[lane] = pz;
+            // met_weights' differences of densities, fused as its unrolled loop is: the odd edges' products,
+            // or (k_hmc_init) each lower edge's
+            S.met[1][lane] = ((lane & 1) && fuse_odd ? fmaf(-C, ee, C * ep) : fmaf(C, ep, -de)) * inv_sz;
+            S.pz[lane] = (xp > 0.0f) ? tp - te : ((xe <= 0.0f) ? te - tp : 1.0f - tp - te);
         }
+        dust = dust_at(bin.lam / ((1.0f + zf) * 5500.0f), th[7], th[8], th[9]);
     }
-    __syncthreads();
-    const double Sm = S.S[0] + S.S[1];
     // burst: first bin of the window (every bin before it ends at or below the window's start)
     const float l_obs = (float)log10_split(t_obs * 1e9), mu = th[5], inv_s3 = 1.0f / (3.0f * k.burst_sig);
     const float v0 = mu - 3.0f * k.burst_sig;
@@ -230,11 +274,18 @@ __device__ __forceinline__ void pair_eval(const DevConsts &k, const PairBin &bin
     const int i_end = min(i0 + k.burst_nbins, NA);
     const float Zb = burst_mass(burst_edge_at<false>(pair_edge(bin, i0), l_obs, mu, inv_s3),
                                 burst_edge_at<false>(pair_edge(bin, i_end), l_obs, mu, inv_s3));
-    const BurstEdge b_lo = burst_edge_at<GRAD>(bin.le_lo, l_obs, mu, inv_s3);
-    const BurstEdge b_hi = burst_edge_at<GRAD>(bin.le_hi, l_obs, mu, inv_s3);
+    const float fb = th[4], bz = (Zb > 0.0f) ? fb / Zb : 0.0f;
     const bool in_win = bin.own && tid >= i0 && tid < i_end;
-    const float bm = burst_mass(b_lo, b_hi);
-    const float fb = th[4], sm = (1.0f - fb) * (float)(1.0 / Sm), bz = (Zb > 0.0f) ? fb / Zb : 0.0f;
+    float bm = 0.0f, b_dd = 0.0f;   // the bin's burst mass and difference of edge densities
+    if (in_win) {
+        const BurstEdge b_lo = burst_edge_at<GRAD>(bin.le_lo, l_obs, mu, inv_s3);
+        const BurstEdge b_hi = burst_edge_at<GRAD>(bin.le_hi, l_obs, mu, inv_s3);
+        bm = burst_mass(b_lo, b_hi);
+        b_dd = b_lo.d - b_hi.d;
+    }
+    __syncthreads();
+    const double Sm = S.S[0] + S.S[1];
+    const float sm = (1.0f - fb) * (float)(1.0 / Sm);
     // the column holds P_age / scale, as in the batched kernels
     const float scale = (sm > 0.0f) ? sm : 1.0f, cb = (sm > 0.0f) ? bz / sm : bz;
     if (tid < SLOT_W) {
@@ -244,107 +295,104 @@ __device__ __forceinline__ void pair_eval(const DevConsts &k, const PairBin &bin
         if (!bin.own) c = 0.0f;
         if (PK) c = __uint_as_float(round24(c) & 0xffffff00u);
 #pragma unroll
-        for (int nd = 0; nd < 2; ++nd) split_store(c * ((nd ? f : 1.0f - f) * scale), &S.hi[nd][tid], &S.lo[nd][tid]);
+        for (int nd = 0; nd < 2; ++nd) split_store(c * ((nd ? wz1 : wz0) * scale), &S.hi[nd][tid], &S.lo[nd][tid]);
     }
     __syncthreads();
 
     // ---- T, then the adjoint's fragments on their way
-    pair_contract(q, S, w, lane, row_blocks(nb));
-    if (GRAD) pair_load(q, k, qa, kb, w, lane, AGE_BLK);
+    pair_contract(q, k, qf, kb, S, w, lane);
+    if (GRAD) pair_load(q, k, qa, kb, w, lane);
     __syncthreads();
 
-    // ---- bands: lane b of each wave (both waves alike)
-    const int R = nb * NZ;
-    const bool is_b = lane < nb;
-    const int bl = is_b ? lane : 0;
-    double ll = 0.0;
-    float sbar = 0.0f, gm = 0.0f, fbar_b = 0.0f, f7 = 0.0f, f8 = 0.0f, f9 = 0.0f;
-    {
+    // ---- bands: lane b of wave 0
+    gp = 0.0f;
+    if (w == 0) {
+        const int R = nb * NZ;
+        const bool is_b = lane < nb;
+        const int bl = is_b ? lane : 0;
         double sb = 0.0;
 #pragma unroll
         for (int j = 0; j < NZ; ++j) sb += (double)S.pz[j] * (double)S.t[bl * NZ + j];
-        const DustVal d = dust_at(bin.lam / ((1.0f + zf) * 5500.0f), th[7], th[8], th[9]);
-        const double mg = m0 - 2.5 * log10_split((double)d.F * sb);
+        const double mg = m0 - 2.5 * log10_split((double)dust.F * sb);
         mag = (float)mg;
-        if (MODE == MODE_MAGS) return;
-        if (is_b && ((mask >> bl) & 1u)) {
-            if (VJP) {
-                gm = ob;
-            } else {
-                const double sg = sg_f;
-                const double r = (mg - (double)ob) / sg;
-                ll = -0.5 * r * r - (double)logf(sg_f * 2.5066282746310002f);
-                gm = (float)(-r / sg);
-            }
-            if (MODE != MODE_LOGL) {
+        if (MODE != MODE_MAGS) {
+            double ll = 0.0;
+            float sbar = 0.0f, gm = 0.0f, fbar_b = 0.0f, f7 = 0.0f, f8 = 0.0f, f9 = 0.0f;
+            if (is_b && ((mask >> bl) & 1u)) {
+                if (VJP) {
+                    gm = ob;
+                } else {
+                    const double sg = sg_f;
+                    const double r = (mg - (double)ob) / sg;
+                    ll = -0.5 * r * r - (double)logf(sg_f * 2.5066282746310002f);
+                    gm = (float)(-r / sg);
+                }
                 const float c = gm * (-2.5f / LN10F);
                 sbar = (float)(c / sb);
-                fbar_b = c / d.F;
-                f7 = d.dF_tauv;
-                f8 = d.dF_delta;
-                f9 = d.dF_floor;
+                fbar_b = c / dust.F;
+                f7 = dust.dF_tauv;
+                f8 = dust.dF_delta;
+                f9 = dust.dF_floor;
+            }
+            if (lane < NB_MAX) {
+                S.ll[lane] = ll;
+                if (GRAD) {
+                    S.sbar[lane] = sbar;
+                    S.bx[0][lane] = -2.5f;
+                    S.bx[1][lane] = S.bx[2][lane] = S.bx[3][lane] = fbar_b;
+                    S.by[0][lane] = gm;
+                    S.by[1][lane] = f7;
+                    S.by[2][lane] = f8;
+                    S.by[3][lane] = f9;
+                }
+            }
+            // sums over the bands in the batched order: bands q, q + PG, ... for each q < PG, then those
+            // added (the entries past the bands are zero)
+            logl = 0.0;
+            const int row = lane == 0 ? 0 : min(max(lane - 6, 1), 3);   // lane p = 0, 7, 8, 9: gr[p]
+#pragma unroll
+            for (int q0 = 0; q0 < PG; ++q0) {
+                double l = 0.0;
+                float v = 0.0f;
+#pragma unroll
+                for (int b = q0; b < NB_MAX; b += PG) {
+                    l += S.ll[b];
+                    if (GRAD) v = fmaf(S.bx[row][b], S.by[row][b], v);
+                }
+                logl += l;
+                gp += v;
             }
         }
-    }
-    // sums over the bands in the batched order: bands q, q + PG, ... for each q < PG, then those added
-    logl = 0.0;
+        if (GRAD) {
+            // d/dmu_Z = sum_j dP_Z(j)/dmu sum_b sbar_b T[b][j] (the last sum in pair_sums), and the operands
+            // C = sbar_b P_Z(j)
+            const int j = min(lane, NZ - 1);
+            float s = 0.0f;
 #pragma unroll
-    for (int p = 0; p < NP; ++p) gr[p] = 0.0f;
+            for (int q0 = 0; q0 < PG; ++q0) {
+                float v = 0.0f;
 #pragma unroll
-    for (int q0 = 0; q0 < PG; ++q0) {
-        double l = 0.0;
-        float v0_ = 0.0f, v7 = 0.0f, v8 = 0.0f, v9 = 0.0f;
+                for (int b = q0; b < NB_MAX; b += PG) v = fmaf(S.sbar[b], S.t[b * NZ + j], v);
+                s += v;
+            }
+            if (lane < NZ) S.met[0][lane] = s;
 #pragma unroll
-        for (int b = q0; b < NB_MAX; b += PG) {
-            if (b >= nb) break;
-            l += lane_value(ll, b);
-            if (MODE == MODE_LOGL) continue;
-            const float fbb = lane_value(fbar_b, b);
-            v0_ += -2.5f * lane_value(gm, b);
-            v7 = fmaf(fbb, lane_value(f7, b), v7);
-            v8 = fmaf(fbb, lane_value(f8, b), v8);
-            v9 = fmaf(fbb, lane_value(f9, b), v9);
+            for (int t = 0; t < 2; ++t) {
+                const int r = lane + WAVE * t;
+                float c = (r < R) ? S.sbar[min(r / NZ, NB_MAX - 1)] * S.pz[r % NZ] : 0.0f;
+                if (PK) c = __uint_as_float(round24(c) & 0xffffff00u);
+                if (r < SLOT_W) {
+                    split_store(c * wz0, &S.hi[0][r], &S.lo[0][r]);
+                    split_store(c * wz1, &S.hi[1][r], &S.lo[1][r]);
+                }
+            }
         }
-        logl += l;
-        gr[0] += v0_;
-        gr[7] += v7;
-        gr[8] += v8;
-        gr[9] += v9;
     }
     if (!GRAD) return;
-
-    // ---- d/dmu_Z = sum_j dP_Z(j)/dmu sum_b sbar_b T[b][j], and the operands C = sbar_b P_Z(j)
-    {
-        const int j = min(lane, NZ - 1);
-        float s = 0.0f;
-#pragma unroll
-        for (int q0 = 0; q0 < PG; ++q0) {
-            float v = 0.0f;
-#pragma unroll
-            for (int b = q0; b < NB_MAX; b += PG) {
-                if (b >= nb) break;
-                v = fmaf(lane_value(sbar, b), S.t[b * NZ + j], v);
-            }
-            s += v;
-        }
-        float mbar = 0.0f;
-#pragma unroll
-        for (int t = 0; t < NZ; ++t) mbar = fmaf(lane_value(s, t), lane_value(dpz, t), mbar);
-        gr[6] = mbar;
-        const float wnode = w ? f : 1.0f - f;   // wave w writes node w's operands
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int r = lane + WAVE * t, rb = min(r / NZ, nb - 1), rj = r % NZ;
-            const float sr = __shfl(sbar, rb, WAVE), pr = S.pz[rj];
-            float c = (r < R) ? sr * pr : 0.0f;
-            if (PK) c = __uint_as_float(round24(c) & 0xffffff00u);
-            if (r < SLOT_W) split_store(c * wnode, &S.hi[w][r], &S.lo[w][r]);
-        }
-    }
     __syncthreads();
 
     // ---- dP_age
-    pair_contract(q, S, w, lane, AGE_BLK);
+    pair_contract(q, k, qa, kb, S, w, lane);
     __syncthreads();
 
     // ---- weights adjoint: the thread's bin, then the sums over bins
@@ -353,20 +401,22 @@ __device__ __forceinline__ void pair_eval(const DevConsts &k, const PairBin &bin
         float gbar = S.t[tid];
         if (PK) gbar = __uint_as_float(round24(gbar) & 0xffffff00u);
         if (!bin.own) gbar = 0.0f;
-        const float psbar = (1.0f - fb) * gbar;
-        S.px[PX_NGBAR][tid] = -gbar;
-        S.px[PX_PSBAR][tid] = psbar;
-        S.px[PX_BURST][tid] = in_win ? fb * gbar : 0.0f;
-        S.px[PX_ONE][tid] = 1.0f;
-        S.py[PY_PS][tid] = dpl ? m * invS : (float)((double)m / Sm);
-        S.py[PY_D1][tid] = d1;
-        S.py[PY_D2][tid] = d2;
-        S.py[PY_D3][tid] = d3;
-        S.py[PY_PB][tid] = in_win ? bm * invZ : 0.0f;
-        S.py[PY_DPB][tid] = in_win ? (b_lo.d - b_hi.d) * inv_s3 : 0.0f;
+        const int at = pair_at<PG>(tid);
+        S.px[PX_NGBAR][at] = -gbar;
+        S.px[PX_PSBAR][at] = (1.0f - fb) * gbar;
+        S.px[PX_BURST][at] = in_win ? fb * gbar : 0.0f;
+        S.px[PX_ONE][at] = 1.0f;
+        S.px[PX_INVS3][at] = inv_s3;
+        S.py[PY_PS][at] = dpl ? m * invS : (float)((double)m / Sm);
+        S.py[PY_D1][at] = d1;
+        S.py[PY_D2][at] = d2;
+        S.py[PY_D3][at] = d3;
+        S.py[PY_PB][at] = bm * invZ;
+        S.py[PY_DPB][at] = b_dd * inv_s3;
+        S.py[PY_DD][at] = b_dd;
     }
     if (!dpl) {   // FP64 sums of the log-normal derivatives
-        const double pb = (1.0f - fb) * (bin.own ? -S.px[PX_NGBAR][min(tid, SLOT_W - 1)] : 0.0f);
+        const double pb = (1.0f - fb) * (bin.own ? -S.px[PX_NGBAR][pair_at<PG>(min(tid, SLOT_W - 1))] : 0.0f);
         const double v[4] = {pb * (double)d1, pb * (double)d2, (double)d1, (double)d2};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -375,18 +425,24 @@ __device__ __forceinline__ void pair_eval(const DevConsts &k, const PairBin &bin
         }
     }
     __syncthreads();
-    if (w == 0) pair_sums<PG>(S, lane);
-    __syncthreads();
-    const float cbar = S.sum[PS_CBAR];
+    if (w != 0) return;
+    const float v = pair_sums<PG>(S, lane, i0, i_end);
+    auto sum = [&](int s) { return lane_value(v, PG * s); };
+    const float cbar = sum(PS_CBAR);
     if (dpl) {
 #pragma unroll
-        for (int j = 0; j < 3; ++j) gr[1 + j] = (S.sum[PS_A0 + j] - cbar * S.sum[PS_B0 + j]) * invS;
+        for (int j = 0; j < 3; ++j) gp = (lane == 1 + j) ? (sum(PS_A0 + j) - cbar * sum(PS_B0 + j)) * invS : gp;
     } else {
-        gr[1] = (float)((S.d[0][0] + S.d[1][0] - (double)cbar * (S.d[0][2] + S.d[1][2])) / Sm);
-        gr[2] = (float)((S.d[0][1] + S.d[1][1] - (double)cbar * (S.d[0][3] + S.d[1][3])) / Sm);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const double a = S.d[0][j] + S.d[1][j], b = S.d[0][j + 2] + S.d[1][j + 2];
+            gp = (lane == 1 + j) ? (float)((a - (double)cbar * b) / Sm) : gp;
+        }
+        gp = (lane == 3) ? 0.0f : gp;
     }
-    gr[4] = S.sum[PS_FBAR];
-    gr[5] = (S.sum[PS_E1] - S.sum[PS_E2] * S.sum[PS_E3]) * invZ;
+    gp = (lane == 4) ? sum(PS_FBAR) : gp;
+    gp = (lane == 5) ? (sum(PS_E1) - sum(PS_E2) * sum(PS_E3)) * invZ : gp;
+    gp = (lane == 6) ? sum(PS_MET) : gp;
 }
 
 }  // namespace sps

@@ -76,3 +76,27 @@ def test_small_batches_match_the_batched_kernels(ctx, kind, op):
         close(a, b, 2e-5 if b.shape[1] == 1 else 2e-6)
     with pytest.raises(Exception):
         ctx.status()                              # the redshifts outside the table were flagged
+
+
+@pytest.mark.parametrize("n", [2048, 2050])
+def test_hmc_at_the_limit_of_the_small_batch_kernel(ssp2000, filt6, orc, n):
+    # 8192 chains: a pair of waves each; 8200: the batched kernel.  Both follow the oracle draw by draw
+    import paper_2506_19919_amd as sps
+    from gpu_common import MAX_EXCUSED, draws_follow_oracle
+    C = 4
+    ctx = sps.Context(ssp2000, filt6, max_gal=n * C)
+    ctx.build_ztable(64, 0.1, 3.0)
+    sfh, th, z = gal_inputs("dpl", n, 821)
+    noise, sig = synth.photometric_noise(n, 6, 822)
+    obs, sig = f32(orc.phot_approx(sfh, th, z) + noise), f32(sig)
+    masks = synth.band_masks(n, 6, 823)
+    bnd, pri = bounds_prior()
+    frac = np.clip((th - bnd[:, 0]) / (bnd[:, 1] - bnd[:, 0]), 0.02, 0.98)
+    x0 = f32(np.log(frac / (1 - frac))[None] + 0.05 * np.random.default_rng(824).normal(size=(C, n, 10)))
+    kw = dict(n_chain=C, n_leapfrog=3, n_warmup=0, n_sample=2, init_step=0.01, seed=407)
+    out = ctx.hmc_run(sfh, dev(z), dev(obs), dev(sig), dev(masks, torch.uint8), dev(bnd), dev(pri),
+                      dev(np.ascontiguousarray(np.transpose(x0, (0, 2, 1)))), keep_samples=True, **kw)
+    ref = orc.hmc_run(sfh, z, obs, sig, masks, bnd, pri, x0, keep_samples=True, keep_trace=True, **kw)
+    ok, excused = draws_follow_oracle(out["samples"].cpu().numpy().transpose(0, 1, 3, 2), ref)
+    assert ok.all() and excused.mean() <= MAX_EXCUSED
+    ctx.close()
