@@ -441,13 +441,13 @@ int launch_bucket_sort(sps_ctx *c, hipStream_t s, int n, const float *z, const G
     return launch_bucket_sort_ws(c, s, ctx_ws(c), n, z, ga, grid);
 }
 
-// Up to PAIR_MAX_GAL galaxies a pair of waves takes each galaxy (k_approx_pair); the chip holds 1024
-// such pairs at a time, 9.6 us each round (value+gradient).  Above it a lane takes each galaxy, whose
-// serial chain of 94 bins, twice, costs the same ~130 us from a few thousand to 65,536 galaxies.
-// Pair / lane kernels, us per call: value+gradient 52 / 139 at 4096, 111 / 133 at 10,240, 131 / 135
-// at 12,288; magnitudes 25 / 69, 53 / 64, 62 / 64; and at 64 galaxies 16 / 770, where a wave of the lane
-// kernel spans all redshift buckets and contracts once for each.
-constexpr int PAIR_MAX_GAL = 10240;
+// Up to PAIR_MAX_GAL galaxies a pair of waves takes each galaxy (k_approx_pair); the chip holds 2048
+// such pairs at a time, ~15 us each round (value+gradient).  Above it a lane takes each galaxy, whose
+// serial chain of 94 bins, twice, costs the same ~135 us from a few thousand to 65,536 galaxies.
+// Pair / lane kernels, us per call: value+gradient 35 / 139 at 4096, 126 / 135 at 16,384, 140 / 139 at
+// 18,432; magnitudes 57 / 64 at 16,384 (log-normal 95 / 101), 63 / 66 at 18,432 (105 / 101); and at 64
+// galaxies 14 / 770, where a wave of the lane kernel spans all redshift buckets, contracting for each.
+constexpr int PAIR_MAX_GAL = 16384;
 
 int launch_approx_ws(sps_ctx *c, hipStream_t s, const ApproxWs &ws, int n, int sfh, int mode, const float *params,
                      const float *z, const float *obs, const float *sigma, const uint8_t *mask, const float *bounds,

@@ -14,7 +14,7 @@ from gpu_common import bounds_prior, dev, f32, gal_inputs, soa
 
 pytestmark = pytest.mark.gpu
 
-PAIR_MAX = 10240            # the batched kernels take over above it
+PAIR_MAX = 16384            # the batched kernels take over above it
 N = PAIR_MAX + 1
 SLICES = [(0, 1), (1, 64), (64, N)]     # a single galaxy, a ragged few, the rest
 
