@@ -230,8 +230,8 @@ void free_ctx(sps_ctx *c) {
     if (c->graph_done) (void)hipEventDestroy(c->graph_done);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     (void)hipFree(c->d_lum64);
-    (void)hipFree(c->d_ls32);
-    (void)hipFree(c->d_lt32);
+    (void)hipFree(c->d_ls_b3);
+    (void)hipFree(c->d_lt_b3);
     (void)hipFree(c->d_ls_bx);
     (void)hipFree(c->d_lt_bx);
     (void)hipFree(c->d_wc);
@@ -513,15 +513,23 @@ int sps_create(sps_ctx **out, int device, const sps_ssp_desc *ssp, const sps_fil
     c->lw = lw;
     const size_t np = (size_t)S_PAD * lw;
     if (prec_mask & (1u << SPS_F32)) {
-        std::vector<float> ls(np, 0.0f), lt(np, 0.0f);
+        std::vector<uint16_t> ls(3 * np, 0), lt(3 * np, 0);
         for (size_t s = 0; s < S; ++s)
             for (int l = 0; l < nw; ++l) {
                 const float f = (float)ssp->lum[s * nw + l];
-                ls[s * lw + l] = f;
-                lt[(size_t)l * S_PAD + s] = f;
+                const uint16_t h = bf16_rne(f);
+                const float r = std::isfinite(f) ? f - bf16_to_f(h) : 0.0f;
+                const uint16_t m = bf16_rne(r), lo = bf16_rne(r - bf16_to_f(m));
+                const size_t a = bf3_at(s, lw, l), b = bf3_at(l, S_PAD, (int)s);
+                ls[a] = h;
+                ls[a + 32] = m;
+                ls[a + 64] = lo;
+                lt[b] = h;
+                lt[b + 32] = m;
+                lt[b + 64] = lo;
             }
-        if ((rc = upload((void **)&c->d_ls32, ls.data(), np * sizeof(float)))) return fail(rc);
-        if ((rc = upload((void **)&c->d_lt32, lt.data(), np * sizeof(float)))) return fail(rc);
+        if ((rc = upload((void **)&c->d_ls_b3, ls.data(), np * 6))) return fail(rc);
+        if ((rc = upload((void **)&c->d_lt_b3, lt.data(), np * 6))) return fail(rc);
     }
     if (prec_mask & (1u << SPS_BF16X)) {
         std::vector<uint16_t> ls_x(2 * np, 0), lt_x(2 * np, 0);

@@ -5,9 +5,9 @@
 //   N[g][b]    = sum_l T_b((1+z_g) l) q_l / l                 (photon-counting AB normaliser)
 //   m[g][b]    = -2.5 log10 K(z_g) - 2.5 log10 M_g - 2.5 log10(num / N)
 //
-// The GEMM runs on MFMA (FP64 16x16x4, FP32 16x16x4, or BF16 16x16x32 with the
-// split W = W_hi + W_lo, L = L_hi + L_lo and three products hi.hi + hi.lo + lo.hi
-// accumulated in FP32).  The attenuation, filter and quadrature weights are
+// The GEMM runs on MFMA (FP64 16x16x4, or BF16 16x16x32 accumulated in FP32: SPS_F32 splits
+// both operands into three BF16 parts, which hold all 24 bits, and takes six products;
+// SPS_BF16X into two, W = W_hi + W_lo, L = L_hi + L_lo, and takes three).  The attenuation, filter and quadrature weights are
 // generated in the epilogue and reduced over each wavelength tile (64 wide on the
 // FP64 path, 128 on the FP32 / BF16X paths) into per-tile partial sums; small
 // kernels finish the sums per galaxy.  The FP32 / BF16X paths skip the wavelength
@@ -53,6 +53,15 @@ __device__ inline uint16_t f2bf(float f) {
     return (uint16_t)(u >> 16);
 }
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+// FP32 as three BF16 values hi + mid + lo: exact (8 + 8 + 8 bits) down to the range of the last; an
+// infinity or NaN is carried by hi alone
+__device__ inline void split3(float v, uint16_t &h, uint16_t &m, uint16_t &l) {
+    h = f2bf(v);
+    const bool fin = (__float_as_uint(v) & 0x7f800000u) != 0x7f800000u;
+    const float r = fin ? v - bf2f(h) : 0.0f;
+    m = f2bf(r);
+    l = f2bf(r - bf2f(m));
+}
 
 __device__ inline float e_exp(float x) { return expf(x); }
 __device__ inline double e_exp(double x) { return exp(x); }
@@ -273,25 +282,30 @@ __global__ void __launch_bounds__(256) k_exact_gemm(GemmArgs a) {
 // C = A . B^T with A [M][K] and B [N][K], both k-contiguous (row strides lda, ldb), K a
 // multiple of 32, N a multiple of 128, A allocated to a multiple of 128 rows.  Block tile
 // 128 x 128, 256 threads as 2 x 2 waves of 64 x 64 (4 x 4 MFMA tiles of 16 x 16); k-tiles
-// of 32 staged through LDS with double buffering (the next tile's global loads are in
-// flight while the current tile's products issue).  LDS rows are 144 bytes: 32 FP32, or
-// 32 BF16 hi then 32 BF16 lo, then padding.
-//   FP32: v_mfma_f32_16x16x4f32.  The four k-slots of one product are taken as
-//         k = 4 (l / 16) + s in step s, so one 16-byte LDS read per lane feeds four steps.
-//   BF16X: v_mfma_f32_16x16x32_bf16, lane l supplying k = 8 (l / 16) .. + 7; three products
-//         lo.hi + hi.lo + hi.hi per tile pair, FP32 accumulation.
+// of 32 staged through LDS (the next tile's global loads are in flight while the current tile's
+// products issue).  Both precisions run on v_mfma_f32_16x16x32_bf16, lane l supplying k =
+// 8 (l / 16) .. + 7, with FP32 accumulation, the operands split into XP BF16 parts that lie
+// side by side per 32-element k chunk (bfx_at, bf3_at), so a k-tile of a row is XP 64-byte runs:
+//   FP32:  hi + mid + lo, which hold all 24 bits; six products lo.hi + hi.lo + mid.mid + mid.hi +
+//          hi.mid + hi.hi per tile pair (the three dropped ones are below 2^-26 of the product).
+//          v_mfma_f32_16x16x4f32 takes 32 cycles for 4 k, these six 96 for 32: the GEMMs at 4096 x
+//          5000 took 378 (forward) and 373 us (gradient) on the former.
+//   BF16X: hi + lo; three products lo.hi + hi.lo + hi.hi.
+// LDS rows carry 16 bytes of padding, which spreads a fragment read's 16 rows over the banks.
 // Blocks are mapped XCD-aware: consecutive dispatch slots go round-robin over the 8 XCDs, so
 // slot b is remapped to tile (b % 8) * T / 8 + b / 8 and each XCD works through one
 // contiguous run of tiles, M fastest (its A rows stay in that XCD's L2), or N fastest where
 // whole wavelength tiles are skipped (see XArgs::win), so the skipped ones spread evenly.
-constexpr int XBM = 128, XBN = 128, XBK = 32, XROW = 144;   // XROW in bytes
-constexpr int XSTAGE = (XBM + XBN) * XROW;                   // 36,864 bytes per stage
+constexpr int XBM = 128, XBN = 128, XBK = 32;
+template <int P> constexpr int x_parts() { return P == SPS_F32 ? 3 : 2; }
+template <int P> constexpr int x_row() { return 64 * x_parts<P>() + 16; }            // bytes per LDS row
+template <int P> constexpr int x_stage() { return (XBM + XBN) * x_row<P>(); }        // 53,248 or 36,864 bytes
 constexpr int XSPLIT = 4;                                    // K ranges of the gradient GEMM
 constexpr int XBAND = 8;                                     // row tiles per band (tile order 3)
 
 struct XArgs {
     int M, N, K;
-    const void *A;             // FP32 [M][lda], or BF16 hi + lo interleaved [M][2 lda] (bfx_at)
+    const void *A;             // BF16 parts interleaved, [M][3 lda] (bf3_at) or [M][2 lda] (bfx_at)
     int lda;
     const void *B;             // likewise [N][ldb]
     int ldb;
@@ -319,49 +333,42 @@ struct XArgs {
     int order, xcd;
 };
 
+// a k-tile of both operand tiles: 16-byte chunks, XCH per row; thread t takes chunks t + 256 c of A
+// for c < XCH / 2 and of B after that, in the LDS row order
+template <int P> constexpr int x_chunks() { return 4 * x_parts<P>(); }
 template <int P>
-__device__ inline void x_load(const XArgs &a, int tile_m, int tile_n, int k0, int tid, v4f (&r)[8]) {
-    // 8 chunks of 16 bytes per thread: chunks 0..3 of A, 4..7 of B; chunk c of an operand
-    // tile covers row (tid + 256 c) / 8 ... see x_store for the matching placement
+__device__ inline void x_load(const XArgs &a, int tile_m, int tile_n, int k0, int tid, v4f (&r)[x_chunks<P>()]) {
+    constexpr int XCH = x_chunks<P>(), PARTS = x_parts<P>();
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const int e = tid + 256 * (c & 3);      // 0..1023 within the operand tile
-        const int row = e >> 3, q = e & 7;       // 8 chunks of 16 B per row
-        const bool isA = c < 4;
+    for (int c = 0; c < XCH; ++c) {
+        const bool isA = c < XCH / 2;
+        const int e = tid + 256 * (c % (XCH / 2)), row = e / XCH, q = e % XCH;
+        const uint16_t *base = (const uint16_t *)(isA ? a.A : a.B);
         const int ld = isA ? a.lda : a.ldb;
         const size_t grow = (size_t)(isA ? tile_m : tile_n) + row;
-        if constexpr (P == SPS_F32) {
-            const float *base = (const float *)(isA ? a.A : a.B);
-            r[c] = *(const v4f *)(base + grow * ld + k0 + 4 * q);
-        } else {
-            // interleaved hi / lo rows: the k-tile's 32 hi then 32 lo are one 128-byte line,
-            // chunks q < 4 hi and q >= 4 lo, in the LDS row order
-            const uint16_t *base = (const uint16_t *)(isA ? a.A : a.B);
-            r[c] = *(const v4f *)(base + grow * 2 * ld + 2 * k0 + 8 * q);
-        }
+        r[c] = *(const v4f *)(base + grow * PARTS * ld + PARTS * k0 + 8 * q);
     }
 }
 
-__device__ inline void x_store(char *stage, int tid, const v4f (&r)[8]) {
+template <int P>
+__device__ inline void x_store(char *stage, int tid, const v4f (&r)[x_chunks<P>()]) {
+    constexpr int XCH = x_chunks<P>();
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const int e = tid + 256 * (c & 3);
-        const int row = e >> 3, q = e & 7;
-        const int orow = (c < 4) ? row : XBM + row;
-        *(v4f *)(stage + orow * XROW + 16 * q) = r[c];
+    for (int c = 0; c < XCH; ++c) {
+        const int e = tid + 256 * (c % (XCH / 2)), row = e / XCH, q = e % XCH;
+        const int orow = (c < XCH / 2) ? row : XBM + row;
+        *(v4f *)(stage + orow * x_row<P>() + 16 * q) = r[c];
     }
 }
 
-// LDS stages: FP32 double-buffers through registers (two blocks per CU); BF16X, whose MFMA
-// phase per k-tile is a quarter as long, runs one register-staged stage with three blocks per
-// CU (RING = false), or (RING = true, a launch choice) a ring of two stages filled by direct
-// global-to-LDS loads, which need no staging registers, with two blocks per CU.  The two BF16X
-// forms multiply the same tiles in the same order (the same bits); which is faster depends on
-// the shape (sps_autotune_exact).
-template <int P> constexpr int x_nstage() { return P == SPS_BF16X ? 1 : 2; }
+// LDS stages: one register-staged stage, with three blocks per CU for BF16X and two for FP32 (whose
+// products per k-tile take twice as long); or for BF16X (RING = true, a launch choice) a ring of two
+// stages filled by direct global-to-LDS loads, which need no staging registers, with two blocks
+// per CU.  The two BF16X forms multiply the same tiles in the same order (the same bits); which is
+// faster depends on the shape (sps_autotune_exact).
 constexpr int RSTAGES = 2;
 constexpr int RSTAGE = 2 * XBM * 128;   // A then B rows, 128 bytes (the k-tile's 32 hi + 32 lo) each
-template <int P, bool RING> constexpr int x_smem() { return RING ? RSTAGES * RSTAGE : x_nstage<P>() * XSTAGE; }
+template <int P, bool RING> constexpr int x_smem() { return RING ? RSTAGES * RSTAGE : x_stage<P>(); }
 template <int P, bool RING> constexpr int x_blocks() { return RING ? 2 : (P == SPS_BF16X ? 3 : 2); }
 
 #define SPS_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
@@ -398,7 +405,6 @@ __device__ inline void x_ring_issue(const XRing &r, char *stage, int k0, int wav
 template <int P, int EPI, bool RING>
 __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
     static_assert(!RING || P == SPS_BF16X, "the ring form is the BF16X kernel's");
-    constexpr int NST = x_nstage<P>();
     __shared__ __attribute__((aligned(16))) char smem[x_smem<P, RING>()];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int wm = wave >> 1, wn = wave & 1;
@@ -496,57 +502,50 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
         }
         __syncthreads();   // every wave is done with the ring before the epilogue reuses it
     } else {
-    v4f r[8];
+    constexpr int XROW = x_row<P>(), PARTS = x_parts<P>();
+    v4f r[x_chunks<P>()];
     x_load<P>(a, tile_m, tile_n, kbeg, tid, r);
-    x_store(smem, tid, r);
+    x_store<P>(smem, tid, r);
     __syncthreads();
     for (int kt = 0; kt < nk; ++kt) {
-        char *cur = smem + (NST == 2 ? (kt & 1) * XSTAGE : 0);
         if (kt + 1 < nk) x_load<P>(a, tile_m, tile_n, kbeg + (kt + 1) * XBK, tid, r);
-        const char *As = cur, *Bs = cur + XBM * XROW;
+        const char *Ar = smem + (wm * 64 + li) * XROW + 16 * lk, *Br = smem + (XBM + wn * 64 + li) * XROW + 16 * lk;
+        b8v af[PARTS][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int p = 0; p < PARTS; ++p) af[p][i] = *(const b8v *)(Ar + i * 16 * XROW + 64 * p);
         if constexpr (P == SPS_F32) {
 #pragma unroll
-            for (int g = 0; g < 2; ++g) {   // two groups of 16 k
-                v4f af[4], bf[4];
+            for (int j = 0; j < 4; ++j) {
+                b8v bf[PARTS];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    af[i] = *(const v4f *)(As + (wm * 64 + i * 16 + li) * XROW + 64 * g + 16 * lk);
-                    bf[i] = *(const v4f *)(Bs + (wn * 64 + i * 16 + li) * XROW + 64 * g + 16 * lk);
-                }
+                for (int p = 0; p < PARTS; ++p) bf[p] = *(const b8v *)(Br + j * 16 * XROW + 64 * p);
+                constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};   // small products first
 #pragma unroll
-                for (int st = 0; st < 4; ++st)
+                for (int t = 0; t < 6; ++t)
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i][st], bf[j][st], acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[PA[t]][i], bf[PB[t]], acc[i][j], 0, 0, 0);
             }
         } else {
-            b8v ah[4], al[4], bh[4], bl[4];
+            b8v bh[4], bl[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const char *ar = As + (wm * 64 + i * 16 + li) * XROW + 16 * lk;
-                const char *br = Bs + (wn * 64 + i * 16 + li) * XROW + 16 * lk;
-                ah[i] = *(const b8v *)ar;
-                al[i] = *(const b8v *)(ar + 64);
-                bh[i] = *(const b8v *)br;
-                bl[i] = *(const b8v *)(br + 64);
+                bh[i] = *(const b8v *)(Br + i * 16 * XROW);
+                bl[i] = *(const b8v *)(Br + i * 16 * XROW + 64);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh[j], acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl[j], acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh[j], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[1][i], bh[j], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[0][i], bl[j], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[0][i], bh[j], acc[i][j], 0, 0, 0);
                 }
         }
-        if constexpr (NST == 2) {
-            if (kt + 1 < nk) x_store(smem + ((kt + 1) & 1) * XSTAGE, tid, r);
-        } else {
-            __syncthreads();   // every wave is done with the stage before it is refilled
-            if (kt + 1 < nk) x_store(smem, tid, r);
-        }
+        __syncthreads();   // every wave is done with the stage before it is refilled
+        if (kt + 1 < nk) x_store<P>(smem, tid, r);
         __syncthreads();
     }
     }
@@ -784,7 +783,7 @@ __global__ void __launch_bounds__(64) k_exact_pw(DevConsts k, int n, int sfh, co
 // weights rows W[g][s] = P_Z(j) P_age(i), s = j NA + i, zero for s >= NSSP.  A block takes
 // XG galaxies: their P_age and P_Z columns (galaxy-contiguous in pw) are staged in LDS, one row
 // of factors per galaxy, then the rows are written with consecutive threads on consecutive
-// pairs of s (whole lines; a pair is one 8-byte FP32 or two 4-byte BF16 stores, and never
+// pairs of s (whole lines; a pair is one 4-byte store per BF16 part, and never
 // straddles a metallicity, the padding or a 32-element chunk, NA, NSSP and S_PAD being even).
 // The lanes of a wave read consecutive pairs of one galaxy's row, and the staging writes of
 // consecutive galaxies fall in different banks (row length 106 words).
@@ -812,7 +811,13 @@ __global__ void __launch_bounds__(256) k_expand(int n, const float *pw, void *w)
             v1 = pzj * pa.y;
         }
         if constexpr (P == SPS_F32) {
-            *(float2 *)((float *)w + (size_t)g * S_PAD + sidx) = make_float2(v0, v1);
+            uint16_t h0, m0, l0, h1, m1, l1;
+            split3(v0, h0, m0, l0);
+            split3(v1, h1, m1, l1);
+            uint16_t *o = (uint16_t *)w + bf3_at(g, S_PAD, sidx);   // even
+            *(uint32_t *)o = (uint32_t)h0 | ((uint32_t)h1 << 16);
+            *(uint32_t *)(o + 32) = (uint32_t)m0 | ((uint32_t)m1 << 16);
+            *(uint32_t *)(o + 64) = (uint32_t)l0 | ((uint32_t)l1 << 16);
         } else {
             const uint16_t h0 = f2bf(v0), h1 = f2bf(v1);
             const uint16_t l0 = f2bf(v0 - bf2f(h0)), l1 = f2bf(v1 - bf2f(h1));
@@ -971,7 +976,8 @@ __global__ void __launch_bounds__(256) k_exact_rbar(int n, int n_wave, int ld, i
                     }
                 }
                 if (P == SPS_F32) {
-                    ((float *)rb)[(size_t)g * ld + l] = v;
+                    uint16_t *o = (uint16_t *)rb + bf3_at(g, ld, l);
+                    split3(v, o[0], o[32], o[64]);
                 } else {
                     const uint16_t h = f2bf(v);
                     const size_t o = bfx_at(g, ld, l);   // interleaved hi / lo rows
@@ -1173,8 +1179,8 @@ static ExactLayout exact_layout(const sps_ctx *c, int n, int prec, bool logl, bo
     const bool want_grad = logl && grad;
     const int npart = (want_grad ? 5 : 2) * nb;
     const int esz = f64 ? 8 : 4;
-    const int tsz = f64 ? 8 : (prec == SPS_F32 ? 4 : 2);
-    const int nsplit = (prec == SPS_BF16X) ? 2 : 1;
+    const int tsz = f64 ? 8 : 2;   // a GEMM operand's element: FP64, or BF16 parts
+    const int nsplit = f64 ? 1 : (prec == SPS_F32 ? 3 : 2);
     ExactLayout L;
     size_t off = 0;
     auto carve = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
@@ -1225,7 +1231,7 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
                                           " (call sps_reserve_exact)");
     char *W = (char *)c->d_work;
     int4 *win = nullptr;   // filter-support windows of the row tiles (FP32 / BF16X paths)
-    void *w_hi = W + o_w;   // weights rows: FP32 [mp][S_PAD], or BF16 hi + lo interleaved [mp][2 S_PAD]
+    void *w_hi = W + o_w;   // weights rows: FP64 [n][S_PAD], or BF16 parts interleaved [mp][3 or 2 S_PAD]
 
     float *pw = f64 ? nullptr : (float *)(W + o_pw);
     if (f64) {
@@ -1282,7 +1288,7 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
         a.K = S_PAD;
         a.A = w_hi;
         a.lda = S_PAD;
-        a.B = (prec == SPS_F32) ? (const void *)c->d_lt32 : (const void *)c->d_lt_bx;
+        a.B = (prec == SPS_F32) ? (const void *)c->d_lt_b3 : (const void *)c->d_lt_bx;
         a.ldb = S_PAD;
         a.n_mt = mp / XBM;
         a.n_nt = lw / XBN;
@@ -1336,7 +1342,7 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
             break;
     }
     if (want_grad) {
-        void *r_hi = W + o_rb;   // Rbar rows: FP32 [mp][lw], or BF16 hi + lo interleaved [mp][2 lw]
+        void *r_hi = W + o_rb;   // Rbar rows: BF16 parts interleaved [mp][3 or 2 lw]
         const bool big = n >= RBAR_BIG_MIN_GAL;
         dim3 gr(big ? (n + RBAR_G_BIG - 1) / RBAR_G_BIG : n), br(256);
         const FiltConst fl = filt_const(c->h_fc, c->h_fs);
@@ -1351,7 +1357,7 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
         b.K = lw;
         b.A = r_hi;
         b.lda = lw;
-        b.B = (prec == SPS_F32) ? (const void *)c->d_ls32 : (const void *)c->d_ls_bx;
+        b.B = (prec == SPS_F32) ? (const void *)c->d_ls_b3 : (const void *)c->d_ls_bx;
         b.ldb = lw;
         b.n_mt = mp / XBM;
         b.n_nt = S_PAD / XBN;

@@ -36,6 +36,10 @@ constexpr int S_PAD = 1152;       // SSP rows padded to a multiple of 128
 __host__ __device__ inline size_t bfx_at(size_t r, int ld, int k) {
     return r * 2 * (size_t)ld + 64 * (size_t)(k >> 5) + (size_t)(k & 31);
 }
+// the same for three parts: hi here, mid 32 further on, lo 64
+__host__ __device__ inline size_t bf3_at(size_t r, int ld, int k) {
+    return r * 3 * (size_t)ld + 96 * (size_t)(k >> 5) + (size_t)(k & 31);
+}
 
 // Kernel-facing constants, passed by value (kernarg segment).
 struct DevConsts {
@@ -74,12 +78,12 @@ struct sps_ctx {
     double h_fc[SPS_MAX_BAND] = {0}, h_fs[SPS_MAX_BAND] = {0};   // filter constants (FP64)
     // device tables
     double *d_lum64 = nullptr;     // [S][n_wave]
-    // FP32 / BF16 hi+lo copies for the matrix-core GEMMs, zero-padded to S_PAD SSP rows and
+    // FP32 (in three BF16 parts) and BF16 hi+lo copies for the matrix-core GEMMs, zero-padded to S_PAD SSP rows and
     // LW = round_up(n_wave, 128) wavelengths, in both orientations (k contiguous):
     //   ls: [S_PAD][LW]  (B of the gradient GEMM, k = wavelength)
     //   lt: [LW][S_PAD]  (B of the forward GEMM, k = SSP)
     int lw = 0;
-    float *d_ls32 = nullptr, *d_lt32 = nullptr;
+    uint16_t *d_ls_b3 = nullptr, *d_lt_b3 = nullptr;   // FP32 as BF16 hi + mid + lo, interleaved (bf3_at)
     uint16_t *d_ls_bx = nullptr, *d_lt_bx = nullptr;   // BF16 hi + lo, interleaved (bfx_at)
     float *d_wc = nullptr;         // per wavelength [LW][4]: ln(l / 5500 A), l q_l, q_l / l, 0
     double *d_wave = nullptr, *d_trap = nullptr;
