@@ -17,13 +17,12 @@
 // approximate path; dust derivatives come from extra epilogue partials.
 #include <type_traits>
 
-#include "sps_eval.h"
+#include "sps_pair.h"
 
 namespace sps {
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef double d4v __attribute__((ext_vector_type(4)));
-typedef __bf16 b8v __attribute__((ext_vector_type(8)));
 
 constexpr int BM = 64, BN = 64;
 constexpr int NSSP = NZ * NA;
@@ -46,12 +45,7 @@ template <> struct Prec<SPS_BF16X> {
     static constexpr int BK = 64, PAD = 8, KSTEP = 32;
 };
 
-__device__ inline uint16_t f2bf(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
+__device__ inline uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }   // nearest even
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 // FP32 as three BF16 values hi + mid + lo: exact (8 + 8 + 8 bits) down to the range of the last; an
 // infinity or NaN is carried by hi alone
@@ -300,7 +294,9 @@ constexpr int XBM = 128, XBN = 128, XBK = 32;
 template <int P> constexpr int x_parts() { return P == SPS_F32 ? 3 : 2; }
 template <int P> constexpr int x_row() { return 64 * x_parts<P>() + 16; }            // bytes per LDS row
 template <int P> constexpr int x_stage() { return (XBM + XBN) * x_row<P>(); }        // 53,248 or 36,864 bytes
-constexpr int XSPLIT = 4;                                    // K ranges of the gradient GEMM
+// K ranges of the gradient GEMM: its n/128 x 9 output tiles are split so that about XSPLIT_BLOCKS blocks
+// run (three fit on a CU), each taking an equal part of its row tile's window
+constexpr int XSPLIT_MAX = 8, XSPLIT_BLOCKS = 640;
 constexpr int XBAND = 8;                                     // row tiles per band (tile order 3)
 
 struct XArgs {
@@ -314,7 +310,7 @@ struct XArgs {
     size_t c_split;            // floats between the partial C of consecutive K ranges
     float *C;                  // EPI_STORE: transposed, [n_store][ldc] (ldc >= 128-padded M)
     int ldc, n_store;
-    const float *params, *z;   // photometry epilogue
+    const float *dust, *z;     // photometry epilogue: tau_V, delta, F_floor [3][M] and z
     const double *wave;
     const float *wc;           // [N][4]: ln(l / 5500), l q, q / l, l
     int n_wave, n_band;
@@ -440,19 +436,19 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
         tile_m = (nfast ? t / a.n_nt : t % a.n_mt) * XBM;
         tile_n = (nfast ? t % a.n_nt : t / a.n_mt) * XBN;
     }
-    int klen = a.K / nsp, kbeg = sp * klen;
+    int klen = a.K, kbeg = 0;
     if (a.win) {
         // wavelengths outside every band's support for all of this tile's galaxies: the
         // forward tile's band sums are below exp(-32) of the band's: the tile is not computed
-        // and the tile sum (k_sum_tiles) skips it; the gradient GEMM's Rbar is exactly zero
-        // there, so its K range is clipped
+        // and the tile sum (k_exact_finish) skips it; the gradient GEMM's Rbar is exactly zero
+        // there, so its K range is the window's
         const int4 w = a.win[tile_m / XBM];
         if constexpr (EPI == EPI_STORE) {
-            const int k0 = max(kbeg, w.z * XBK), k1 = min(kbeg + klen, w.w * XBK);
-            kbeg = k0;
-            klen = max(k1 - k0, 0);
+            const int nk_w = max(w.w - w.z, 0), k0 = w.z + nk_w * sp / nsp, k1 = w.z + nk_w * (sp + 1) / nsp;
+            kbeg = k0 * XBK;
+            klen = (k1 - k0) * XBK;
         } else if (tile_n / XBN < w.x || tile_n / XBN >= w.y) {
-            return;   // k_sum_tiles reads only the tiles inside the window
+            return;   // k_exact_finish reads only the tiles inside the window
         }
     }
 
@@ -581,8 +577,7 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
 #pragma unroll
             for (int q = 0; q < NPB; ++q) accp[bb][q] = 0.0f;
         const int gg = g < a.M ? g : a.M - 1;
-        const float tauv = a.params[(size_t)7 * a.M + gg], delta = a.params[(size_t)8 * a.M + gg];
-        const float ffl = a.params[(size_t)9 * a.M + gg];
+        const float tauv = a.dust[gg], delta = a.dust[(size_t)a.M + gg], ffl = a.dust[(size_t)2 * a.M + gg];
         const double opz = 1.0 + (double)a.z[gg];
         // the galaxy's filter offsets as one FP32 FMA per band and wavelength: t = l ta_b + tc_b
         // = x_b sqrt(log2(e) / 2) with x_b = ((1+z) l - c_b) / s_b, so T_b = exp2(-t^2); the
@@ -740,18 +735,15 @@ __global__ void __launch_bounds__(64) k_exact_weights64(DevConsts k, int n, int 
     for (int s = NSSP + lane; s < S_PAD; s += 64) w[s] = 0.0;
 }
 
-// ------------------------------------------------------------------ FP32 / BF16X weights, GPL lanes per galaxy
-// GPL adjacent lanes share a galaxy (and its LDS column) and split its age bins: eight for
-// batches of a few thousand galaxies (too few waves for fewer lanes per galaxy), two from
-// GPL_BIG_N on (more galaxies per wave, fewer group sums: the exact HMC's weights kernels
-// 3 % of its iteration faster; eight are 10 % faster at 4096 galaxies).
+// ------------------------------------------------------------------ FP32 / BF16X weights, large batches
+// From GPL_BIG_N galaxies on, GPL adjacent lanes share a galaxy (and its LDS column) and split its age
+// bins; below, a wave takes each galaxy (k_exact_weights).
 // Per-galaxy results, SoA [slot][n]: slots 0..93 P_age, 96..107 P_Z, 108/109 the FP64 total
 // smooth mass (low/high words), 110 the burst normaliser, 111 log10 t_obs, 112 the first
 // burst bin (int bits).
 constexpr int PW_SLOTS = 128, PW_PZ = 96, PW_S = 108, PW_ZB = 110, PW_LOBS = 111, PW_I0 = 112;
-constexpr int GPL_BIG_N = 16384;
+constexpr int GPL_BIG_N = 16384, GPL = 2;
 
-template <int GPL>
 __global__ void __launch_bounds__(64) k_exact_pw(DevConsts k, int n, int sfh, const float *params, const float *z,
                                                  float *pw) {
     __shared__ float lds[LDS_SLOTS * (64 / GPL)];
@@ -789,6 +781,34 @@ __global__ void __launch_bounds__(64) k_exact_pw(DevConsts k, int n, int sfh, co
 // consecutive galaxies fall in different banks (row length 106 words).
 constexpr int XG = 16, XROWF = NA + NZ;
 static_assert(NA % 2 == 0 && NSSP % 2 == 0 && S_PAD % 2 == 0 && XROWF % 2 == 0, "pairs of SSPs");
+// elements sidx, sidx + 1 of row g from its factors (P_age, then P_Z)
+template <int P>
+__device__ inline void expand_pair(const float *f, int sidx, size_t g, void *w) {
+    float v0 = 0.0f, v1 = 0.0f;
+    if (sidx < NSSP) {
+        const int j = sidx / NA, i = sidx - j * NA;
+        const float pzj = f[NA + j];
+        const float2 pa = *(const float2 *)&f[i];
+        v0 = pzj * pa.x;
+        v1 = pzj * pa.y;
+    }
+    if constexpr (P == SPS_F32) {
+        uint16_t h0, m0, l0, h1, m1, l1;
+        split3(v0, h0, m0, l0);
+        split3(v1, h1, m1, l1);
+        uint16_t *o = (uint16_t *)w + bf3_at(g, S_PAD, sidx);   // even
+        *(uint32_t *)o = (uint32_t)h0 | ((uint32_t)h1 << 16);
+        *(uint32_t *)(o + 32) = (uint32_t)m0 | ((uint32_t)m1 << 16);
+        *(uint32_t *)(o + 64) = (uint32_t)l0 | ((uint32_t)l1 << 16);
+    } else {
+        const uint16_t h0 = f2bf(v0), h1 = f2bf(v1);
+        const uint16_t l0 = f2bf(v0 - bf2f(h0)), l1 = f2bf(v1 - bf2f(h1));
+        uint16_t *o = (uint16_t *)w + bfx_at(g, S_PAD, sidx);
+        *(uint32_t *)o = (uint32_t)h0 | ((uint32_t)h1 << 16);
+        *(uint32_t *)(o + 32) = (uint32_t)l0 | ((uint32_t)l1 << 16);
+    }
+}
+
 template <int P>
 __global__ void __launch_bounds__(256) k_expand(int n, const float *pw, void *w) {
     __shared__ __attribute__((aligned(8))) float sp[XG][XROWF];
@@ -801,100 +821,95 @@ __global__ void __launch_bounds__(256) k_expand(int n, const float *pw, void *w)
     const int ng = min(XG, n - g0);
     constexpr int HP = S_PAD / 2;
     for (int e = tid; e < ng * HP; e += 256) {
-        const int t = e / HP, sidx = 2 * (e - t * HP), g = g0 + t;
-        float v0 = 0.0f, v1 = 0.0f;
-        if (sidx < NSSP) {
-            const int j = sidx / NA, i = sidx - j * NA;
-            const float pzj = sp[t][NA + j];
-            const float2 pa = *(const float2 *)&sp[t][i];
-            v0 = pzj * pa.x;
-            v1 = pzj * pa.y;
-        }
-        if constexpr (P == SPS_F32) {
-            uint16_t h0, m0, l0, h1, m1, l1;
-            split3(v0, h0, m0, l0);
-            split3(v1, h1, m1, l1);
-            uint16_t *o = (uint16_t *)w + bf3_at(g, S_PAD, sidx);   // even
-            *(uint32_t *)o = (uint32_t)h0 | ((uint32_t)h1 << 16);
-            *(uint32_t *)(o + 32) = (uint32_t)m0 | ((uint32_t)m1 << 16);
-            *(uint32_t *)(o + 64) = (uint32_t)l0 | ((uint32_t)l1 << 16);
-        } else {
-            const uint16_t h0 = f2bf(v0), h1 = f2bf(v1);
-            const uint16_t l0 = f2bf(v0 - bf2f(h0)), l1 = f2bf(v1 - bf2f(h1));
-            const size_t o = bfx_at(g, S_PAD, sidx);   // interleaved hi / lo rows; o is even
-            *(uint32_t *)((uint16_t *)w + o) = (uint32_t)h0 | ((uint32_t)h1 << 16);
-            *(uint32_t *)((uint16_t *)w + o + 32) = (uint32_t)l0 | ((uint32_t)l1 << 16);
-        }
+        const int t = e / HP;
+        expand_pair<P>(sp[t], 2 * (e - t * HP), (size_t)(g0 + t), w);
     }
 }
 
 // ------------------------------------------------------------------ finish: magnitudes / likelihood
-template <int P>
-__global__ void k_exact_finish(DevConsts k, int n, int n_tiles, const void *params_v, const void *z_v,
-                               const void *part_v, int npart, void *mag_v, const float *obs, const float *sigma,
-                               const uint8_t *mask, float *logl, float *grad, float *cnum, int vjp) {
-    typedef typename Prec<P>::E E;
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+// FP64 path: magnitudes from the summed partials [g][quantity]
+__global__ void __launch_bounds__(128) k_exact_finish64(DevConsts k, int n, const double *params, const double *z,
+                                                        const double *part, int npart, double *mag) {
+    const int g = blockIdx.x * blockDim.x + threadIdx.x, nb = k.n_band;
     if (g >= n) return;
-    const int nb = k.n_band;
-    const E *prm = (const E *)params_v;
-    const double zf = (double)((const E *)z_v)[g];
-    const double m0 = mag_offset(k, zf) - 2.5 * (double)prm[g];
-    const E *part = (const E *)part_v;
-    double num[NB_MAX], nrm[NB_MAX], dd[3][NB_MAX];
-    for (int b = 0; b < nb; ++b) {
-        num[b] = nrm[b] = dd[0][b] = dd[1][b] = dd[2][b] = 0.0;
-        for (int t = 0; t < n_tiles; ++t) {
-            // FP64 partials are [tile][galaxy][quantity]; FP32 ones [tile][quantity][galaxy]
-            const E *pp = (P == SPS_F64) ? part + ((size_t)t * n + g) * npart : part + (size_t)t * npart * n + g;
-            const size_t st = (P == SPS_F64) ? 1 : (size_t)n;
-            num[b] += (double)pp[b * st];
-            nrm[b] += (double)pp[(nb + b) * st];
-            if (grad) {
-                dd[0][b] += (double)pp[(2 * nb + b) * st];
-                dd[1][b] += (double)pp[(3 * nb + b) * st];
-                dd[2][b] += (double)pp[(4 * nb + b) * st];
-            }
+    const double m0 = mag_offset(k, z[g]) - 2.5 * params[g];
+    const double *pp = part + (size_t)g * npart;
+    for (int b = 0; b < nb; ++b) mag[(size_t)g * nb + b] = m0 - 2.5 * log10(pp[b] / pp[nb + b]);
+}
+
+// FP32 / BF16X: the photometry partials [tile][quantity][rank] summed over the wavelength tiles of the
+// row tile's window (the forward GEMM writes none outside it), then magnitudes, or log L (vjp: the
+// caller's adjoints obs = dL/dm_b take the place of the residuals), the mass and dust derivatives and
+// dlogL/dnum.  Eight lanes per galaxy, a band each; perm: the caller's index of a rank (null: the same).
+// A block's 32 galaxies share a row tile.  One thread per galaxy and a pass of its own for the tile sums
+// took 28 + 9 us at 4096 galaxies.
+template <bool GRAD>
+__global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_tiles, const int *perm,
+                                                      const float *params, const float *z, const int4 *win,
+                                                      const float *part, int npart, float *mag, const float *obs,
+                                                      const float *sigma, const uint8_t *mask, float *logl,
+                                                      float *grad, float *cnum, int vjp) {
+    static_assert(NB_MAX == 8, "a lane per band");
+    const int r = blockIdx.x * 32 + (threadIdx.x >> 3), b = threadIdx.x & 7, nb = k.n_band;
+    const bool valid = r < n, act = b < nb;
+    const int rr = min(r, n - 1), g = perm ? perm[rr] : rr, bb = min(b, nb - 1);
+    static_assert(XBM % 32 == 0, "a block's galaxies lie in one row tile");
+    const int4 w = win[blockIdx.x * 32 / XBM];
+    constexpr int NQ = GRAD ? 5 : 2;
+    float v[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    const float *pp = part + (size_t)bb * n + rr;
+    const size_t qs = (size_t)nb * n, ts = (size_t)npart * n;
+    const int t_end = min(w.y, n_tiles);
+#pragma unroll 4
+    for (int t = w.x; t < t_end; ++t) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) v[q] += pp[t * ts + q * qs];
+    }
+    // the distance integral's nodes split over the eight lanes (mag_offset)
+    const double zf = (double)z[rr];
+    double chi = 0.0;
+    const double ol = 1.0 - k.om, h = 0.5 * zf;
+#pragma unroll
+    for (int i = 0; i < NGL_DL; i += 8) {
+        if (i + b < NGL_DL) {
+            const double ep = 1.0 + h + h * k.gl_x[i + b], em = 1.0 + h - h * k.gl_x[i + b];
+            chi += k.gl_w[i + b] * (1.0 / sqrt(k.om * ep * ep * ep + ol) + 1.0 / sqrt(k.om * em * em * em + ol));
         }
     }
-    if (mag_v) {
-        for (int b = 0; b < nb; ++b) {
-            const double m = m0 - 2.5 * log10(num[b] / nrm[b]);
-            if (P == SPS_F64) ((double *)mag_v)[(size_t)g * nb + b] = m;
-            else ((float *)mag_v)[(size_t)g * nb + b] = (float)m;
-        }
+    chi = group_sum<8>(chi);
+    const double dl = (1.0 + zf) * k.dh_cm * h * chi;
+    const double m0 = -2.5 * log10((1.0 + zf) * k.kfac) + 5.0 * log10(dl) - 2.5 * (double)params[g];
+    const double num = v[0], m = m0 - 2.5 * log10(num / (double)v[1]);
+    if (mag) {
+        if (valid && act) mag[(size_t)g * nb + b] = (float)m;
         return;
     }
-    double ll = 0.0, g0 = 0.0, g7 = 0.0, g8 = 0.0, g9 = 0.0;
-    // vjp: obs holds the caller's adjoints dL/dm_b (every band), in place of observations
     const uint32_t mk = (vjp || !mask) ? 0xffffffffu : mask[g];
-    for (int b = 0; b < nb; ++b) {
-        double cb = 0.0;
-        if ((mk >> b) & 1u) {
-            double gm;   // d logL / d m_b
-            if (vjp) {
-                gm = (double)obs[(size_t)g * nb + b];
-            } else {
-                const double m = m0 - 2.5 * log10(num[b] / nrm[b]);
-                const double s = sigma[(size_t)g * nb + b], r = (m - (double)obs[(size_t)g * nb + b]) / s;
-                ll += -0.5 * r * r - log(s * 2.5066282746310002);
-                gm = -r / s;
-            }
-            g0 += -2.5 * gm;
-            cb = gm * (-2.5 / 2.302585092994046) / num[b];   // d logL / d num_b
-            g7 += cb * dd[0][b];
-            g8 += cb * dd[1][b];
-            g9 += cb * dd[2][b];
+    double ll = 0.0, g0 = 0.0, g7 = 0.0, g8 = 0.0, g9 = 0.0, cb = 0.0;
+    if (act && ((mk >> b) & 1u)) {
+        double gm;   // d logL / d m_b
+        if (vjp) {
+            gm = (double)obs[(size_t)g * nb + b];
+        } else {
+            const double s = sigma[(size_t)g * nb + b], res = (m - (double)obs[(size_t)g * nb + b]) / s;
+            ll = -0.5 * res * res - log(s * 2.5066282746310002);
+            gm = -res / s;
         }
-        if (cnum) cnum[(size_t)g * NB_MAX + b] = (float)cb;
+        g0 = -2.5 * gm;
+        cb = gm * (-2.5 / 2.302585092994046) / num;   // d logL / d num_b
+        g7 = cb * (double)v[2];
+        g8 = cb * (double)v[3];
+        g9 = cb * (double)v[4];
     }
-    if (logl) logl[g] = (float)ll;
-    if (grad) {
-        grad[(size_t)0 * n + g] = (float)g0;
-        grad[(size_t)7 * n + g] = (float)g7;
-        grad[(size_t)8 * n + g] = (float)g8;
-        grad[(size_t)9 * n + g] = (float)g9;
-    }
+    if (valid && cnum) cnum[(size_t)r * NB_MAX + b] = (float)cb;
+    ll = group_sum<8>(ll);
+    if (logl && valid && b == 0) logl[g] = (float)ll;
+    if (!GRAD) return;
+    g0 = group_sum<8>(g0);
+    g7 = group_sum<8>(g7);
+    g8 = group_sum<8>(g8);
+    g9 = group_sum<8>(g9);
+    if (valid && b < 4) grad[(size_t)(b == 0 ? 0 : 6 + b) * n + g] = (float)(b == 0 ? g0 : b == 1 ? g7 : b == 2 ? g8 : g9);
 }
 
 // Rbar[g][l] = sum_b (d logL / d num_b) F_att(l) T_b((1+z) l) l q_l  (zero beyond n_wave);
@@ -909,7 +924,7 @@ constexpr int RBAR_G_BIG = 4, RBAR_BIG_MIN_GAL = 32768;
 static_assert(XBM % RBAR_G_BIG == 0, "a block's galaxies share one row tile");
 template <int P, int RBAR_G>
 __global__ void __launch_bounds__(256) k_exact_rbar(int n, int n_wave, int ld, int nb, FiltConst fl,
-                                                    const float *params, const float *z, const float *wc,
+                                                    const float *dust, const float *z, const float *wc,
                                                     const float *cnum, const int4 *win, void *rb) {
     const int g0 = blockIdx.x * RBAR_G, tid = threadIdx.x;
     const int ng = min(RBAR_G, n - g0);   // galaxies of this block (>= 1)
@@ -927,8 +942,8 @@ __global__ void __launch_bounds__(256) k_exact_rbar(int n, int n_wave, int ld, i
     for (int j = 0; j < RBAR_G; ++j) {
         const int g = min(g0 + j, n - 1);
         opz[j] = 1.0 + (double)z[g];
-        const float tauv = params[(size_t)7 * n + g], delta = params[(size_t)8 * n + g];
-        ffl[j] = params[(size_t)9 * n + g];
+        const float tauv = dust[g], delta = dust[(size_t)n + g];
+        ffl[j] = dust[(size_t)2 * n + g];
         delta2[j] = delta * LOG2E_F;
         tauv2[j] = -tauv * LOG2E_F;
 #pragma unroll
@@ -1037,18 +1052,6 @@ __global__ void __launch_bounds__(256) k_sum_splits(size_t n4, int n_split, size
     c[i] = v;
 }
 
-// per-tile photometry partials summed over the wavelength tiles: out[q][g] = sum_t part[t][q][g],
-// over the tiles of the galaxy's row-tile window (the forward GEMM writes no partials outside it)
-__global__ void __launch_bounds__(256) k_sum_tiles(int n, int npart, int n_tiles, const int4 *win, const float *part,
-                                                   float *out) {
-    const int g = blockIdx.x * 256 + threadIdx.x, q = blockIdx.y;
-    if (g >= n) return;
-    const int4 w = win[g / XBM];
-    float v = 0.0f;
-    for (int t = w.x; t < min(w.y, n_tiles); ++t) v += part[((size_t)t * npart + q) * n + g];
-    out[(size_t)q * n + g] = v;
-}
-
 // FP64 partials [t][g][q] summed over the wavelength tiles and the K split: out[g][q].  One
 // block per galaxy; thread (r, q) sums every R-th partial of quantity q, then the R row sums
 // of each quantity are added in LDS.
@@ -1068,8 +1071,185 @@ __global__ void __launch_bounds__(256) k_sum_parts64(int n, int npart, int n_par
     }
 }
 
-// the weights adjoint -> grad slots 1..6, GPL lanes per galaxy
-template <int GPL>
+// ------------------------------------------------------------------ weights and their adjoint, a wave per galaxy
+// Below GPL_BIG_N galaxies: a lane takes age bins lane and lane + 64, so the serial chain of a galaxy
+// is two bins instead of the twelve of eight lanes per galaxy, and the weights row is written by the
+// wave that formed it.  A block takes XWG galaxies.  From GPL_BIG_N on the lanes that idle over short
+// bins cost more than the chain.
+constexpr int XWG = 8;
+
+// age_universe_gyr to a few ulp with one square root pair and one log1p: asinh(y) = log1p(y + y^2 /
+// (1 + sqrt(1 + y^2)))
+__device__ inline double age_gyr_log1p(const DevConsts &k, double z) {
+    const double ol = 1.0 - k.om, ep = 1.0 + z, a15 = 1.0 / (ep * sqrt(ep));
+    if (!(ol > 0.0)) return 2.0 / (3.0 * k.h0_gyr) * a15;
+    const double y = sqrt(ol / k.om) * a15, y2 = y * y;
+    return 2.0 / (3.0 * k.h0_gyr * sqrt(ol)) * log1p(y + y2 / (1.0 + sqrt(1.0 + y2)));
+}
+
+struct WaveWeights {
+    float m[2], d1[2], d2[2], d3[2], bm[2], dd[2];   // the lane's bins: mass, derivatives, burst mass, edge densities
+    double S;
+    float Zb, l_obs, pz, dpz;                        // pz, dpz: metallicity bin `lane`
+};
+template <bool DERIV>
+__device__ inline WaveWeights wave_weights(const DevConsts &k, int sfh, const float (&th)[NP], double t_obs, int lane) {
+    WaveWeights r{};
+    const float t_obs_f = (float)t_obs;
+    const bool two = lane + WAVE < NA;
+    const int i1 = two ? lane + WAVE : NA - 1;
+    const float up0 = k.lage_hi[lane], up1 = k.lage_hi[i1];
+    if (sfh == SPS_SFH_DPL) {
+        Dpl p = make_dpl(th[1], th[2], th[3]);
+        dpl_at_obs(p, t_obs_f);
+        dpl_bin<DERIV>(k.age_lo[lane], k.age_hi[lane], t_obs_f, p, r.m[0], r.d1[0], r.d2[0], r.d3[0]);
+        if (two) dpl_bin<DERIV>(k.age_lo[i1], k.age_hi[i1], t_obs_f, p, r.m[1], r.d1[1], r.d2[1], r.d3[1]);
+    } else {
+        const Logn p = make_logn(th[1], th[2]);
+        logn_bin<DERIV>(k.age_lo[lane], k.age_hi[lane], t_obs_f, p, r.m[0], r.d1[0], r.d2[0]);
+        if (two) logn_bin<DERIV>(k.age_lo[i1], k.age_hi[i1], t_obs_f, p, r.m[1], r.d1[1], r.d2[1]);
+    }
+    r.S = wave_sum((double)r.m[0] + (double)r.m[1]);
+    // burst window, as in forward_weights
+    const float mu = th[5], inv_s3 = 1.0f / (3.0f * k.burst_sig), v0 = mu - 3.0f * k.burst_sig;
+    r.l_obs = (float)log10_split(t_obs * 1e9);
+    const unsigned long long a0 = __ballot(up0 > v0), a1 = __ballot(two && up1 > v0);
+    const int i0 = a0 ? __builtin_ctzll(a0) : (a1 ? WAVE + __builtin_ctzll(a1) : NA - 1);
+    const int i_end = min(i0 + k.burst_nbins, NA);
+    auto edge = [&](int e) { return e == 0 ? -INFINITY : (e <= WAVE ? lane_value(up0, e - 1) : lane_value(up1, e - 1 - WAVE)); };
+    r.Zb = burst_mass(burst_edge_at<false>(edge(i0), r.l_obs, mu, inv_s3),
+                      burst_edge_at<false>(edge(i_end), r.l_obs, mu, inv_s3));
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int i = lane + WAVE * t;
+        if (i >= i0 && i < i_end) {
+            const BurstEdge lo = burst_edge_at<DERIV>(k.lage_lo[i], r.l_obs, mu, inv_s3);
+            const BurstEdge hi = burst_edge_at<DERIV>(k.lage_hi[i], r.l_obs, mu, inv_s3);
+            r.bm[t] = burst_mass(lo, hi);
+            r.dd[t] = lo.d - hi.d;
+        }
+    }
+    // metallicity bin `lane`: its upper edge, the lower one from the lane before
+    const float inv_sz = 1.0f / k.sigma_logz;
+    const bool top = lane >= NZ - 1;
+    const float xe = top ? INFINITY : (k.met_hi[min(lane, NZ - 1)] - th[6]) * inv_sz;
+    const float te = top ? 0.0f : 0.5f * erfcf(0.7071067811865475f * fabsf(xe)), de = top ? 0.0f : phi_f(xe);
+    float xp = __shfl_up(xe, 1, WAVE), tp = __shfl_up(te, 1, WAVE), dp = __shfl_up(de, 1, WAVE);
+    if (lane == 0) {
+        xp = -INFINITY;
+        tp = dp = 0.0f;
+    }
+    if (lane < NZ) {
+        r.pz = (xp > 0.0f) ? tp - te : ((xe <= 0.0f) ? te - tp : 1.0f - tp - te);
+        r.dpz = (dp - de) * inv_sz;
+    }
+    return r;
+}
+// galaxy g's parameters, in every lane
+__device__ inline void wave_params(const float *params, int n, int g, int lane, float (&th)[NP]) {
+    const float v = params[(size_t)min(lane, NP - 1) * n + g];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) th[p] = lane_value(v, p);
+}
+
+// P_age, P_Z -> pw (slots as above), the weights row -> w, and the epilogue's inputs tau_V, delta,
+// F_floor, z in rank order -> eg [4][n]
+template <int P>
+__global__ void __launch_bounds__(XWG * WAVE) k_exact_weights(DevConsts k, int n, int sfh, const int *perm,
+                                                              const float *params, const float *z, float *pw,
+                                                              float *eg, void *w) {
+    __shared__ __attribute__((aligned(8))) float sp[XWG][XROWF];
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & (WAVE - 1);
+    const int r0 = blockIdx.x * XWG, r = min(r0 + wv, n - 1), g = perm ? perm[r] : r;
+    float th[NP];
+    wave_params(params, n, g, lane, th);
+    const float zf = z[g];
+    const WaveWeights ww = wave_weights<false>(k, sfh, th, age_gyr_log1p(k, (double)zf), lane);
+    const float fb = th[4], sm = (1.0f - fb) * (float)(1.0 / ww.S), bz = (ww.Zb > 0.0f) ? fb / ww.Zb : 0.0f;
+    sp[wv][lane] = fmaf(bz, ww.bm[0], ww.m[0] * sm);
+    if (lane + WAVE < NA) sp[wv][lane + WAVE] = fmaf(bz, ww.bm[1], ww.m[1] * sm);
+    if (lane < NZ) sp[wv][NA + lane] = ww.pz;
+    __syncthreads();
+    if (lane < 4) eg[(size_t)lane * n + r] = lane == 3 ? zf : th[7 + lane];
+    for (int e = tid; e < XROWF * XWG; e += XWG * WAVE) {
+        const int row = e / XWG, t = e % XWG;
+        if (r0 + t < n) pw[(size_t)(row < NA ? row : PW_PZ + (row - NA)) * n + r0 + t] = sp[t][row];
+    }
+    if (r0 + wv >= n) return;
+    for (int e = lane; e < S_PAD / 2; e += WAVE) expand_pair<P>(sp[wv], 2 * e, (size_t)r, w);
+}
+
+// the weights adjoint -> grad slots 1..6
+__global__ void __launch_bounds__(XWG * WAVE) k_exact_adjoint_wave(DevConsts k, int n, int sfh, const int *perm,
+                                                                   const float *params, const float *z,
+                                                                   const float *pb, float *grad) {
+    constexpr int ROWS = NA + WB_GROUPS * NZ;
+    __shared__ float sp[XWG][ROWS];
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & (WAVE - 1);
+    const int r0 = blockIdx.x * XWG, r = min(r0 + wv, n - 1), g = perm ? perm[r] : r;
+    for (int e = tid; e < ROWS * XWG; e += XWG * WAVE) {
+        const int row = e / XWG, t = e % XWG;
+        sp[t][row] = pb[(size_t)row * n + min(r0 + t, n - 1)];
+    }
+    float th[NP];
+    wave_params(params, n, g, lane, th);
+    const WaveWeights ww = wave_weights<true>(k, sfh, th, age_gyr_log1p(k, (double)z[g]), lane);
+    __syncthreads();
+    const float fb = th[4], invS = (float)(1.0 / ww.S), invZ = (ww.Zb > 0.0f) ? 1.0f / ww.Zb : 0.0f;
+    const float inv_s3 = 1.0f / (3.0f * k.burst_sig);
+    const bool dpl = sfh == SPS_SFH_DPL;
+    float v[12] = {};   // fbar, cbar, e1, e2, e3, A0..2, B0..2, d/dmu_Z
+    double dv[4] = {};
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int i = lane + WAVE * t;
+        const float gbar = i < NA ? sp[wv][i] : 0.0f, psbar = (1.0f - fb) * gbar;
+        const float ps = dpl ? ww.m[t] * invS : (float)((double)ww.m[t] / ww.S);
+        const float pb_i = ww.bm[t] * invZ, dpb = ww.dd[t] * inv_s3, pbbar = fb * gbar;
+        v[0] += gbar * (pb_i - ps);
+        v[1] = fmaf(psbar, ps, v[1]);
+        v[2] = fmaf(pbbar, dpb, v[2]);
+        v[3] = fmaf(pbbar, pb_i, v[3]);
+        v[4] += dpb;
+        if (dpl) {
+            v[5] = fmaf(psbar, ww.d1[t], v[5]);
+            v[6] = fmaf(psbar, ww.d2[t], v[6]);
+            v[7] = fmaf(psbar, ww.d3[t], v[7]);
+            v[8] += ww.d1[t];
+            v[9] += ww.d2[t];
+            v[10] += ww.d3[t];
+        } else {
+            dv[0] += (double)psbar * (double)ww.d1[t];
+            dv[1] += (double)psbar * (double)ww.d2[t];
+            dv[2] += (double)ww.d1[t];
+            dv[3] += (double)ww.d2[t];
+        }
+    }
+    if (lane < NZ) {
+        float s = 0.0f;
+#pragma unroll
+        for (int q = 0; q < WB_GROUPS; ++q) s += sp[wv][NA + q * NZ + lane];
+        v[11] = s * ww.dpz;
+    }
+#pragma unroll
+    for (int j = 0; j < 12; ++j) v[j] = wave_sum(v[j]);
+    float out = v[11];   // lane p: component p
+    out = (lane == 4) ? v[0] : out;
+    out = (lane == 5) ? (v[2] - v[3] * v[4]) * invZ : out;
+    if (dpl) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) out = (lane == 1 + j) ? (v[5 + j] - v[1] * v[8 + j]) * invS : out;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dv[j] = wave_sum(dv[j]);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) out = (lane == 1 + j) ? (float)((dv[j] - (double)v[1] * dv[2 + j]) / ww.S) : out;
+        out = (lane == 3) ? 0.0f : out;
+    }
+    if (r0 + wv < n && lane >= 1 && lane <= 6) grad[(size_t)lane * n + g] = out;
+}
+
+// the weights adjoint of large batches -> grad slots 1..6, GPL lanes per galaxy
 __global__ void __launch_bounds__(64) k_exact_adjoint(DevConsts k, int n, int sfh, const float *params,
                                                       const float *z, const float *pw, const float *pb,
                                                       float *grad) {
@@ -1124,27 +1304,29 @@ __global__ void __launch_bounds__(128) k_xwindows(int n, int n_wave, FiltConst f
         zhi[tid >> 6] = mx;
     }
     __syncthreads();
-    if (tid != 0) return;
     const double z0 = fmin(zlo[0], zlo[1]), z1 = fmax(zhi[0], zhi[1]);
     double lo = 1e300, hi = 0.0;
     for (int b = 0; b < nb; ++b) {
         lo = fmin(lo, fl.lo8[b] / (1.0 + z1));
         hi = fmax(hi, fl.hi8[b] / (1.0 + z0));
     }
-    // first index with wave >= lo, last with wave <= hi (binary searches on the ascending grid)
+    // the number of wavelengths below lo (wave 0) and up to hi (wave 1) on the ascending grid: 64 probes at
+    // a time (a serial binary search waited out 26 loads, 7.6 us)
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     int a = 0, c = n_wave;
     while (a < c) {
-        const int m = (a + c) >> 1;
-        if (wave[m] < lo) a = m + 1; else c = m;
+        const int step = (c - a + 63) >> 6, i = a + lane * step;
+        const double l = wave[min(i, n_wave - 1)];
+        const int cnt = __popcll(__ballot(i < c && (wv ? l <= hi : l < lo)));
+        c = min(c, a + cnt * step);
+        a = cnt ? a + (cnt - 1) * step + 1 : a;
     }
-    const int l0 = max(a - 1, 0);
-    a = 0;
-    c = n_wave;
-    while (a < c) {
-        const int m = (a + c) >> 1;
-        if (wave[m] <= hi) a = m + 1; else c = m;
-    }
-    const int l1 = min(a, n_wave - 1);   // one past the last index <= hi, as margin
+    __shared__ int found[2];
+    if (lane == 0) found[wv] = a;
+    __syncthreads();
+    if (tid != 0) return;
+    const int l0 = max(found[0] - 1, 0);
+    const int l1 = min(found[1], n_wave - 1);   // one past the last index <= hi, as margin
     win[blockIdx.x] = make_int4(l0 / XBN, l1 / XBN + 1, l0 / XBK, l1 / XBK + 1);
 }
 
@@ -1170,6 +1352,21 @@ static F64Split f64_split(int n, int n_tiles) {
     return F64Split{(steps + per - 1) / per, per * Prec<SPS_F64>::BK};
 }
 
+// K ranges of the gradient GEMM for n galaxies, and the rows of its partial products for any batch up to n
+static int grad_splits(int n) {
+    const int tiles = round_up(n, XBM) / XBM * (S_PAD / XBN);
+    return std::min(XSPLIT_MAX, std::max(1, (XSPLIT_BLOCKS + tiles / 2) / tiles));
+}
+static int wbar_rows(int n) {
+    int most = 0;
+    for (int m = XBM;; m += XBM) {   // the split falls to 1 within a few thousand rows
+        const int k = grad_splits(std::min(m, n));
+        most = std::max(most, k * std::min(m, round_up(n, XBM)));
+        if (m >= n) return most;
+        if (k == 1) return std::max(most, round_up(n, XBM));
+    }
+}
+
 static ExactLayout exact_layout(const sps_ctx *c, int n, int prec, bool logl, bool grad) {
     const int nw = c->n_wave, nb = c->n_band;
     const bool f64 = (prec == SPS_F64);
@@ -1187,13 +1384,13 @@ static ExactLayout exact_layout(const sps_ctx *c, int n, int prec, bool logl, bo
     L.o_w = carve((size_t)nsplit * mp * S_PAD * tsz);
     L.o_pw = f64 ? 0 : carve((size_t)PW_SLOTS * n * 4);
     L.o_part = carve((size_t)n_parts * n * npart * esz);
-    L.o_psum = carve((size_t)n * npart * esz);
+    L.o_psum = carve(f64 ? (size_t)n * npart * esz : (size_t)4 * n * sizeof(float));   // FP64 tile sums | eg
     L.o_win = f64 ? 0 : carve((size_t)(mp / XBM) * sizeof(int4));
     if (logl) {
         L.o_cn = carve((size_t)n * NB_MAX * 4);
         if (want_grad) {
             L.o_rb = carve((size_t)nsplit * mp * c->lw * tsz);
-            L.o_wb = carve((size_t)XSPLIT * S_PAD * mp * 4);
+            L.o_wb = carve((size_t)wbar_rows(n) * S_PAD * 4);
             L.o_pb = carve((size_t)(NA + WB_GROUPS * NZ) * n * 4);
         }
     }
@@ -1211,9 +1408,11 @@ size_t exact_ws_bytes(const sps_ctx *c, int n, int prec, bool logl, bool grad) {
     return most;
 }
 
+// perm: the caller's index of each rank, or null where the arrays come in rank order (always from
+// GPL_BIG_N galaxies on)
 static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const void *params, const void *z,
                       void *mag_out, const float *obs, const float *sigma, const uint8_t *mask, float *logl,
-                      float *grad, bool zordered, bool vjp) {
+                      float *grad, bool zordered, bool vjp, const int *perm) {
     const int nw = c->n_wave, nb = c->n_band;
     const bool f64 = (prec == SPS_F64);
     const int n_tiles = f64 ? (nw + BN - 1) / BN : c->lw / XBN;
@@ -1234,19 +1433,24 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
     void *w_hi = W + o_w;   // weights rows: FP64 [n][S_PAD], or BF16 parts interleaved [mp][3 or 2 S_PAD]
 
     float *pw = f64 ? nullptr : (float *)(W + o_pw);
+    const bool big = n >= GPL_BIG_N;
+    // the dust parameters and z in rank order (large batches come in rank order)
+    float *eg = (float *)(W + o_psum);
+    const float *dust = big ? (const float *)params + (size_t)7 * n : eg;
+    const float *z_r = big ? (const float *)z : eg + (size_t)3 * n;
     if (f64) {
         hipLaunchKernelGGL(k_exact_weights64, dim3(n), dim3(64), 0, s, c->k, n, sfh,
                            (const double *)params, (const double *)z, c->d_edges, (double *)w_hi);
-    } else {
-        if (n >= GPL_BIG_N)
-            hipLaunchKernelGGL(k_exact_pw<2>, dim3((n + 31) / 32), dim3(64), 0, s, c->k, n, sfh, (const float *)params,
-                               (const float *)z, pw);
-        else
-            hipLaunchKernelGGL(k_exact_pw<8>, dim3((n + 7) / 8), dim3(64), 0, s, c->k, n, sfh, (const float *)params,
-                               (const float *)z, pw);
+    } else if (big) {
+        hipLaunchKernelGGL(k_exact_pw, dim3((n + 64 / GPL - 1) / (64 / GPL)), dim3(64), 0, s, c->k, n, sfh,
+                           (const float *)params, (const float *)z, pw);
         const dim3 ge((n + XG - 1) / XG), be(256);
         if (prec == SPS_F32) hipLaunchKernelGGL(k_expand<SPS_F32>, ge, be, 0, s, n, (const float *)pw, w_hi);
         else hipLaunchKernelGGL(k_expand<SPS_BF16X>, ge, be, 0, s, n, (const float *)pw, w_hi);
+    } else {
+        auto kw = prec == SPS_F32 ? k_exact_weights<SPS_F32> : k_exact_weights<SPS_BF16X>;
+        hipLaunchKernelGGL(kw, dim3((n + XWG - 1) / XWG), dim3(XWG * WAVE), 0, s, c->k, n, sfh, perm,
+                           (const float *)params, (const float *)z, pw, eg, w_hi);
     }
     float *part = (float *)(W + o_part);
     if (f64) {
@@ -1278,8 +1482,7 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
     } else {
         const FiltConst fl = filt_const(c->h_fc, c->h_fs);
         win = (int4 *)(W + o_win);
-        hipLaunchKernelGGL(k_xwindows, dim3(mp / XBM), dim3(128), 0, s, n, nw, fl, nb, (const float *)z, c->d_wave,
-                           win);
+        hipLaunchKernelGGL(k_xwindows, dim3(mp / XBM), dim3(128), 0, s, n, nw, fl, nb, z_r, c->d_wave, win);
         XArgs a{};
         a.win = win;
         a.band_skip = zordered ? 1 : 0;
@@ -1292,8 +1495,8 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
         a.ldb = S_PAD;
         a.n_mt = mp / XBM;
         a.n_nt = lw / XBN;
-        a.params = (const float *)params;
-        a.z = (const float *)z;
+        a.dust = dust;
+        a.z = z_r;
         a.wave = c->d_wave;
         a.wc = c->d_wc;
         a.n_wave = nw;
@@ -1314,42 +1517,26 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
     }
 
     float *cn = lik ? (float *)(W + o_cn) : nullptr;
-    dim3 gf((n + 127) / 128), bf(128);
-    int n_fin = f64 ? n_tiles * f64_split(n, n_tiles).ks : n_tiles;   // partials the finish kernel sums
-    if (!f64) {
-        float *psum = (float *)(W + o_psum);
-        hipLaunchKernelGGL(k_sum_tiles, dim3((n + 255) / 256, npart), dim3(256), 0, s, n, npart, n_tiles,
-                           (const int4 *)win, (const float *)part, psum);
-        part = psum;
-    } else {
+    if (f64) {
         double *psum = (double *)(W + o_psum);
-        hipLaunchKernelGGL(k_sum_parts64, dim3(n), dim3(256), 0, s, n, npart, n_fin, (const double *)part, psum);
-        part = (float *)psum;
-    }
-    n_fin = 1;
-    switch (prec) {
-        case SPS_F64:
-            hipLaunchKernelGGL(k_exact_finish<SPS_F64>, gf, bf, 0, s, c->k, n, n_fin, params, z, (const void *)part,
-                               npart, mag_out, obs, sigma, mask, logl, grad, cn, vjp ? 1 : 0);
-            break;
-        case SPS_F32:
-            hipLaunchKernelGGL(k_exact_finish<SPS_F32>, gf, bf, 0, s, c->k, n, n_fin, params, z, (const void *)part,
-                               npart, mag_out, obs, sigma, mask, logl, grad, cn, vjp ? 1 : 0);
-            break;
-        default:
-            hipLaunchKernelGGL(k_exact_finish<SPS_BF16X>, gf, bf, 0, s, c->k, n, n_fin, params, z, (const void *)part,
-                               npart, mag_out, obs, sigma, mask, logl, grad, cn, vjp ? 1 : 0);
-            break;
+        hipLaunchKernelGGL(k_sum_parts64, dim3(n), dim3(256), 0, s, n, npart, n_tiles * f64_split(n, n_tiles).ks,
+                           (const double *)part, psum);
+        hipLaunchKernelGGL(k_exact_finish64, dim3((n + 127) / 128), dim3(128), 0, s, c->k, n, (const double *)params,
+                           (const double *)z, (const double *)psum, npart, (double *)mag_out);
+    } else {
+        auto kf = want_grad ? k_exact_finish<true> : k_exact_finish<false>;
+        hipLaunchKernelGGL(kf, dim3((n + 31) / 32), dim3(256), 0, s, c->k, n, n_tiles, perm,
+                           (const float *)params, z_r, (const int4 *)win, (const float *)part, npart, (float *)mag_out,
+                           obs, sigma, mask, logl, grad, cn, vjp ? 1 : 0);
     }
     if (want_grad) {
         void *r_hi = W + o_rb;   // Rbar rows: BF16 parts interleaved [mp][3 or 2 lw]
-        const bool big = n >= RBAR_BIG_MIN_GAL;
-        dim3 gr(big ? (n + RBAR_G_BIG - 1) / RBAR_G_BIG : n), br(256);
+        const bool many = n >= RBAR_BIG_MIN_GAL;
+        dim3 gr(many ? (n + RBAR_G_BIG - 1) / RBAR_G_BIG : n), br(256);
         const FiltConst fl = filt_const(c->h_fc, c->h_fs);
-        auto kr = (prec == SPS_F32) ? (big ? k_exact_rbar<SPS_F32, RBAR_G_BIG> : k_exact_rbar<SPS_F32, 1>)
-                                    : (big ? k_exact_rbar<SPS_BF16X, RBAR_G_BIG> : k_exact_rbar<SPS_BF16X, 1>);
-        hipLaunchKernelGGL(kr, gr, br, 0, s, n, nw, lw, nb, fl, (const float *)params, (const float *)z,
-                           c->d_wc, cn, win, r_hi);
+        auto kr = (prec == SPS_F32) ? (many ? k_exact_rbar<SPS_F32, RBAR_G_BIG> : k_exact_rbar<SPS_F32, 1>)
+                                    : (many ? k_exact_rbar<SPS_BF16X, RBAR_G_BIG> : k_exact_rbar<SPS_BF16X, 1>);
+        hipLaunchKernelGGL(kr, gr, br, 0, s, n, nw, lw, nb, fl, dust, z_r, c->d_wc, cn, win, r_hi);
         XArgs b{};
         b.win = win;
         b.M = n;
@@ -1364,11 +1551,7 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
         b.C = (float *)(W + o_wb);
         b.ldc = mp;
         b.n_store = S_PAD;
-        // at a few thousand galaxies the gradient GEMM has few output tiles (n_mt x 9): K is then
-        // split into XSPLIT ranges whose partial products k_sum_splits adds; from 1024 tiles
-        // (four blocks per CU) on the chip is full without the split and its extra traffic
-        const int tiles2 = b.n_mt * b.n_nt;
-        b.k_splits = (tiles2 < 1024 && lw % (XSPLIT * XBK) == 0) ? XSPLIT : 1;
+        b.k_splits = grad_splits(n);
         b.c_split = (size_t)S_PAD * mp;
         b.order = c->launch.exact_order;
         b.xcd = c->launch.exact_xcd;
@@ -1382,18 +1565,17 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
             hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, n4, b.k_splits, n4,
                                (v4f *)b.C);
         }
-        if (n >= GPL_BIG_N)
+        if (big) {
             hipLaunchKernelGGL(k_wbar_reduce<256>, dim3((n + 255) / 256, WB_GROUPS), dim3(256), 0, s, n,
                                (const float *)pw, (const float *)b.C, mp, pb);
-        else
+            hipLaunchKernelGGL(k_exact_adjoint, dim3((n + 64 / GPL - 1) / (64 / GPL)), dim3(64), 0, s, c->k, n, sfh,
+                               (const float *)params, (const float *)z, (const float *)pw, (const float *)pb, grad);
+        } else {
             hipLaunchKernelGGL(k_wbar_reduce<64>, dim3((n + 63) / 64, WB_GROUPS), dim3(64), 0, s, n,
                                (const float *)pw, (const float *)b.C, mp, pb);
-        if (n >= GPL_BIG_N)
-            hipLaunchKernelGGL(k_exact_adjoint<2>, dim3((n + 31) / 32), dim3(64), 0, s, c->k, n, sfh,
-                               (const float *)params, (const float *)z, (const float *)pw, (const float *)pb, grad);
-        else
-            hipLaunchKernelGGL(k_exact_adjoint<8>, dim3((n + 7) / 8), dim3(64), 0, s, c->k, n, sfh,
-                               (const float *)params, (const float *)z, (const float *)pw, (const float *)pb, grad);
+            hipLaunchKernelGGL(k_exact_adjoint_wave, dim3((n + XWG - 1) / XWG), dim3(XWG * WAVE), 0, s, c->k, n, sfh,
+                               perm, (const float *)params, (const float *)z, (const float *)pb, grad);
+        }
     }
     SPS_HIP(hipGetLastError());
     return SPS_OK;
@@ -1433,13 +1615,82 @@ __global__ void __launch_bounds__(256) k_exact_order_out(int n, int nb, const in
         for (int p = 0; p < NP; ++p) grad[(size_t)p * n + g] = grad_s[(size_t)p * n + r];
 }
 
-// From XSORT_MIN galaxies on, the FP32 / BF16X paths rank the galaxies by z first (a bucket
-// sort on the z table's grid, or on 64 buckets over 0 <= z < 8 without a table): a 128-galaxy
-// row tile then spans a narrow z range, and its filter-support window (k_xwindows) covers
-// about half of the wavelength grid instead of two thirds.  Smaller batches keep their order:
-// at 4096 galaxies x 5000 wavelengths the active tiles take two rounds of blocks either way,
-// and the sort costs more than the GEMMs gain.
+// The FP32 / BF16X paths rank the galaxies by z first (by buckets of the z table's grid, or 64 over
+// 0 <= z < 8 without a table): a 128-galaxy row tile then spans a narrow z range, its filter-support
+// window (k_xwindows) covers about half of the wavelength grid instead of two thirds, and the forward
+// epilogue skips the bands out of reach of a wave's galaxies.  From XSORT_MIN galaxies on the inputs
+// are gathered and the outputs returned by passes of their own; below, one block ranks the batch
+// (k_exact_rank) and the per-galaxy kernels read and write through the ranks.  A single row tile keeps
+// its order.
 constexpr int XSORT_MIN = 16384;
+static_assert(XSORT_MIN == GPL_BIG_N, "batches with their own passes are the large ones");
+// perm: the caller's indices ordered by z bucket, in their own order within a bucket (the same tiles and
+// windows, so the same sums, on every run); n < XSORT_MIN, at most RANK_BK buckets.  Each wave ranks a
+// contiguous part of the batch, 64 galaxies at a time: lanes of equal bucket are found by ballots over
+// the bucket's bits, and the first of them advances the wave's count.
+constexpr int RANK_T = 1024, RANK_BK = 1024, RANK_W = RANK_T / WAVE, RANK_PER = XSORT_MIN / RANK_T;
+static_assert(RANK_BK == RANK_T && SORT_MAX_BUCKETS <= RANK_BK && XSORT_MIN <= 65536, "a thread per bucket, 16-bit counts");
+__global__ void __launch_bounds__(RANK_T) k_exact_rank(DevConsts k, int n, const float *__restrict__ z,
+                                                       int *__restrict__ perm) {
+    __shared__ uint16_t cnt[RANK_W][RANK_BK];
+    __shared__ int start[RANK_BK], wsum[RANK_W];
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = tid >> 6, nbk = k.n_z;
+    for (int w = 0; w < RANK_W; ++w) cnt[w][tid] = 0;
+    const int per = ((n + RANK_W - 1) / RANK_W + WAVE - 1) / WAVE * WAVE, base = wv * per;   // per <= 64 RANK_PER
+    const int bits = 32 - __clz(max(nbk - 1, 1));
+    int bk[RANK_PER], at[RANK_PER];
+#pragma unroll
+    for (int t = 0; t < RANK_PER; ++t) {
+        const int i = base + WAVE * t + lane;
+        bk[t] = -1;
+        if (WAVE * t < per && i < n) {
+            float f;
+            const int kk = z_bucket(k, z[i], &f);
+            bk[t] = kk < 0 ? nbk - 1 : kk;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < RANK_PER; ++t) {
+        at[t] = 0;
+        unsigned long long same = __ballot(bk[t] >= 0);
+        if (same == 0) continue;
+        for (int bit = 0; bit < bits; ++bit) {
+            const bool on = (bk[t] >> bit) & 1;
+            const unsigned long long m = __ballot(on);
+            same &= on ? m : ~m;
+        }
+        if (bk[t] >= 0) {
+            const int before = __popcll(same & ((1ull << lane) - 1ull)), c = cnt[wv][bk[t]];
+            at[t] = c + before;
+            if (before == 0) cnt[wv][bk[t]] = (uint16_t)(c + __popcll(same));
+        }
+    }
+    __syncthreads();
+    // bucket tid: its waves' counts to offsets, and the exclusive scan of the totals
+    int own = 0;
+    for (int w = 0; w < RANK_W; ++w) {
+        const int c = cnt[w][tid];
+        cnt[w][tid] = (uint16_t)own;
+        own += c;
+    }
+    int x = own;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const int y = __shfl_up(x, o, WAVE);
+        if (lane >= o) x += y;
+    }
+    if (lane == WAVE - 1) wsum[wv] = x;
+    __syncthreads();
+    int before = 0;
+    for (int w = 0; w < wv; ++w) before += wsum[w];
+    start[tid] = before + x - own;
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < RANK_PER; ++t)
+        if (bk[t] >= 0) perm[start[bk[t]] + cnt[wv][bk[t]] + at[t]] = base + WAVE * t + lane;
+}
+
 struct XsortLayout {
     size_t o_par, o_z, o_obs, o_sig, o_msk, o_mag, o_ll, o_gr, bytes;
 };
@@ -1465,10 +1716,19 @@ size_t exact_xsort_bytes(const sps_ctx *c, int n) { return n >= XSORT_MIN ? xsor
 int launch_exact(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const void *params, const void *z,
                  void *mag_out, const float *obs, const float *sigma, const uint8_t *mask, float *logl,
                  float *grad, bool ordered, bool vjp) {
-    if (prec == SPS_F64 || ordered || n < XSORT_MIN)
+    if (prec == SPS_F64 || ordered)
         return exact_core(c, s, n, sfh, prec, params, z, mag_out, obs, sigma, mask, logl, grad,
-                          ordered && prec != SPS_F64, vjp);
+                          ordered && prec != SPS_F64, vjp, nullptr);
     const DevConsts grid = z_sort_grid(c);
+    if (n < XSORT_MIN) {
+        const bool rank = n > XBM;
+        if (rank) {
+            hipLaunchKernelGGL(k_exact_rank, dim3(1), dim3(RANK_T), 0, s, grid, n, (const float *)z, c->d_perm);
+            SPS_HIP(hipGetLastError());
+        }
+        return exact_core(c, s, n, sfh, prec, params, z, mag_out, obs, sigma, mask, logl, grad, rank, vjp,
+                          rank ? c->d_perm : nullptr);
+    }
     const int nb = c->n_band;
     const XsortLayout xl = xsort_layout(c, n);
     const size_t o_par = xl.o_par, o_z = xl.o_z, o_obs = xl.o_obs, o_sig = xl.o_sig, o_msk = xl.o_msk;
@@ -1488,7 +1748,7 @@ int launch_exact(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const void
                        (const float *)z, obs, sigma, mask, par_s, z_s, obs_s, sig_s, msk_s);
     rc = exact_core(c, s, n, sfh, prec, par_s, z_s, mag_out ? mag_s : nullptr, obs ? obs_s : nullptr,
                     sigma ? sig_s : nullptr, mask ? msk_s : nullptr, logl ? ll_s : nullptr, grad ? gr_s : nullptr,
-                    true, vjp);
+                    true, vjp, nullptr);
     if (rc) return rc;
     hipLaunchKernelGGL(k_exact_order_out, g1, b1, 0, s, n, nb, (const int *)c->d_perm, mag_s, ll_s, gr_s,
                        (float *)mag_out, logl, grad);

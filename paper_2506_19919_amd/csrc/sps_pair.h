@@ -23,6 +23,10 @@ constexpr int PAIR_NB = AGE_BLK / 2;   // blocks of 16 table rows or ages per wa
 
 // ------------------------------------------------------------------ sums over a wave
 template <int CTRL, int ROWS = 0xf>
+__device__ inline float dpp_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS = 0xf>
 __device__ inline double dpp_add(double v) {
     const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
     const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
@@ -38,7 +42,8 @@ __device__ inline double lane_value(double v, int l) {
 // the wave's sum, in every lane (all 64 lanes must call it): rotations by 8, 4, 2, 1 within each
 // row of 16, then rows 1 and 3 take the row before them (row_bcast:15) and rows 2 and 3 row 1's
 // total (row_bcast:31); lane 63 holds the sum
-__device__ inline double wave_sum(double v) {
+template <typename T>
+__device__ inline T wave_sum(T v) {
     v = dpp_add<0x128>(v);
     v = dpp_add<0x124>(v);
     v = dpp_add<0x122>(v);
