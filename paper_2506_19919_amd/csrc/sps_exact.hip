@@ -285,15 +285,14 @@ __global__ void __launch_bounds__(256) k_exact_gemm(GemmArgs a) {
 //          v_mfma_f32_16x16x4f32 takes 32 cycles for 4 k, these six 96 for 32: the GEMMs at 4096 x
 //          5000 took 378 (forward) and 373 us (gradient) on the former.
 //   BF16X: hi + lo; three products lo.hi + hi.lo + hi.hi.
-// LDS rows carry 16 bytes of padding, which spreads a fragment read's 16 rows over the banks.
 // Blocks are mapped XCD-aware: consecutive dispatch slots go round-robin over the 8 XCDs, so
 // slot b is remapped to tile (b % 8) * T / 8 + b / 8 and each XCD works through one
 // contiguous run of tiles, M fastest (its A rows stay in that XCD's L2), or N fastest where
 // whole wavelength tiles are skipped (see XArgs::win), so the skipped ones spread evenly.
 constexpr int XBM = 128, XBN = 128, XBK = 32;
 template <int P> constexpr int x_parts() { return P == SPS_F32 ? 3 : 2; }
-template <int P> constexpr int x_row() { return 64 * x_parts<P>() + 16; }            // bytes per LDS row
-template <int P> constexpr int x_stage() { return (XBM + XBN) * x_row<P>(); }        // 53,248 or 36,864 bytes
+constexpr int XSUB = XBM * 64;                                                  // bytes of one part of an operand tile
+template <int P> constexpr int x_stage() { return 2 * x_parts<P>() * XSUB; }     // 49,152 or 32,768 bytes
 // K ranges of the gradient GEMM: its n/128 x 9 output tiles are split so that about XSPLIT_BLOCKS blocks
 // run (three fit on a CU), each taking an equal part of its row tile's window
 constexpr int XSPLIT_MAX = 8, XSPLIT_BLOCKS = 640;
@@ -329,43 +328,18 @@ struct XArgs {
     int order, xcd;
 };
 
-// a k-tile of both operand tiles: 16-byte chunks, XCH per row; thread t takes chunks t + 256 c of A
-// for c < XCH / 2 and of B after that, in the LDS row order
-template <int P> constexpr int x_chunks() { return 4 * x_parts<P>(); }
-template <int P>
-__device__ inline void x_load(const XArgs &a, int tile_m, int tile_n, int k0, int tid, v4f (&r)[x_chunks<P>()]) {
-    constexpr int XCH = x_chunks<P>(), PARTS = x_parts<P>();
-#pragma unroll
-    for (int c = 0; c < XCH; ++c) {
-        const bool isA = c < XCH / 2;
-        const int e = tid + 256 * (c % (XCH / 2)), row = e / XCH, q = e % XCH;
-        const uint16_t *base = (const uint16_t *)(isA ? a.A : a.B);
-        const int ld = isA ? a.lda : a.ldb;
-        const size_t grow = (size_t)(isA ? tile_m : tile_n) + row;
-        r[c] = *(const v4f *)(base + grow * PARTS * ld + PARTS * k0 + 8 * q);
-    }
-}
-
-template <int P>
-__device__ inline void x_store(char *stage, int tid, const v4f (&r)[x_chunks<P>()]) {
-    constexpr int XCH = x_chunks<P>();
-#pragma unroll
-    for (int c = 0; c < XCH; ++c) {
-        const int e = tid + 256 * (c % (XCH / 2)), row = e / XCH, q = e % XCH;
-        const int orow = (c < XCH / 2) ? row : XBM + row;
-        *(v4f *)(stage + orow * x_row<P>() + 16 * q) = r[c];
-    }
-}
-
-// LDS stages: one register-staged stage, with three blocks per CU for BF16X and two for FP32 (whose
-// products per k-tile take twice as long); or for BF16X (RING = true, a launch choice) a ring of two
-// stages filled by direct global-to-LDS loads, which need no staging registers, with two blocks
-// per CU.  The two BF16X forms multiply the same tiles in the same order (the same bits); which is
-// faster depends on the shape (sps_autotune_exact).
+// LDS stages, filled by direct global-to-LDS loads (no staging registers): one stage with three blocks
+// per CU, whose products cover each other's loads; or for BF16X (RING = true, a launch choice) a ring
+// of two stages with two blocks per CU.  The two BF16X forms multiply the same tiles in the same order
+// (the same bits); which is faster depends on the shape (sps_autotune_exact).
 constexpr int RSTAGES = 2;
 constexpr int RSTAGE = 2 * XBM * 128;   // A then B rows, 128 bytes (the k-tile's 32 hi + 32 lo) each
-template <int P, bool RING> constexpr int x_smem() { return RING ? RSTAGES * RSTAGE : x_stage<P>(); }
-template <int P, bool RING> constexpr int x_blocks() { return RING ? 2 : (P == SPS_BF16X ? 3 : 2); }
+// the single stage is at least the epilogue's half SED tile with the wavelength constants
+constexpr int XSED = XBM * (XBN / 2 + 1) * 4 + XBN * 16;
+template <int P, bool RING> constexpr int x_smem() {
+    return RING ? RSTAGES * RSTAGE : (x_stage<P>() > XSED ? x_stage<P>() : XSED);
+}
+template <int P, bool RING> constexpr int x_blocks() { return RING ? 2 : 3; }
 
 #define SPS_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 // s_waitcnt immediate for "at most n vector-memory operations outstanding" (other counters free)
@@ -396,6 +370,23 @@ __device__ inline void x_ring_issue(const XRing &r, char *stage, int k0, int wav
     for (int j = 0; j < 8; ++j)
         __builtin_amdgcn_global_load_lds((const void *)(r.src + j * r.jstep + 2 * k0),
                                          SPS_LDS_PTR(stage + 1024 * (8 * w + j)), 16, 0, 0);
+}
+
+// Single stage: part p of operand o (A, B) is 128 rows of 64 bytes at (o XP + p) XSUB.  A load covers
+// 16 rows, lane L writing slot L % 4 of row L / 4 with the row's 16-byte chunk (L % 4) ^ (L / 16): that
+// XOR by the row's bits 2..3 spreads the 16 rows of a fragment read over all banks.  Wave w loads rows
+// 32 w .. 32 w + 31 of every part.
+// (base: wave-uniform, the wave's first row of the operand; off: the lane's bytes from there.)
+template <int P>
+__device__ inline void x_issue(const char *base, uint32_t off, int ld, int k0, char *stage) {
+    constexpr int PARTS = x_parts<P>();
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p)
+            __builtin_amdgcn_global_load_lds(
+                (const void *)(base + ((size_t)h * 16 * PARTS * ld + PARTS * k0 + 32 * p) * 2 + off),
+                SPS_LDS_PTR(stage + p * XSUB + 1024 * h), 16, 0, 0);
 }
 
 template <int P, int EPI, bool RING>
@@ -498,52 +489,58 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
         }
         __syncthreads();   // every wave is done with the ring before the epilogue reuses it
     } else {
-    constexpr int XROW = x_row<P>(), PARTS = x_parts<P>();
-    v4f r[x_chunks<P>()];
-    x_load<P>(a, tile_m, tile_n, kbeg, tid, r);
-    x_store<P>(smem, tid, r);
-    __syncthreads();
+    constexpr int PARTS = x_parts<P>();
+    const int ws = __builtin_amdgcn_readfirstlane(wave);
+    const int lch = 16 * ((lane & 3) ^ (lane >> 4));
+    const char *pa = (const char *)a.A + (size_t)(tile_m + 32 * ws) * PARTS * a.lda * 2;
+    const char *pb = (const char *)a.B + (size_t)(tile_n + 32 * ws) * PARTS * a.ldb * 2;
+    const uint32_t oa = (uint32_t)(lane >> 2) * PARTS * a.lda * 2 + lch, ob = (uint32_t)(lane >> 2) * PARTS * a.ldb * 2 + lch;
+    char *sa = smem + 2048 * ws, *sb = sa + PARTS * XSUB;
+    const int frag = li * 64 + ((lk ^ (li >> 2)) << 4);
+    if (nk > 0) {
+        x_issue<P>(pa, oa, a.lda, kbeg, sa);
+        x_issue<P>(pb, ob, a.ldb, kbeg, sb);
+    }
     for (int kt = 0; kt < nk; ++kt) {
-        if (kt + 1 < nk) x_load<P>(a, tile_m, tile_n, kbeg + (kt + 1) * XBK, tid, r);
-        const char *Ar = smem + (wm * 64 + li) * XROW + 16 * lk, *Br = smem + (XBM + wn * 64 + li) * XROW + 16 * lk;
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        __syncthreads();
+        // the k-tile's fragments into registers, then the stage is free for the next k-tile, whose loads
+        // run under this one's products
+        const char *Ar = smem + opaque(frag) + 4096 * (ws >> 1), *Br = smem + opaque(frag) + PARTS * XSUB + 4096 * (ws & 1);
+        auto next = [&]() {
+            __syncthreads();
+            if (kt + 1 < nk) {
+                x_issue<P>(pa, oa, a.lda, kbeg + (kt + 1) * XBK, sa);
+                x_issue<P>(pb, ob, a.ldb, kbeg + (kt + 1) * XBK, sb);
+            }
+        };
         b8v af[PARTS][4];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int p = 0; p < PARTS; ++p) af[p][i] = *(const b8v *)(Ar + i * 16 * XROW + 64 * p);
-        if constexpr (P == SPS_F32) {
+            for (int p = 0; p < PARTS; ++p) af[p][i] = *(const b8v *)(Ar + i * 1024 + p * XSUB);
+        // FP32 takes B's fragments in two halves (all of them would not fit beside A's in 168 registers)
+        constexpr int JH = (P == SPS_F32) ? 2 : 4;
+        constexpr int NPROD = (P == SPS_F32) ? 6 : 3;   // small products first
+        constexpr int PA[6] = {PARTS - 1, 0, P == SPS_F32 ? 1 : 0, 1, 0, 0}, PB[6] = {0, PARTS - 1, P == SPS_F32 ? 1 : 0, 0, 1, 0};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                b8v bf[PARTS];
+        for (int j0 = 0; j0 < 4; j0 += JH) {
+            b8v bf[PARTS][JH];
 #pragma unroll
-                for (int p = 0; p < PARTS; ++p) bf[p] = *(const b8v *)(Br + j * 16 * XROW + 64 * p);
-                constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};   // small products first
+            for (int j = 0; j < JH; ++j)
 #pragma unroll
-                for (int t = 0; t < 6; ++t)
+                for (int p = 0; p < PARTS; ++p) bf[p][j] = *(const b8v *)(Br + (j0 + j) * 1024 + p * XSUB);
+            if (j0 + JH == 4) next();
+#pragma unroll
+            for (int t = 0; t < NPROD; ++t)
+#pragma unroll
+                for (int j = 0; j < JH; ++j)
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[PA[t]][i], bf[PB[t]], acc[i][j], 0, 0, 0);
-            }
-        } else {
-            b8v bh[4], bl[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                bh[i] = *(const b8v *)(Br + i * 16 * XROW);
-                bl[i] = *(const b8v *)(Br + i * 16 * XROW + 64);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[1][i], bh[j], acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[0][i], bl[j], acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[0][i], bh[j], acc[i][j], 0, 0, 0);
-                }
+                        acc[i][j0 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[PA[t]][i], bf[PB[t]][j], acc[i][j0 + j], 0, 0, 0);
         }
-        __syncthreads();   // every wave is done with the stage before it is refilled
-        if (kt + 1 < nk) x_store<P>(smem, tid, r);
-        __syncthreads();
     }
+    __syncthreads();   // every wave is done before the epilogue reuses the stage
     }
 
     if constexpr (EPI == EPI_STORE) {
