@@ -263,9 +263,9 @@ size_t sps_hmc_state_bytes(int n_gal, int n_chain);
 
 /* Launch choices of a context that never change any result, only the order or grouping in
  * which independent work is issued (every output is bitwise the same for every setting):
- *   exact_order      exact-path GEMM tile order: 0 the built-in policy (M fastest, N fastest
- *                    for the windowed forward GEMM), 1 M fastest, 2 N fastest, 3 bands of 8
- *                    row tiles (M fastest within a band that sweeps every column tile)
+ *   exact_order      exact-path GEMM tile order: 0 the built-in policy (bands, in dispatch order
+ *                    below 64 row tiles), 1 M fastest, 2 N fastest, 3 bands of 8 row tiles (M
+ *                    fastest within a band that sweeps every column tile)
  *   exact_xcd        1: each of the 8 XCDs takes one contiguous run of tiles; 0: tiles in
  *                    dispatch order (round-robin over the XCDs)
  *   hmc_block_iters  approximate-path HMC iterations per kernel launch, 1..1000 (default 25)
@@ -273,9 +273,8 @@ size_t sps_hmc_state_bytes(int n_gal, int n_chain);
  *   hmcx_graph       exact-path HMC: 1 captures one iteration (about 10 kernels per leapfrog
  *                    step) as a hipGraph once per call and replays it, the iteration index read
  *                    from device memory; 0 launches the kernels one by one (default 1)
- *   exact_ring       BF16X exact-path GEMMs: 0 operands staged through registers into one LDS
- *                    stage, three blocks per CU; 1 a two-stage LDS ring filled by direct
- *                    global-to-LDS loads, two blocks per CU (default 0) */
+ *   exact_ring       BF16X exact-path GEMMs, operands loaded straight to LDS: 0 one stage, three
+ *                    blocks per CU; 1 a ring of two stages, two blocks per CU (default 0) */
 typedef struct {
     int exact_order, exact_xcd, hmc_block_iters, nuts_block_iters, hmcx_graph, exact_ring;
 } sps_launch_cfg;

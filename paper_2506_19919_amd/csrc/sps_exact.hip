@@ -287,8 +287,7 @@ __global__ void __launch_bounds__(256) k_exact_gemm(GemmArgs a) {
 //   BF16X: hi + lo; three products lo.hi + hi.lo + hi.hi.
 // Blocks are mapped XCD-aware: consecutive dispatch slots go round-robin over the 8 XCDs, so
 // slot b is remapped to tile (b % 8) * T / 8 + b / 8 and each XCD works through one
-// contiguous run of tiles, M fastest (its A rows stay in that XCD's L2), or N fastest where
-// whole wavelength tiles are skipped (see XArgs::win), so the skipped ones spread evenly.
+// contiguous run of tiles (tile_order for the built-in choice).
 constexpr int XBM = 128, XBN = 128, XBK = 32;
 template <int P> constexpr int x_parts() { return P == SPS_F32 ? 3 : 2; }
 constexpr int XSUB = XBM * 64;                                                  // bytes of one part of an operand tile
@@ -322,9 +321,8 @@ struct XArgs {
     // rows in z order: the forward epilogue skips, per wave, the bands farther than 8 sigma
     // from all of its wavelengths (a wave's galaxies then share nearly one redshift)
     int band_skip;
-    // tile order (sps_launch_cfg): 0 the built-in policy, 1 M fastest, 2 N fastest, 3 bands of
-    // XBAND row tiles; xcd: one contiguous run of tiles per XCD (1) or dispatch order (0).  Every
-    // order computes the same tiles the same way.
+    // tile order: 1 M fastest, 2 N fastest, 3 bands of XBAND row tiles; xcd: one contiguous run of
+    // tiles per XCD (1) or dispatch order (0).  Every order computes the same tiles the same way.
     int order, xcd;
 };
 
@@ -373,9 +371,12 @@ __device__ inline void x_ring_issue(const XRing &r, char *stage, int k0, int wav
 }
 
 // Single stage: part p of operand o (A, B) is 128 rows of 64 bytes at (o XP + p) XSUB.  A load covers
-// 16 rows, lane L writing slot L % 4 of row L / 4 with the row's 16-byte chunk (L % 4) ^ (L / 16): that
-// XOR by the row's bits 2..3 spreads the 16 rows of a fragment read over all banks.  Wave w loads rows
-// 32 w .. 32 w + 31 of every part.
+// 16 rows, lane L writing slot L % 4 of row L / 4 with the row's 16-byte chunk (L % 4) ^ x_swz(L / 16).
+// A fragment read (16 bytes per lane, row lane % 16, chunk lane / 16) is served 16 lanes at a time,
+// lanes 0-3, 12-15, 20-23, 24-27 together and 4-11, 16-19, 28-31: x_swz of the row's bits 2..3 puts each
+// of those sets on all banks once (the plain XOR with those bits doubled the reads' cycles).  Wave w
+// loads rows 32 w .. 32 w + 31 of every part.
+__device__ inline int x_swz(int q) { return (((q ^ (q >> 1)) & 1) << 1) | (q >> 1); }   // 0, 2, 3, 1
 // (base: wave-uniform, the wave's first row of the operand; off: the lane's bytes from there.)
 template <int P>
 __device__ inline void x_issue(const char *base, uint32_t off, int ld, int k0, char *stage) {
@@ -412,9 +413,7 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
         sp = t / T;
         t -= sp * T;
     }
-    // M fastest, except in a windowed forward GEMM: its skipped tiles are whole wavelength
-    // ranges, so there each XCD's run of tiles takes every wavelength tile of a few row tiles
-    const bool nfast = a.order == 0 ? (EPI != EPI_STORE && a.win != nullptr) : (a.order == 2);
+    const bool nfast = a.order == 2;
     int tile_m, tile_n;
     if (a.order == 3) {
         // bands of XBAND row tiles: M fastest inside a band, which sweeps every column tile, so
@@ -491,12 +490,12 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
     } else {
     constexpr int PARTS = x_parts<P>();
     const int ws = __builtin_amdgcn_readfirstlane(wave);
-    const int lch = 16 * ((lane & 3) ^ (lane >> 4));
+    const int lch = 16 * ((lane & 3) ^ x_swz(lane >> 4));
     const char *pa = (const char *)a.A + (size_t)(tile_m + 32 * ws) * PARTS * a.lda * 2;
     const char *pb = (const char *)a.B + (size_t)(tile_n + 32 * ws) * PARTS * a.ldb * 2;
     const uint32_t oa = (uint32_t)(lane >> 2) * PARTS * a.lda * 2 + lch, ob = (uint32_t)(lane >> 2) * PARTS * a.ldb * 2 + lch;
     char *sa = smem + 2048 * ws, *sb = sa + PARTS * XSUB;
-    const int frag = li * 64 + ((lk ^ (li >> 2)) << 4);
+    const int frag = li * 64 + ((lk ^ x_swz(li >> 2)) << 4);
     if (nk > 0) {
         x_issue<P>(pa, oa, a.lda, kbeg, sa);
         x_issue<P>(pb, ob, a.ldb, kbeg, sb);
@@ -1405,6 +1404,18 @@ size_t exact_ws_bytes(const sps_ctx *c, int n, int prec, bool logl, bool grad) {
     return most;
 }
 
+// The built-in tile order (sps_launch_cfg): bands of row tiles, whose panels the blocks in flight share
+// in L2; each XCD its own run of them from ORDER_XCD_MT row tiles on, below in dispatch order, where the
+// row tiles' different windows would load the XCDs unevenly.  BF16X value+gradient, us, bands in runs /
+// in dispatch order / M fastest in runs (N fastest forward): 4096 x 5000 303 / 269 / 276, 20,011 x 2000
+// 499 / 511 / 532, 65,536 x 2000 1254 / 1352 / 1440.
+constexpr int ORDER_XCD_MT = 64;
+static void tile_order(const sps_ctx *c, XArgs &a) {
+    const bool own = c->launch.exact_order == 0;
+    a.order = own ? 3 : c->launch.exact_order;
+    a.xcd = c->launch.exact_xcd && (!own || a.n_mt >= ORDER_XCD_MT);
+}
+
 // perm: the caller's index of each rank, or null where the arrays come in rank order (always from
 // GPL_BIG_N galaxies on)
 static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const void *params, const void *z,
@@ -1501,8 +1512,7 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
         for (int b = 0; b < NB_MAX; ++b) { a.fc[b] = c->h_fc[b]; a.inv_fs[b] = 1.0 / c->h_fs[b]; }
         a.part = part;
         a.npart = npart;
-        a.order = c->launch.exact_order;
-        a.xcd = c->launch.exact_xcd;
+        tile_order(c, a);
         const dim3 gx(a.n_mt * a.n_nt), bx(256);
         const bool ring = c->launch.exact_ring != 0;
         if (prec == SPS_F32 && !want_grad) hipLaunchKernelGGL((k_xgemm<SPS_F32, EPI_PHOT, false>), gx, bx, 0, s, a);
@@ -1550,8 +1560,7 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
         b.n_store = S_PAD;
         b.k_splits = grad_splits(n);
         b.c_split = (size_t)S_PAD * mp;
-        b.order = c->launch.exact_order;
-        b.xcd = c->launch.exact_xcd;
+        tile_order(c, b);
         const dim3 g2(b.n_mt * b.n_nt * b.k_splits), b2(256);
         if (prec == SPS_F32) hipLaunchKernelGGL((k_xgemm<SPS_F32, EPI_STORE, false>), g2, b2, 0, s, b);
         else if (c->launch.exact_ring) hipLaunchKernelGGL((k_xgemm<SPS_BF16X, EPI_STORE, true>), g2, b2, 0, s, b);
