@@ -240,14 +240,15 @@ struct ApproxArgs {
     float *mag, *val, *grad;  // outputs in the caller's order: [n][n_band], [n], [10][n] (may be null)
 };
 
-template <int MODE>
+// G adjacent lanes per galaxy (approx_lanes)
+template <int MODE, int G>
 __global__ void __launch_bounds__(WAVE, 2) k_approx(DevConsts k, ApproxArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char lds_dyn[];   // approx_lds_bytes(n_band, true)
-    const ApproxLds lds = approx_lds(lds_dyn, k.n_band, true, 1);
+    extern __shared__ __attribute__((aligned(16))) char lds_dyn[];   // approx_lds_bytes(n_band, true, G)
+    const ApproxLds lds = approx_lds(lds_dyn, k.n_band, true, G);
     __shared__ float ledge[NA + 1];
     stage_log_age_edges(k, ledge);
     const int lane = threadIdx.x;
-    const int idx = blockIdx.x * WAVE + lane;
+    const int idx = (blockIdx.x * WAVE + lane) / G, q = lane % G;
     const bool valid = idx < a.n;
     // the galaxy's place in the caller's arrays (its results are written there directly: each
     // lane's few scattered stores cost the VALU-bound kernel less than a separate reordering pass)
@@ -287,7 +288,7 @@ __global__ void __launch_bounds__(WAVE, 2) k_approx(DevConsts k, ApproxArgs a) {
     float mags[NB_MAX] = {}, gr[NP];
     double logl;
     constexpr int EM = (MODE == MODE_LOGPOST_GRAD || MODE == MODE_VJP) ? MODE_LOGL_GRAD : MODE;
-    approx_eval<EM, true, 1, MODE == MODE_VJP>(k, ledge, a.sfh, a.qf, a.qa, lds, th, zf, kk, f, t_obs, m0, kmin, kmax, rec + REC_OBS, rec + REC_SIG,
+    approx_eval<EM, true, G, MODE == MODE_VJP>(k, ledge, a.sfh, a.qf, a.qa, lds, th, zf, kk, f, t_obs, m0, kmin, kmax, rec + REC_OBS, rec + REC_SIG,
                     mask, mags, logl, gr);
     if (!valid) return;
     const float bad = (kk >= 0) ? 0.0f : __int_as_float(0x7fc00000);
@@ -295,9 +296,10 @@ __global__ void __launch_bounds__(WAVE, 2) k_approx(DevConsts k, ApproxArgs a) {
         const int nb = k.n_band;
 #pragma unroll
         for (int b = 0; b < NB_MAX; ++b)
-            if (b < nb) a.mag[(size_t)dst_g * nb + b] = mags[b] + bad;
+            if (b < nb && b % G == q) a.mag[(size_t)dst_g * nb + b] = mags[b] + bad;
         return;
     }
+    if (q != 0) return;
     float val = (float)logl;
     if (MODE == MODE_LOGPOST_GRAD) {
         double lp = logl;
@@ -442,16 +444,32 @@ int launch_bucket_sort(sps_ctx *c, hipStream_t s, int n, const float *z, const G
 }
 
 // Up to PAIR_MAX_GAL galaxies a pair of waves takes each galaxy (k_approx_pair); the chip holds 2048
-// such pairs at a time, ~15 us each round (value+gradient).  Above it a lane takes each galaxy, whose
-// serial chain of 94 bins, twice, costs the same ~135 us from a few thousand to 65,536 galaxies.
-// Pair / lane kernels, us per call: value+gradient 35 / 139 at 4096, 126 / 135 at 16,384, 140 / 139 at
-// 18,432; magnitudes 57 / 64 at 16,384 (log-normal 95 / 101), 63 / 66 at 18,432 (105 / 101); and at 64
-// galaxies 14 / 770, where a wave of the lane kernel spans all redshift buckets, contracting for each.
-constexpr int PAIR_MAX_GAL = 16384;
+// such pairs at a time, ~15 us each round (value+gradient).  Above it k_approx with G lanes per galaxy,
+// whose serial chain of 94 / G bins, twice, sets the time while the n G / 64 waves fit the chip's 2048
+// slots: four lanes up to 32,768 galaxies, two up to 65,536, then one (more lanes repeat the
+// per-galaxy work).  us per call, value+gradient, pairs / 4 / 2 / 1 lanes: 67 / 76 / - / 130 at 8192,
+// 126 / 75 / 94 / 136 at 16,500, - / 80 / 95 / 138 at 32,768, - / 136 / 106 / 140 at 65,536, - / - / 179 /
+// 149 at 131,072; magnitudes 32 / 43 / - / 64, 57 / 44 / 52 / 64, - / 46 / 53 / 67, - / 74 / 58 / 71, - / - / 97 / 77.
+// (At 64 galaxies one lane took 770 us: a wave spans all redshift buckets, contracting for each.)
+constexpr int PAIR_MAX_GAL = 8192, LANES4_MAX_GAL = 32768, LANES2_MAX_GAL = 65536;
+static int approx_lanes(int n) { return n <= LANES4_MAX_GAL ? 4 : n <= LANES2_MAX_GAL ? 2 : 1; }
+template <int G>
+static void launch_k_approx(sps_ctx *c, hipStream_t s, int n, int mode, const ApproxArgs &a) {
+    const dim3 grid((unsigned)(((long long)n * G + WAVE - 1) / WAVE)), block(WAVE);
+    const size_t lds = approx_lds_bytes(c->n_band, true, G);
+    switch (mode) {
+        case MODE_MAGS: hipLaunchKernelGGL((k_approx<MODE_MAGS, G>), grid, block, lds, s, c->k, a); break;
+        case MODE_LOGL: hipLaunchKernelGGL((k_approx<MODE_LOGL, G>), grid, block, lds, s, c->k, a); break;
+        case MODE_LOGL_GRAD: hipLaunchKernelGGL((k_approx<MODE_LOGL_GRAD, G>), grid, block, lds, s, c->k, a); break;
+        case MODE_VJP: hipLaunchKernelGGL((k_approx<MODE_VJP, G>), grid, block, lds, s, c->k, a); break;
+        default: hipLaunchKernelGGL((k_approx<MODE_LOGPOST_GRAD, G>), grid, block, lds, s, c->k, a); break;
+    }
+}
 
 int launch_approx_ws(sps_ctx *c, hipStream_t s, const ApproxWs &ws, int n, int sfh, int mode, const float *params,
                      const float *z, const float *obs, const float *sigma, const uint8_t *mask, const float *bounds,
                      const float *prior, float *out_mag, float *out_val, float *out_grad) {
+    if (mode < MODE_MAGS || mode > MODE_VJP) return set_error(SPS_E_INVAL, "bad approx mode");
     if (n <= PAIR_MAX_GAL) {
         const PairArgs a{n, sfh, params, z, obs, sigma, mask, bounds, prior, c->d_qf, c->d_qa, out_mag,
                          mode == MODE_VJP ? nullptr : out_val, out_grad, c->d_status};
@@ -464,10 +482,7 @@ int launch_approx_ws(sps_ctx *c, hipStream_t s, const ApproxWs &ws, int n, int s
                 hipLaunchKernelGGL(k_approx_pair<MODE_LOGL_GRAD>, dim3(n), dim3(PAIR_T), 0, s, c->k, a);
                 break;
             case MODE_VJP: hipLaunchKernelGGL(k_approx_pair<MODE_VJP>, dim3(n), dim3(PAIR_T), 0, s, c->k, a); break;
-            case MODE_LOGPOST_GRAD:
-                hipLaunchKernelGGL(k_approx_pair<MODE_LOGPOST_GRAD>, dim3(n), dim3(PAIR_T), 0, s, c->k, a);
-                break;
-            default: return set_error(SPS_E_INVAL, "bad approx mode");
+            default: hipLaunchKernelGGL(k_approx_pair<MODE_LOGPOST_GRAD>, dim3(n), dim3(PAIR_T), 0, s, c->k, a); break;
         }
         if (tev) (void)hipEventRecord(tev[1], s);
         SPS_HIP(hipGetLastError());
@@ -479,17 +494,12 @@ int launch_approx_ws(sps_ctx *c, hipStream_t s, const ApproxWs &ws, int n, int s
     if (rc) return rc;
     ApproxArgs a{n, sfh, mode, ws.rec, bounds, prior, c->d_qf, c->d_qa, ws.perm, out_mag,
                  mode == MODE_VJP ? nullptr : out_val, out_grad};
-    const dim3 grid((n + WAVE - 1) / WAVE), block(WAVE);
-    const size_t lds_bytes = approx_lds_bytes(c->n_band, true);
     hipEvent_t *tev = timing_pair(c);
     if (tev) (void)hipEventRecord(tev[0], s);
-    switch (mode) {
-        case MODE_MAGS: hipLaunchKernelGGL(k_approx<MODE_MAGS>, grid, block, lds_bytes, s, c->k, a); break;
-        case MODE_LOGL: hipLaunchKernelGGL(k_approx<MODE_LOGL>, grid, block, lds_bytes, s, c->k, a); break;
-        case MODE_LOGL_GRAD: hipLaunchKernelGGL(k_approx<MODE_LOGL_GRAD>, grid, block, lds_bytes, s, c->k, a); break;
-        case MODE_VJP: hipLaunchKernelGGL(k_approx<MODE_VJP>, grid, block, lds_bytes, s, c->k, a); break;
-        case MODE_LOGPOST_GRAD: hipLaunchKernelGGL(k_approx<MODE_LOGPOST_GRAD>, grid, block, lds_bytes, s, c->k, a); break;
-        default: return set_error(SPS_E_INVAL, "bad approx mode");
+    switch (approx_lanes(n)) {
+        case 1: launch_k_approx<1>(c, s, n, mode, a); break;
+        case 2: launch_k_approx<2>(c, s, n, mode, a); break;
+        default: launch_k_approx<4>(c, s, n, mode, a); break;
     }
     if (tev) (void)hipEventRecord(tev[1], s);
     SPS_HIP(hipGetLastError());

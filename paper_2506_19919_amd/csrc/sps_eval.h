@@ -80,15 +80,17 @@ __host__ __device__ inline int approx_half_bytes(int n_band, bool pk) {
     const int t = n_band * NZ * HALF * 4;
     return pk ? (t > PK_BYTES ? t : PK_BYTES) : SLOT_W * HALF * 4;
 }
-// G lanes per galaxy: 64 / G galaxies per wave, 2 / G half regions
+// G lanes per galaxy (1, 2 or 4): 64 / G galaxies per wave, in n_halves(G) half regions (with G = 4
+// half of the one region is used)
+__host__ __device__ constexpr int n_halves(int G) { return G == 1 ? 2 : 1; }
 __host__ __device__ inline int approx_lds_bytes(int n_band, bool pk, int G = 1) {
-    return (2 / G) * (approx_half_bytes(n_band, pk) + RSKEW) + 2 * WAVE * 4;
+    return n_halves(G) * (approx_half_bytes(n_band, pk) + RSKEW) + 2 * WAVE * 4;
 }
 
 struct ApproxLds {
     char *base;
     int rstride;   // bytes from one half's region to the next
-    int w_off;     // the slice weights: after the 2 / G half regions
+    int w_off;     // the slice weights: after the half regions
     __device__ uint16_t *hi(int h) const { return (uint16_t *)(base + h * rstride); }
     __device__ uint8_t *lo(int h) const { return (uint8_t *)(base + h * rstride + SLOT_W * HALF * 2); }
     __device__ float *t(int h) const { return (float *)(base + h * rstride); }
@@ -98,7 +100,7 @@ struct ApproxLds {
 // the layout of a wave's block of approx_lds_bytes(n_band, pk, G) bytes at base
 __device__ inline ApproxLds approx_lds(char *base, int n_band, bool pk, int G) {
     const int rs = approx_half_bytes(n_band, pk) + RSKEW;
-    return ApproxLds{base, rs, (2 / G) * rs};
+    return ApproxLds{base, rs, n_halves(G) * rs};
 }
 
 // one lane's 24-bit column
@@ -338,29 +340,31 @@ typedef __bf16 b8v __attribute__((ext_vector_type(8)));
 
 // the pass's slice weights of the A rows 16 (2h + m) + l % 16 (0 outside the pass's bucket),
 // times the column scale; row: the lane's galaxy row
+template <int NM>
 __device__ inline void pass_weights(const ApproxLds &L, int lane, int row, int h, bool act, float f, float scale,
-                                    float (&w0)[2], float (&w1)[2]) {
+                                    float (&w0)[NM], float (&w1)[NM]) {
     float *w = L.w();
     w[row] = act ? (1.0f - f) * scale : 0.0f;
     w[WAVE + row] = act ? f * scale : 0.0f;
     __syncthreads();
     const int li = lane & 15;
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
+    for (int m = 0; m < NM; ++m) {
         w0[m] = w[16 * (2 * h + m) + li];
         w1[m] = w[WAVE + 16 * (2 * h + m) + li];
     }
 }
 
-// A fragments of k-step ks for the galaxy pair of blocks of half h: w0- and w1-scaled, split
-template <bool PK>
-__device__ inline void a_frags(const ApproxLds &L, int lane, int h, int ks, const float (&w0)[2],
-                               const float (&w1)[2], b8v (&a0h)[2], b8v (&a0l)[2], b8v (&a1h)[2], b8v (&a1l)[2]) {
+// A fragments of k-step ks for the NM blocks of 16 galaxies of half h: w0- and w1-scaled, split
+template <bool PK, int NM>
+__device__ inline void a_frags(const ApproxLds &L, int lane, int h, int ks, const float (&w0)[NM],
+                               const float (&w1)[NM], b8v (&a0h)[NM], b8v (&a0l)[NM], b8v (&a1h)[NM],
+                               b8v (&a1l)[NM]) {
     const int li = lane & 15, lk = lane >> 4;
     const uint16_t *hi = L.hi(h);
     const uint8_t *lo = L.lo(h);
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
+    for (int m = 0; m < NM; ++m) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int slot = 32 * ks + 8 * lk + e, c = 16 * m + li;
@@ -396,28 +400,28 @@ __device__ inline v4f mfma3(const b8v &ah, const b8v &al, const b8v &bh, const b
 
 // one contraction: D[g][n] = scale(g) sum_s w_s(g) sum_k A[g][k] B_s[k][n] over K = 96
 // (3 k-steps), N = 16 nbk; B fragments of node kb at q + kb QB_NODE (hi) and + n_z QB_NODE (lo).
-// M = 64 / G galaxies (G lanes per galaxy), in 2 / G halves of 32.
+// M = 64 / G galaxies (G lanes per galaxy), in halves of NM blocks of 16.
 template <int MODE_ADJ, bool PK, int G>
 __device__ __forceinline__ void contract(const DevConsts &k, const uint16_t *q, const ApproxLds &L, int lane, int kk,
                                          float f, float scale, int kmin, int kmax, int nbk, int n_out) {
     // both halves of the wave in one sweep: each B fragment is loaded once and multiplied into
     // the two halves' accumulators
-    constexpr int NH = 2 / G;
+    constexpr int NH = n_halves(G), NM = (G == 4) ? 1 : 2;
     const int li = lane & 15, lk = lane >> 4;
     const size_t lo_off = (size_t)k.n_z * QB_NODE;
-    v4f acc[NH][6][2];
+    v4f acc[NH][6][NM];
 #pragma unroll
     for (int h = 0; h < NH; ++h)
 #pragma unroll
         for (int nb = 0; nb < 6; ++nb)
 #pragma unroll
-            for (int m = 0; m < 2; ++m) acc[h][nb][m] = v4f{0.f, 0.f, 0.f, 0.f};
+            for (int m = 0; m < NM; ++m) acc[h][nb][m] = v4f{0.f, 0.f, 0.f, 0.f};
     for (int kb = kmin; kb <= kmax; ++kb) {
         const bool act = (kk == kb);
         if (__builtin_amdgcn_readfirstlane(__ballot(act) != 0ull) == 0) continue;
-        float w0[NH][2], w1[NH][2];
+        float w0[NH][NM], w1[NH][NM];
 #pragma unroll
-        for (int h = 0; h < NH; ++h) pass_weights(L, lane, lane / G, h, act, f, scale, w0[h], w1[h]);
+        for (int h = 0; h < NH; ++h) pass_weights<NM>(L, lane, lane / G, h, act, f, scale, w0[h], w1[h]);
         const uint16_t *b0 = q + (size_t)kb * QB_NODE + lane * 8, *b1 = b0 + QB_NODE;
 #pragma unroll 1
         for (int ks = 0; ks < KSTEPS; ++ks) {
@@ -427,9 +431,9 @@ __device__ __forceinline__ void contract(const DevConsts &k, const uint16_t *q, 
             // products first)
             size_t o = (size_t)ks * 512;
             b8v n0h = *(const b8v *)(b0 + o), n0l = *(const b8v *)(b0 + lo_off + o);
-            b8v a0h[NH][2], a0l[NH][2], a1h[NH][2], a1l[NH][2];
+            b8v a0h[NH][NM], a0l[NH][NM], a1h[NH][NM], a1l[NH][NM];
 #pragma unroll
-            for (int h = 0; h < NH; ++h) a_frags<PK>(L, lane, h, ks, w0[h], w1[h], a0h[h], a0l[h], a1h[h], a1l[h]);
+            for (int h = 0; h < NH; ++h) a_frags<PK, NM>(L, lane, h, ks, w0[h], w1[h], a0h[h], a0l[h], a1h[h], a1l[h]);
 #pragma unroll
             for (int nb = 0; nb < 6; ++nb) {
                 if (nb >= nbk) break;
@@ -444,11 +448,11 @@ __device__ __forceinline__ void contract(const DevConsts &k, const uint16_t *q, 
 #pragma unroll
                 for (int h = 0; h < NH; ++h)
 #pragma unroll
-                    for (int m = 0; m < 2; ++m) acc[h][nb][m] = mfma3(a0h[h][m], a0l[h][m], q0h, q0l, acc[h][nb][m]);
+                    for (int m = 0; m < NM; ++m) acc[h][nb][m] = mfma3(a0h[h][m], a0l[h][m], q0h, q0l, acc[h][nb][m]);
 #pragma unroll
                 for (int h = 0; h < NH; ++h)
 #pragma unroll
-                    for (int m = 0; m < 2; ++m) acc[h][nb][m] = mfma3(a1h[h][m], a1l[h][m], q1h, q1l, acc[h][nb][m]);
+                    for (int m = 0; m < NM; ++m) acc[h][nb][m] = mfma3(a1h[h][m], a1l[h][m], q1h, q1l, acc[h][nb][m]);
             }
         }
         __syncthreads();   // the next pass rewrites the weight slots
@@ -461,7 +465,7 @@ __device__ __forceinline__ void contract(const DevConsts &k, const uint16_t *q, 
         for (int nb = 0; nb < 6; ++nb)
             if (nb < nbk && 16 * nb + li < n_out) {
 #pragma unroll
-                for (int m = 0; m < 2; ++m) {
+                for (int m = 0; m < NM; ++m) {
                     const int r = 16 * nb + li, c = 16 * m + 4 * lk;
                     if (MODE_ADJ && PK) store4_24(L.hi(h), L.lo(h), prow(r) * HALF + c, acc[h][nb][m]);
                     else *(v4f *)(L.t(h) + r * HALF + c) = acc[h][nb][m];
@@ -491,8 +495,9 @@ __device__ __forceinline__ void contract_adjoint(const DevConsts &k, const uint1
 // parameters (MODE_LOGL_GRAD) for the lane's galaxy.  Every lane of the (single-wave)
 // workgroup must call it: the contractions are wave-wide and synchronise the workgroup.
 // Lanes with kk < 0 take part without contributing.  kmin/kmax: wave-uniform range of
-// the lanes' buckets.  L: the wave's LDS block.  G adjacent lanes may share a galaxy (value
-// and gradient only): they split its age bins and bands, and all end with the same results.
+// the lanes' buckets.  L: the wave's LDS block.  G adjacent lanes may share a galaxy: they
+// split its age bins and bands (with MODE_MAGS lane q forms the magnitudes of bands q, q + G, ...;
+// else all end with the same results).
 // VJP (with MODE_LOGL_GRAD): obs_g holds the caller's adjoints dL/dm_b of the magnitudes in
 // place of observations, and the gradient is their vector-Jacobian product (no likelihood).
 template <int MODE, bool PK, int G = 1, bool VJP = false>
@@ -501,7 +506,6 @@ __device__ __forceinline__ void approx_eval(const DevConsts &k, const float *led
                                    const float (&th)[NP], float zf, int kk, float f, double t_obs, double m0,
                                    int kmin, int kmax, const float *obs_g, const float *sig_g, uint32_t mask,
                                    float *mag_out, double &logl, float (&gr)[NP]) {
-    static_assert(G == 1 || MODE == MODE_LOGL_GRAD, "shared galaxies: value and gradient only");
     static_assert(!VJP || MODE == MODE_LOGL_GRAD, "the vector-Jacobian product is the gradient pass");
     const int nb = k.n_band;
     const int lane = opaque((int)threadIdx.x & (WAVE - 1));
