@@ -337,9 +337,14 @@ __device__ inline void logn_bin_e(double a_lo, double a_hi, double t_obs, double
 // The same nodes give the derivatives: d/dt_p = (1 / (t_p w)) int x phi and, with
 // dx/dw = -x/w - 2 at both edges, d/dw = int phi (x^2 / w + 2 x - 1 / w).  Rule, on the span
 // h measured in units of phi's local scale, h max(1, |x|): the midpoint up to 0.01, 2 points up
-// to 0.15, else 4-point panels of at most 0.5 (against FP64 normal-CDF differences over t_p
+// to 0.15, 4-point panels of at most 0.5 up to 1, and beyond it, where nothing cancels any more, the
+// difference of the tails at the bin's ends.  (Panels throughout took up to 256 of them in the
+// old bins of a narrow log-normal, and a wave its largest lane's number: 1470 nodes per galaxy
+// over a batch of widths 0.2 to 1.5, where its own lanes need 320.  Magnitudes of 100,000 galaxies in 6
+// bands, us per call: 117 then, 87 now; of a million 632 and 474.)  Against FP64 normal-CDF differences over t_p
 // 0.5-13 Gyr, w 0.15-2, t_obs 2-12 Gyr: bin masses within 1e-5 relative, where FP32 x itself
-// limits far tails, and the derivatives within 5e-7 of their sum over the bins).  The oldest
+// limits far tails, and the derivatives within 5e-7 of their sum over the bins; over t_p 1-12, w 0.2-1.5
+// the weights' summed error is 2.31e-7 on average (2.32e-7 with panels alone), 1.85e-6 at most.  The oldest
 // bin, open to t = 0, is the normal CDF at its upper edge (a tail value: no cancellation).
 struct Logn {
     float w, inv_w, ltp, inv_tpw;   // width, 1 / w, ln t_p, 1 / (t_p w)
@@ -390,9 +395,8 @@ __device__ inline void logn_bin(float a_lo, float a_hi, float t_obs, const Logn 
         const float c = x_hi - hw, dd = hw * GL2X;
         node(c - dd, 1.0f);
         node(c + dd, 1.0f);
-    } else {
-        int n = (int)ceilf(heff * 2.0f);
-        n = min(max(n, 1), 256);
+    } else if (heff <= 1.0f) {
+        const int n = heff <= 0.5f ? 1 : 2;
         hw = 0.5f * span * __builtin_amdgcn_rcpf((float)n);
         const float xlo = x_hi - span;
         for (int q = 0; q < n; ++q) {
@@ -400,6 +404,18 @@ __device__ inline void logn_bin(float a_lo, float a_hi, float t_obs, const Logn 
 #pragma unroll
             for (int g = 0; g < 4; ++g) node(fmaf(hw, GL4X[g], c), GL4W[g]);
         }
+    } else {
+        // the difference of the tails C(|x|) = erfc(|x| / sqrt 2) / 2 at the ends, and with phi' = -x phi
+        // int x phi = phi(x_lo) - phi(x_hi), int (x^2 - 1) phi = x_lo phi(x_lo) - x_hi phi(x_hi)
+        const float x_lo = x_hi - span;
+        const float c_lo = 0.5f * erfcf(0.7071067811865475f * fabsf(x_lo)), c_hi = 0.5f * erfcf(0.7071067811865475f * fabsf(x_hi));
+        m = x_lo > 0.0f ? c_lo - c_hi : x_hi <= 0.0f ? c_hi - c_lo : 1.0f - c_lo - c_hi;
+        if (DERIV) {
+            const float f_lo = phi_f(x_lo), f_hi = phi_f(x_hi), df = f_lo - f_hi;
+            d_tp = df * p.inv_tpw;
+            d_w = fmaf(x_lo * f_lo - x_hi * f_hi, p.inv_w, 2.0f * df);
+        }
+        return;
     }
     const float h = 0.3989422804014327f * hw;   // 1 / sqrt(2 pi) and the panel half-width
     m = h * s0;
