@@ -160,32 +160,21 @@ struct WeightsState {
 // and the sums over bins are combined across the group.  FOLD: the column holds P_age /
 // ws.scale (the smooth masses as computed, the burst added in proportion), which saves a
 // pass over the column; the contraction applies the scale.
-template <int G = 1, bool FOLD = false, typename Col>
+template <int G = 1, bool FOLD = false, int U = 1, typename Col>
 __device__ inline void forward_weights(const DevConsts &k, const float *ledge, int sfh, const float *th, double t_obs,
                                        Col col, float (&pz)[NZ], WeightsState &ws, int q = 0) {
     const float t_obs_f = (float)t_obs;
     double S = 0.0;
+    auto mass = [&](int i, float m, float, float, float) {
+        col[i] = m;
+        S += (double)m;
+    };
     if (sfh == SPS_SFH_DPL) {
         Dpl p = make_dpl(th[1], th[2], th[3]);
         dpl_at_obs(p, t_obs_f);
-        AgeEdges<G> ed(k, q);
-        for (int i = q; i < NA; i += G) {
-            float m, a, b, c, a_lo, a_hi;
-            ed.step(i, a_lo, a_hi);
-            dpl_bin<false>(a_lo, a_hi, t_obs_f, p, m, a, b, c);
-            col[i] = m;
-            S += (double)m;
-        }
+        walk_dpl<G, U, false>(k, q, t_obs_f, p, mass);
     } else {
-        const Logn p = make_logn(th[1], th[2]);
-        AgeEdges<G> ed(k, q);
-        for (int i = q; i < NA; i += G) {
-            float m, a, b, a_lo, a_hi;
-            ed.step(i, a_lo, a_hi);
-            logn_bin<false>(a_lo, a_hi, t_obs_f, p, m, a, b);
-            col[i] = m;
-            S += (double)m;
-        }
+        walk_logn<G, U, false>(k, q, t_obs_f, make_logn(th[1], th[2]), mass);
     }
     S = group_sum<G>(S);
     // burst: only the bins the triweight window [mu - 3 sigma, mu + 3 sigma] touches; a bin
@@ -232,7 +221,7 @@ __device__ inline void forward_weights(const DevConsts &k, const float *ledge, i
 // gradient of the weights: given dP_age (LDS column, slots 0..NA) and dP_Z,
 // accumulate d/d(theta_1..6).  With G lanes per galaxy, lane q takes the bins i = q mod G;
 // every lane of the group ends with the same totals.
-template <int G = 1, typename Col>
+template <int G = 1, int U = 1, typename Col>
 __device__ inline void adjoint_weights(const DevConsts &k, const float *ledge, int sfh, const float *th, double t_obs,
                                        const WeightsState &ws, Col col, const float (&pzbar)[NZ],
                                        float *g, int q = 0) {
@@ -241,43 +230,27 @@ __device__ inline void adjoint_weights(const DevConsts &k, const float *ledge, i
     float fbar = 0.0f, cbar = 0.0f, e1 = 0.0f, e2 = 0.0f, e3 = 0.0f;
     float A0 = 0.f, A1 = 0.f, A2 = 0.f, B0 = 0.f, B1 = 0.f, B2 = 0.f;
     double dA0 = 0.0, dA1 = 0.0, dB0 = 0.0, dB1 = 0.0;
-    Dpl p;
-    Logn lp;
-    if (sfh == SPS_SFH_DPL) {
-        p = make_dpl(th[1], th[2], th[3]);
-        dpl_at_obs(p, t_obs_f);
-    } else {
-        lp = make_logn(th[1], th[2]);
-    }
     // smooth part: dP_age/dF_burst = P_burst - P_smooth; the P_burst term is added below
-    AgeEdges<G> ed(k, q);
-    for (int i = q; i < NA; i += G) {
-        const float gbar = col[i];
-        float ps;
-        float m, mt, ma, mb, a_lo, a_hi;
-        double dm, dmt, dmw;
-        ed.step(i, a_lo, a_hi);
-        if (sfh == SPS_SFH_DPL) {
-            dpl_bin<true>(a_lo, a_hi, t_obs_f, p, m, mt, ma, mb);
-            ps = m * invS;
-        } else {
-            float fm, ft, fw;
-            logn_bin<true>(a_lo, a_hi, t_obs_f, lp, fm, ft, fw);
-            dm = fm;
-            dmt = ft;
-            dmw = fw;
-            ps = (float)(dm / ws.S);
-        }
-        fbar = fmaf(-gbar, ps, fbar);
-        const float psbar = (1.0f - fb) * gbar;
-        cbar = fmaf(psbar, ps, cbar);
-        if (sfh == SPS_SFH_DPL) {
+    if (sfh == SPS_SFH_DPL) {
+        Dpl p = make_dpl(th[1], th[2], th[3]);
+        dpl_at_obs(p, t_obs_f);
+        walk_dpl<G, U, true>(k, q, t_obs_f, p, [&](int i, float m, float mt, float ma, float mb) {
+            const float gbar = col[i], ps = m * invS;
+            fbar = fmaf(-gbar, ps, fbar);
+            const float psbar = (1.0f - fb) * gbar;
+            cbar = fmaf(psbar, ps, cbar);
             A0 = fmaf(psbar, mt, A0); A1 = fmaf(psbar, ma, A1); A2 = fmaf(psbar, mb, A2);
             B0 += mt; B1 += ma; B2 += mb;
-        } else {
-            dA0 += (double)psbar * dmt; dA1 += (double)psbar * dmw;
-            dB0 += dmt; dB1 += dmw;
-        }
+        });
+    } else {
+        walk_logn<G, U, true>(k, q, t_obs_f, make_logn(th[1], th[2]), [&](int i, float m, float mt, float mw, float) {
+            const float gbar = col[i], ps = (float)((double)m / ws.S);
+            fbar = fmaf(-gbar, ps, fbar);
+            const float psbar = (1.0f - fb) * gbar;
+            cbar = fmaf(psbar, ps, cbar);
+            dA0 += (double)psbar * (double)mt; dA1 += (double)psbar * (double)mw;
+            dB0 += (double)mt; dB1 += (double)mw;
+        });
     }
     // burst part over the triweight window
     const float inv_s3 = 1.0f / (3.0f * k.burst_sig);
@@ -507,6 +480,11 @@ __device__ __forceinline__ void approx_eval(const DevConsts &k, const float *led
                                    int kmin, int kmax, const float *obs_g, const float *sig_g, uint32_t mask,
                                    float *mag_out, double &logl, float (&gr)[NP]) {
     static_assert(!VJP || MODE == MODE_LOGL_GRAD, "the vector-Jacobian product is the gradient pass");
+    // bins the walks take at a time where a wave's lanes agree: bin by bin 981 us, two 913, four 905,
+    // value+gradient of a million DPL galaxies in 6 bands.  The samplers (PK = false) go bin by bin: the
+    // chains of a wave agree less and their loop already exceeds the instruction cache (102 us per
+    // evaluation of 65,536 chains with one, two or four).
+    constexpr int WALK = PK ? 4 : 1;
     const int nb = k.n_band;
     const int lane = opaque((int)threadIdx.x & (WAVE - 1));
     const ApproxLds L{L0.base, opaque(L0.rstride), opaque(L0.w_off)};
@@ -517,7 +495,7 @@ __device__ __forceinline__ void approx_eval(const DevConsts &k, const float *led
     const float *tcol = L.t(hl) + ll;   // T rows of this lane: tcol[r * HALF]
     float pz[NZ];
     WeightsState ws;
-    forward_weights<G, true>(k, ledge, sfh, th, t_obs, col, pz, ws, q);
+    forward_weights<G, true, WALK>(k, ledge, sfh, th, t_obs, col, pz, ws, q);
     if (q == 0) {
         col[NA] = 0.0f;
         col[NA + 1] = 0.0f;
@@ -598,7 +576,7 @@ __device__ __forceinline__ void approx_eval(const DevConsts &k, const float *led
     for (int r = nb * NZ + q; r < 32 * KSTEPS; r += G) col[r] = 0.0f;
     // dP_age(i) = sum_{b,j} sbar_b P_Z(j) Qz[b][j][i]
     contract_adjoint<PK, G>(k, qa, L, lane, kk, f, kmin, kmax);
-    adjoint_weights<G>(k, ledge, sfh, th, t_obs, ws, col, pzbar, gr, q);
+    adjoint_weights<G, WALK>(k, ledge, sfh, th, t_obs, ws, col, pzbar, gr, q);
 }
 
 // bounding function (App. C): theta = lo + (hi - lo) sigmoid(k (x - x0)) and d theta / d x

@@ -166,46 +166,66 @@ __device__ inline void dpl_node(const Dpl &p, float X, float wg, float &s, float
     }
 }
 
+// the span W of a bin in X and its upper end, formed directly as log1p of the age-edge ratio (young
+// bins are ~1e-5 wide at |X| ~ 1, where xhi - xlo would cancel in FP32).
+// Young bin (older edge within 2^-7 of t_obs): X_hi = X_obs + ln(1 - a_lo / t_obs) and
+// W = ln(1 + d) by series, no transcendental beyond one reciprocal
+constexpr float YOUNG = 0.0078125f;
+__device__ inline void dpl_span_young(float a_lo, float a_hi, float t_obs, const Dpl &p, float &xhi, float &span) {
+    xhi = p.x_obs + log1p_small(-a_lo * p.inv_tobs);
+    span = log1p_small((a_hi - a_lo) * __builtin_amdgcn_rcpf(t_obs - a_hi));
+}
+// bin closed before t_obs: hardware log2 / reciprocal, ~1 ulp, shifting every node of the bin alike
+// by < 3e-7; log1p(d) as log(u) d / (u - 1) with u = 1 + d, which absorbs the rounding of u
+__device__ inline void dpl_span(float a_lo, float a_hi, float t_obs, const Dpl &p, float &xhi, float &span) {
+    xhi = __builtin_amdgcn_logf(t_obs - a_lo) * 0.69314718055994531f - p.ltau;
+    const float d = (a_hi - a_lo) * __builtin_amdgcn_rcpf(t_obs - a_hi);
+    const float u = 1.0f + d;
+    span = (u == 1.0f) ? d : __builtin_amdgcn_logf(u) * 0.69314718055994531f * (d * __builtin_amdgcn_rcpf(u - 1.0f));
+}
+// a young bin's node: its span in X is below 9e-4, so the midpoint rule's relative error,
+// span^2 |g''/g| / 24 with |g''/g| <= (beta+1)^2 + (alpha+beta)^2 / 4 + ..., stays
+// below 5e-6 over alpha, beta <= 8 (typically below 1e-7)
+template <bool DERIV>
+__device__ inline float dpl_mid(const Dpl &p, float xhi, float span, float &s, float &sf, float &sa, float &sb) {
+    const float hw = 0.5f * span;
+    dpl_node<DERIV>(p, xhi - hw, 2.0f, s, sf, sa, sb);
+    return hw;
+}
+// two nodes, for spans of at most a quarter panel
+template <bool DERIV>
+__device__ inline float dpl_two(const Dpl &p, float xhi, float span, float &s, float &sf, float &sa, float &sb) {
+    const float hw = 0.5f * span, c = xhi - hw, d = hw * GL2X;
+    dpl_node<DERIV>(p, c - d, 1.0f, s, sf, sa, sb);
+    dpl_node<DERIV>(p, c + d, 1.0f, s, sf, sa, sb);
+    return hw;
+}
+// the bin's mass and derivatives from its node sums, half width and the oldest bin's tail
+template <bool DERIV>
+__device__ inline void dpl_finish(const Dpl &p, float hw, float s, float sf, float sa, float sb, float tail,
+                                  float tail_t, float tail_a, float tail_b, float &m, float &d_tau, float &d_al,
+                                  float &d_be) {
+    const float th = p.tau * hw;
+    m = fmaf(s, th, tail);
+    if (DERIV) {
+        d_tau = fmaf(hw, p.alpha * s - p.ab * sf, tail_t);
+        d_al = fmaf(-th, sa, tail_a);
+        d_be = fmaf(sb, th, tail_b);
+    }
+}
+
 // Mass formed in the age bin [a_lo, a_hi) (rate amplitude 1) and, if DERIV, its derivatives
 // w.r.t. (tau, alpha, beta).
-// The age edges of the bins i = q, q + G, ... in turn, each bin's edges read one bin ahead of their
-// use (the bins are contiguous: the upper edge of bin i is the lower edge of bin i + 1, so with
-// G = 1 each step reads one edge)
-template <int G>
-struct AgeEdges {
-    const DevConsts &k;
-    float lo, hi;
-    __device__ AgeEdges(const DevConsts &k_, int q) : k(k_), lo(k_.age_lo[q]), hi(k_.age_hi[q]) {}
-    // the edges of bin i, then those of bin i + G prefetched
-    __device__ void step(int i, float &a_lo, float &a_hi) {
-        a_lo = lo;
-        a_hi = hi;
-        const int in = min(i + G, NA - 1);
-        lo = (G == 1) ? hi : k.age_lo[in];
-        hi = k.age_hi[in];
-    }
-};
-
 template <bool DERIV>
 __device__ inline void dpl_bin(float a_lo, float a_hi, float t_obs, const Dpl &p, float &m, float &d_tau,
                                float &d_al, float &d_be) {
     m = d_tau = d_al = d_be = 0.0f;
     if (!(a_lo < t_obs)) return;
-    // span W of the bin in X is formed directly as log1p of the age-edge ratio (young bins
-    // are ~1e-5 wide at |X| ~ 1, where xhi - xlo would cancel in FP32)
     float xhi, span, tail = 0.0f, tail_t = 0.0f, tail_a = 0.0f, tail_b = 0.0f;
-    if (a_hi <= 0.0078125f * t_obs) {
-        // young bin (older edge within 2^-7 of t_obs): X_hi = X_obs + ln(1 - a_lo / t_obs) and
-        // W = ln(1 + d) by series, no transcendental beyond one reciprocal
-        xhi = p.x_obs + log1p_small(-a_lo * p.inv_tobs);
-        span = log1p_small((a_hi - a_lo) * __builtin_amdgcn_rcpf(t_obs - a_hi));
+    if (a_hi <= YOUNG * t_obs) {
+        dpl_span_young(a_lo, a_hi, t_obs, p, xhi, span);
     } else if (a_hi < t_obs) {
-        // hardware log2 / reciprocal: ~1 ulp, shifting every node of the bin alike by < 3e-7;
-        // log1p(d) as log(u) d / (u - 1) with u = 1 + d, which absorbs the rounding of u
-        xhi = __builtin_amdgcn_logf(t_obs - a_lo) * 0.69314718055994531f - p.ltau;
-        const float d = (a_hi - a_lo) * __builtin_amdgcn_rcpf(t_obs - a_hi);
-        const float u = 1.0f + d;
-        span = (u == 1.0f) ? d : __builtin_amdgcn_logf(u) * 0.69314718055994531f * (d * __builtin_amdgcn_rcpf(u - 1.0f));
+        dpl_span(a_lo, a_hi, t_obs, p, xhi, span);
     } else {
         xhi = __builtin_amdgcn_logf(t_obs - a_lo) * 0.69314718055994531f - p.ltau;
         // oldest bin: panels down to the cut xc, where u = e^{(alpha+beta) X} <= e^-4; below
@@ -238,17 +258,10 @@ __device__ inline void dpl_bin(float a_lo, float a_hi, float t_obs, const Dpl &p
     }
     float s = 0.0f, sf = 0.0f, sa = 0.0f, sb = 0.0f, hw;
     const float npan = span * p.inv_w;
-    if (a_hi <= 0.0078125f * t_obs) {
-        // young bin: its span in X is below 9e-4, so the midpoint rule's relative error,
-        // span^2 |g''/g| / 24 with |g''/g| <= (beta+1)^2 + (alpha+beta)^2 / 4 + ..., stays
-        // below 5e-6 over alpha, beta <= 8 (typically below 1e-7)
-        hw = 0.5f * span;
-        dpl_node<DERIV>(p, xhi - hw, 2.0f, s, sf, sa, sb);
+    if (a_hi <= YOUNG * t_obs) {
+        hw = dpl_mid<DERIV>(p, xhi, span, s, sf, sa, sb);
     } else if (npan <= 0.25f) {
-        hw = 0.5f * span;
-        const float c = xhi - hw, d = hw * GL2X;
-        dpl_node<DERIV>(p, c - d, 1.0f, s, sf, sa, sb);
-        dpl_node<DERIV>(p, c + d, 1.0f, s, sf, sa, sb);
+        hw = dpl_two<DERIV>(p, xhi, span, s, sf, sa, sb);
     } else {
         int n = (int)ceilf(npan);
         n = min(max(n, 1), 64);
@@ -260,13 +273,7 @@ __device__ inline void dpl_bin(float a_lo, float a_hi, float t_obs, const Dpl &p
             for (int g = 0; g < 4; ++g) dpl_node<DERIV>(p, fmaf(hw, GL4X[g], c), GL4W[g], s, sf, sa, sb);
         }
     }
-    const float th = p.tau * hw;
-    m = fmaf(s, th, tail);
-    if (DERIV) {
-        d_tau = fmaf(hw, p.alpha * s - p.ab * sf, tail_t);
-        d_al = fmaf(-th, sa, tail_a);
-        d_be = fmaf(sb, th, tail_b);
-    }
+    dpl_finish<DERIV>(p, hw, s, sf, sa, sb, tail, tail_t, tail_a, tail_b, m, d_tau, d_al, d_be);
 }
 
 // FP64 variant (exact FP64 path): 8-point Gauss-Legendre panels of half the
@@ -358,12 +365,45 @@ __device__ inline Logn make_logn(float tp, float w) {
     return p;
 }
 
+// upper end in x, span and span in units of phi's local scale (phi changes over 1 / |x| in its
+// tails) of a bin closed before t_obs
+__device__ inline void logn_span(float a_lo, float a_hi, float t_obs, const Logn &p, float x_hi, float &span,
+                                 float &heff) {
+    const float d = (a_hi - a_lo) * __builtin_amdgcn_rcpf(t_obs - a_hi), u = 1.0f + d;
+    const float dl = (u == 1.0f) ? d : __builtin_amdgcn_logf(u) * 0.69314718055994531f * (d * __builtin_amdgcn_rcpf(u - 1.0f));
+    span = dl * p.inv_w;
+    heff = span * fmaxf(1.0f, fmaxf(fabsf(x_hi), fabsf(x_hi - span)));
+}
+__device__ inline float logn_x(float a_lo, float t_obs, const Logn &p) {
+    return (__builtin_amdgcn_logf(t_obs - a_lo) * 0.69314718055994531f - p.ltp) * p.inv_w - p.w;
+}
+template <bool DERIV>
+__device__ inline void logn_node(float x, float wg, float &s0, float &s1, float &s2) {
+    const float f = wg * __builtin_amdgcn_exp2f(-0.72134752044448170f * x * x);   // e^{-x^2/2}
+    s0 += f;
+    if (DERIV) {
+        s1 = fmaf(f, x, s1);
+        s2 = fmaf(f * x, x, s2);
+    }
+}
+template <bool DERIV>
+__device__ inline void logn_finish(const Logn &p, float hw, float s0, float s1, float s2, float &m, float &d_tp,
+                                   float &d_w) {
+    const float h = 0.3989422804014327f * hw;   // 1 / sqrt(2 pi) and the panel half-width
+    m = h * s0;
+    if (DERIV) {
+        d_tp = h * s1 * p.inv_tpw;
+        d_w = h * fmaf(s2 - s0, p.inv_w, 2.0f * s1);
+    }
+}
+constexpr float LOGN_MID = 0.01f, LOGN_TWO = 0.15f, LOGN_PANELS = 1.0f;   // largest spans of the rules
+
 template <bool DERIV>
 __device__ inline void logn_bin(float a_lo, float a_hi, float t_obs, const Logn &p, float &m, float &d_tp,
                                 float &d_w) {
     m = d_tp = d_w = 0.0f;
     if (!(a_lo < t_obs)) return;
-    const float x_hi = (__builtin_amdgcn_logf(t_obs - a_lo) * 0.69314718055994531f - p.ltp) * p.inv_w - p.w;
+    const float x_hi = logn_x(a_lo, t_obs, p);
     if (!(a_hi < t_obs)) {
         m = Phi_f(x_hi);
         if (DERIV) {
@@ -373,36 +413,25 @@ __device__ inline void logn_bin(float a_lo, float a_hi, float t_obs, const Logn 
         }
         return;
     }
-    const float d = (a_hi - a_lo) * __builtin_amdgcn_rcpf(t_obs - a_hi), u = 1.0f + d;
-    const float dl = (u == 1.0f) ? d : __builtin_amdgcn_logf(u) * 0.69314718055994531f * (d * __builtin_amdgcn_rcpf(u - 1.0f));
-    const float span = dl * p.inv_w;
-    // phi changes over 1 / |x| in its tails: the rule is chosen on the span in those units
-    const float heff = span * fmaxf(1.0f, fmaxf(fabsf(x_hi), fabsf(x_hi - span)));
+    float span, heff;
+    logn_span(a_lo, a_hi, t_obs, p, x_hi, span, heff);
     float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, hw;
-    auto node = [&](float x, float wg) {
-        const float f = wg * __builtin_amdgcn_exp2f(-0.72134752044448170f * x * x);   // e^{-x^2/2}
-        s0 += f;
-        if (DERIV) {
-            s1 = fmaf(f, x, s1);
-            s2 = fmaf(f * x, x, s2);
-        }
-    };
-    if (heff <= 0.01f) {
+    if (heff <= LOGN_MID) {
         hw = 0.5f * span;
-        node(x_hi - hw, 2.0f);
-    } else if (heff <= 0.15f) {
+        logn_node<DERIV>(x_hi - hw, 2.0f, s0, s1, s2);
+    } else if (heff <= LOGN_TWO) {
         hw = 0.5f * span;
         const float c = x_hi - hw, dd = hw * GL2X;
-        node(c - dd, 1.0f);
-        node(c + dd, 1.0f);
-    } else if (heff <= 1.0f) {
+        logn_node<DERIV>(c - dd, 1.0f, s0, s1, s2);
+        logn_node<DERIV>(c + dd, 1.0f, s0, s1, s2);
+    } else if (heff <= LOGN_PANELS) {
         const int n = heff <= 0.5f ? 1 : 2;
         hw = 0.5f * span * __builtin_amdgcn_rcpf((float)n);
         const float xlo = x_hi - span;
         for (int q = 0; q < n; ++q) {
             const float c = xlo + (float)(2 * q + 1) * hw;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) node(fmaf(hw, GL4X[g], c), GL4W[g]);
+            for (int g = 0; g < 4; ++g) logn_node<DERIV>(fmaf(hw, GL4X[g], c), GL4W[g], s0, s1, s2);
         }
     } else {
         // the difference of the tails C(|x|) = erfc(|x| / sqrt 2) / 2 at the ends, and with phi' = -x phi
@@ -417,11 +446,143 @@ __device__ inline void logn_bin(float a_lo, float a_hi, float t_obs, const Logn 
         }
         return;
     }
-    const float h = 0.3989422804014327f * hw;   // 1 / sqrt(2 pi) and the panel half-width
-    m = h * s0;
-    if (DERIV) {
-        d_tp = h * s1 * p.inv_tpw;
-        d_w = h * fmaf(s2 - s0, p.inv_w, 2.0f * s1);
+    logn_finish<DERIV>(p, hw, s0, s1, s2, m, d_tp, d_w);
+}
+
+// ------------------------------------------------------------------ walk over the age bins
+// f(i, m, d1, d2, d3) for the bins i = q, q + G, ... in turn (G lanes share a galaxy; d3 = 0 for the
+// log-normal).  A bin is a chain of ~25 dependent operations, some of them quarter rate, and a SIMD
+// holds two waves or fewer: where every lane of the wave takes the same short rule the walk goes U
+// bins at a time without branches, so that U chains overlap.  Ages increase, so these are the young
+// end and the bins after it; from the first bin too wide for two nodes on, or where the lanes
+// differ, bin by bin.  Every bin keeps its nodes and its place in the sums.  The next edges are read
+// ahead of their use.
+// With U = 1 it is bin by bin throughout.
+template <int G, int U>
+struct AgeEdges {   // the edges of the bins i, i + G, ... i + (U - 1) G, read ahead
+    float lo[U], hi[U];
+    __device__ AgeEdges(const DevConsts &k, int i) { load(k, i); }
+    __device__ void load(const DevConsts &k, int i) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = min(i + u * G, NA - 1);
+            lo[u] = (G == 1 && u > 0) ? hi[u - 1] : k.age_lo[j];   // the bins are contiguous
+            hi[u] = k.age_hi[j];
+        }
+    }
+    __device__ void take(float (&al)[U], float (&ah)[U]) const {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            al[u] = lo[u];
+            ah[u] = hi[u];
+        }
+    }
+};
+
+template <int G, int U, bool DERIV, typename F>
+__device__ inline void walk_dpl(const DevConsts &k, int q, float t_obs, const Dpl &p, F f) {
+    AgeEdges<G, U> next(k, q);
+    bool two = U > 1;
+    for (int b = 0; b + q < NA;) {
+        const int i = b + q;
+        float al[U], ah[U];
+        next.take(al, ah);
+        if (two && b + U * G <= NA) {
+            float xhi[U], span[U];
+            if (__all(ah[U - 1] <= YOUNG * t_obs)) {
+                next.load(k, i + U * G);
+                b += U * G;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float s = 0.0f, sf = 0.0f, sa = 0.0f, sb = 0.0f, m, mt = 0.0f, ma = 0.0f, mb = 0.0f;
+                    dpl_span_young(al[u], ah[u], t_obs, p, xhi[u], span[u]);
+                    const float hw = dpl_mid<DERIV>(p, xhi[u], span[u], s, sf, sa, sb);
+                    dpl_finish<DERIV>(p, hw, s, sf, sa, sb, 0.0f, 0.0f, 0.0f, 0.0f, m, mt, ma, mb);
+                    f(i + u * G, m, mt, ma, mb);
+                }
+                continue;
+            }
+            if (__all(ah[0] > YOUNG * t_obs)) {
+                bool ok = ah[U - 1] < t_obs;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    dpl_span(al[u], ah[u], t_obs, p, xhi[u], span[u]);
+                    ok = ok && span[u] * p.inv_w <= 0.25f;
+                }
+                two = __all(ok);
+                if (two) {
+                    next.load(k, i + U * G);
+                    b += U * G;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        float s = 0.0f, sf = 0.0f, sa = 0.0f, sb = 0.0f, m, mt = 0.0f, ma = 0.0f, mb = 0.0f;
+                        const float hw = dpl_two<DERIV>(p, xhi[u], span[u], s, sf, sa, sb);
+                        dpl_finish<DERIV>(p, hw, s, sf, sa, sb, 0.0f, 0.0f, 0.0f, 0.0f, m, mt, ma, mb);
+                        f(i + u * G, m, mt, ma, mb);
+                    }
+                    continue;
+                }
+            }
+        }
+        next.load(k, i + G);
+        b += G;
+        float m, mt, ma, mb;
+        dpl_bin<DERIV>(al[0], ah[0], t_obs, p, m, mt, ma, mb);
+        f(i, m, mt, ma, mb);
+    }
+}
+
+template <int G, int U, bool DERIV, typename F>
+__device__ inline void walk_logn(const DevConsts &k, int q, float t_obs, const Logn &p, F f) {
+    AgeEdges<G, U> next(k, q);
+    bool two = U > 1;
+    for (int b = 0; b + q < NA;) {
+        const int i = b + q;
+        float al[U], ah[U];
+        next.take(al, ah);
+        if (two && b + U * G <= NA) {
+            float x[U], span[U], heff[U];
+            bool ok = ah[U - 1] < t_obs, mid = ok;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                x[u] = logn_x(al[u], t_obs, p);
+                logn_span(al[u], ah[u], t_obs, p, x[u], span[u], heff[u]);
+                mid = mid && heff[u] <= LOGN_MID;
+                ok = ok && heff[u] <= LOGN_TWO;
+            }
+            two = __all(ok);
+            if (two) {
+                next.load(k, i + U * G);
+                b += U * G;
+                if (__all(mid)) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, m, mt = 0.0f, mw = 0.0f;
+                        const float hw = 0.5f * span[u];
+                        logn_node<DERIV>(x[u] - hw, 2.0f, s0, s1, s2);
+                        logn_finish<DERIV>(p, hw, s0, s1, s2, m, mt, mw);
+                        f(i + u * G, m, mt, mw, 0.0f);
+                    }
+                } else {   // a lane whose span is a midpoint's gives its second node no weight
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, m, mt = 0.0f, mw = 0.0f;
+                        const float hw = 0.5f * span[u], c = x[u] - hw;
+                        const bool one = heff[u] <= LOGN_MID;
+                        logn_node<DERIV>(one ? c : fmaf(-hw, GL2X, c), one ? 2.0f : 1.0f, s0, s1, s2);
+                        logn_node<DERIV>(fmaf(hw, GL2X, c), one ? 0.0f : 1.0f, s0, s1, s2);
+                        logn_finish<DERIV>(p, hw, s0, s1, s2, m, mt, mw);
+                        f(i + u * G, m, mt, mw, 0.0f);
+                    }
+                }
+                continue;
+            }
+        }
+        next.load(k, i + G);
+        b += G;
+        float m, mt, mw;
+        logn_bin<DERIV>(al[0], ah[0], t_obs, p, m, mt, mw);
+        f(i, m, mt, mw, 0.0f);
     }
 }
 
