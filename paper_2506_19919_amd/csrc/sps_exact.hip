@@ -24,26 +24,8 @@ namespace sps {
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef double d4v __attribute__((ext_vector_type(4)));
 
-constexpr int BM = 64, BN = 64;
 constexpr int NSSP = NZ * NA;
 constexpr int EPI_PHOT = 0, EPI_PHOT_DUST = 1, EPI_STORE = 2;
-
-template <int P> struct Prec;
-template <> struct Prec<SPS_F64> {
-    typedef double T;
-    typedef double E;   // epilogue arithmetic
-    static constexpr int BK = 16, PAD = 1, KSTEP = 4;
-};
-template <> struct Prec<SPS_F32> {
-    typedef float T;
-    typedef float E;
-    static constexpr int BK = 32, PAD = 1, KSTEP = 4;
-};
-template <> struct Prec<SPS_BF16X> {
-    typedef uint16_t T;
-    typedef float E;
-    static constexpr int BK = 64, PAD = 8, KSTEP = 32;
-};
 
 __device__ inline uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }   // nearest even
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
@@ -81,193 +63,142 @@ inline FiltConst filt_const(const double *fc, const double *fs) {
 constexpr int round_up(int x, int m) { return (x + m - 1) / m * m; }
 static_assert(S_PAD % 128 == 0 && S_PAD >= NSSP, "SSP padding");
 
-struct GemmArgs {
-    int M, N, K_valid, K_pad;
-    const void *A_hi, *A_lo;   // [M][K_pad] row-major
-    int lda;
-    const void *B_hi, *B_lo;   // L as [S][n_wave]
-    int ldb;
-    bool b_nk;                 // false: B[k][n] = L[k][n] (k = SSP);  true: B[k][n] = L[n][k] (k = wavelength)
-    float *C;                  // EPI_STORE: [M][ldc]
-    int ldc;
-    // photometry epilogue
-    const void *params;        // [10][M] (double for F64, else float)
-    const void *z;
-    const double *wave, *trap;
-    int n_band;
-    double fc[NB_MAX], fs[NB_MAX];
-    float *part;               // [k_split][n_tiles_n][M][npart]
-    int npart;
-    int k_chunk;               // K columns per blockIdx.z (a multiple of BK)
+// ------------------------------------------------------------------ FP64 GEMM + photometry
+// SED[g][l] = sum_s W[g][s] L[s][l] on v_mfma_f64_16x16x4, then the band partials of its wavelengths.
+// A small batch is the rule (the parity batch is 64 galaxies), and a chain of loads, not the 4 us of
+// products or bytes, is its time: a block takes D_ROWS galaxies x D_LAM wavelengths, so that 64
+// galaxies x 2000 wavelengths fill the chip, its waves split the SSP axis, each reads its operands
+// straight into the fragments with the next batch of loads in flight, and the waves' sums meet in LDS,
+// where a thread owns one (galaxy, wavelength) for the transmissions.  (64 x 64 tiles with the SSP axis cut
+// over 15 blocks repeated those exponentials 15 times: 60 us of 82 per call at 64 x 2000, 6 bands; these take 19.)
+// Large batches take several wavelength tiles per block, which bounds the partials.
+constexpr int D_ROWS = 32, D_LAM = 16, D_WAVES = 8, D_T = D_WAVES * WAVE;
+constexpr int D_K = S_PAD / D_WAVES, D_G = D_K / 8, D_BATCH = 3;   // SSPs, groups of 8, groups per load batch
+static_assert(S_PAD % (8 * D_WAVES) == 0 && D_G % D_BATCH == 0 && D_ROWS * D_LAM == D_T, "FP64 tile");
+// wavelength tiles per block, and whether it takes them two at a time, each weight fragment then feeding
+// two products (a CU holds one block at a time: from a block per CU on, fewer loads count for more than more
+// blocks).  us per call at 2000 wavelengths, 6 bands, one at a time / two: 64 galaxies 36.9 / 40.0, 65
+// 47.3 / 40.8, 500 148 / 106, 4096 917 / 600 (192, 883 on the tiles above).
+constexpr int D_WIDE = 256;
+static int f64_tiles(int n, int n_wave, bool *wide) {
+    const int blocks = (n + D_ROWS - 1) / D_ROWS * ((n_wave + D_LAM - 1) / D_LAM);
+    *wide = blocks > D_WIDE;
+    return *wide ? std::min(4, std::max(2, blocks / 2048)) & ~1 : 1;
+}
+static int f64_parts(int n, int n_wave) {
+    bool wide;
+    const int t = f64_tiles(n, n_wave, &wide) * D_LAM;
+    return (n_wave + t - 1) / t;
+}
+struct DArgs {
+    int n, n_wave, n_band, tiles;   // tiles: wavelength tiles per block, a multiple of NT
+    const double *w, *lum;          // [n][S_PAD], [NSSP][n_wave]
+    const double *params, *z, *wave, *trap;
+    FiltConst fl;
+    double *part;                   // [blockIdx.x][n][2 n_band]: numerators, normalisers
 };
 
-// ------------------------------------------------------------------ GEMM + epilogue
-template <int P, int EPI>
-__global__ void __launch_bounds__(256) k_exact_gemm(GemmArgs a) {
-    typedef typename Prec<P>::T T;
-    typedef typename Prec<P>::E E;
-    constexpr int BK = Prec<P>::BK, LDK = BK + Prec<P>::PAD, KSTEP = Prec<P>::KSTEP;
-    constexpr bool SPLIT = (P == SPS_BF16X);
-    constexpr int NS = SPLIT ? 2 : 1;
-    typedef typename std::conditional<P == SPS_F64, d4v, f4v>::type AccT;
-    typedef typename std::conditional<P == SPS_F64, double, float>::type AccE;
-    // A/B tiles, re-used as the SED tile in the epilogue
-    constexpr int TILE_BYTES = NS * (BM + BN) * LDK * (int)sizeof(T);
-    constexpr int SED_BYTES = BM * (BN + 1) * (int)sizeof(AccE);
-    __shared__ __attribute__((aligned(16))) char smem[TILE_BYTES > SED_BYTES ? TILE_BYTES : SED_BYTES];
-    T (*As)[BM][LDK] = reinterpret_cast<T (*)[BM][LDK]>(smem);
-    T (*Bs)[BN][LDK] = reinterpret_cast<T (*)[BN][LDK]>(smem + NS * BM * LDK * sizeof(T));
-
-    const int tile_m = blockIdx.y * BM, tile_n = blockIdx.x * BN;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int li = lane & 15, lk = lane >> 4;
-    // output row of accumulator register r in lane group lk: FP32 16x16x4 and BF16 16x16x32
-    // hold rows 4*lk + r; FP64 16x16x4 holds rows 4*r + lk
-    auto out_row = [](int lk_, int r) { return (P == SPS_F64) ? 4 * r + lk_ : 4 * lk_ + r; };
-
-    AccT acc[2][2];
+template <int NT>
+__global__ void __launch_bounds__(D_T, 2) k_exact_phot64(DArgs a) {
+    __shared__ double red[NT][D_WAVES][D_ROWS * D_LAM];
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), m0 = blockIdx.y * D_ROWS;
+    // SSPs k0 + 8 t + 2 lk and + 1 of group t feed the k slots lk of two products, from A and B alike
+    const int k0 = w * D_K + 2 * lk;
+    const double *ap[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int t = 0; t < 2; ++t) ap[t] = a.w + (size_t)min(m0 + 16 * t + li, a.n - 1) * S_PAD + k0;
+    const int row = m0 + (tid >> 4), g = min(row, a.n - 1);
+    const double tauv = a.params[(size_t)7 * a.n + g], delta = a.params[(size_t)8 * a.n + g];
+    const double ffl = a.params[(size_t)9 * a.n + g], opz = 1.0 + a.z[g];
+    double num[NB_MAX], nrm[NB_MAX];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = AccT{0, 0, 0, 0};
-
-    const T *Ah = (const T *)a.A_hi, *Al = (const T *)a.A_lo;
-    const T *Bh = (const T *)a.B_hi, *Bl = (const T *)a.B_lo;
-    const int k_beg = blockIdx.z * a.k_chunk, k_end = min(a.K_pad, k_beg + a.k_chunk);
-    for (int k0 = k_beg; k0 < k_end; k0 += BK) {
-        // ---- stage A: rows = galaxies (beyond M: zero); columns padded with zeros in memory
-        for (int e = tid; e < BM * BK; e += 256) {
-            const int r = e / BK, c = e % BK, m = tile_m + r;
-            const bool in = m < a.M;
-            const size_t off = (size_t)m * a.lda + k0 + c;
-            As[0][r][c] = in ? Ah[off] : (T)0;
-            if (SPLIT) As[1][r][c] = in ? Al[off] : (T)0;
+    for (int b = 0; b < NB_MAX; ++b) num[b] = nrm[b] = 0.0;
+    const int l_end = min(a.n_wave, (int)(blockIdx.x + 1) * a.tiles * D_LAM);
+    for (int l0 = blockIdx.x * a.tiles * D_LAM; l0 < l_end; l0 += NT * D_LAM) {
+        const double *bp[NT];
+        d4v acc[2][NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            bp[j] = a.lum + min(l0 + j * D_LAM + li, a.n_wave - 1);
+            acc[0][j] = acc[1][j] = d4v{0, 0, 0, 0};
         }
-        // ---- stage B into Bs[n][k]
-        if (!a.b_nk) {
-            for (int e = tid; e < BN * BK; e += 256) {
-                const int r = e % BN, c = e / BN, n = tile_n + r, kq = k0 + c;
-                const bool in = n < a.N && kq < a.K_valid;
-                const size_t off = (size_t)kq * a.ldb + n;
-                Bs[0][r][c] = in ? Bh[off] : (T)0;
-                if (SPLIT) Bs[1][r][c] = in ? Bl[off] : (T)0;
-            }
-        } else {
-            for (int e = tid; e < BN * BK; e += 256) {
-                const int r = e / BK, c = e % BK, n = tile_n + r, kq = k0 + c;
-                const bool in = n < a.N && kq < a.K_valid;
-                const size_t off = (size_t)n * a.ldb + kq;
-                Bs[0][r][c] = in ? Bh[off] : (T)0;
-                if (SPLIT) Bs[1][r][c] = in ? Bl[off] : (T)0;
-            }
+        double av[2][D_BATCH][2][2], bv[2][D_BATCH][2][NT];
+        auto load = [&](int q, int t0) {
+#pragma unroll
+            for (int u = 0; u < D_BATCH; ++u)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int ks = k0 + 8 * (t0 + u) + e;
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) av[q][u][t][e] = ap[t][8 * (t0 + u) + e];
+                    // the padding SSPs have weight 0
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) {
+                        const double v = bp[j][(size_t)min(ks, NSSP - 1) * a.n_wave];
+                        bv[q][u][e][j] = ks < NSSP ? v : 0.0;
+                    }
+                }
+        };
+        load(0, 0);
+#pragma unroll
+        for (int t0 = 0, q = 0; t0 < D_G; t0 += D_BATCH, q ^= 1) {
+            if (t0 + D_BATCH < D_G) load(q ^ 1, t0 + D_BATCH);
+#pragma unroll
+            for (int u = 0; u < D_BATCH; ++u)
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int j = 0; j < NT; ++j)
+                            acc[t][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[q][u][t][e], bv[q][u][e][j], acc[t][j], 0, 0, 0);
         }
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) red[j][w][(16 * t + 4 * r + lk) * D_LAM + li] = acc[t][j][r];
         __syncthreads();
+#pragma unroll 1
+        for (int j = 0; j < NT; ++j) {
+            double s = 0.0;
 #pragma unroll
-        for (int kk = 0; kk < BK; kk += KSTEP) {
+            for (int i = 0; i < D_WAVES; ++i) s += red[j][i][tid];
+            const int l = l0 + j * D_LAM + (tid & (D_LAM - 1));
+            if (l < a.n_wave) {
+                const double lam = a.wave[l], q = a.trap[l];
+                const double xd = exp(delta * log(lam * (1.0 / 5500.0))), F = ffl + (1.0 - ffl) * exp(-tauv * xd);
+                const double wn = s * F * (lam * q), wq = q / lam;
 #pragma unroll
-            for (int ti = 0; ti < 2; ++ti) {
-                const int ra = wm * 32 + ti * 16 + li;
-#pragma unroll
-                for (int tj = 0; tj < 2; ++tj) {
-                    const int rb = wn * 32 + tj * 16 + li;
-                    if constexpr (P == SPS_F64) {
-                        acc[ti][tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(As[0][ra][kk + lk], Bs[0][rb][kk + lk],
-                                                                           acc[ti][tj], 0, 0, 0);
-                    } else if constexpr (P == SPS_F32) {
-                        acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(As[0][ra][kk + lk], Bs[0][rb][kk + lk],
-                                                                           acc[ti][tj], 0, 0, 0);
-                    } else {
-                        const int ko = kk + 8 * lk;
-                        const b8v ah = *reinterpret_cast<const b8v *>(&As[0][ra][ko]);
-                        const b8v al = *reinterpret_cast<const b8v *>(&As[1][ra][ko]);
-                        const b8v bh = *reinterpret_cast<const b8v *>(&Bs[0][rb][ko]);
-                        const b8v bl = *reinterpret_cast<const b8v *>(&Bs[1][rb][ko]);
-                        acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, acc[ti][tj], 0, 0, 0);
-                        acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, acc[ti][tj], 0, 0, 0);
-                        acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, acc[ti][tj], 0, 0, 0);
+                for (int b = 0; b < NB_MAX; ++b) {
+                    if (b >= a.n_band) break;
+                    const double x = (opz * lam - a.fl.fc[b]) * a.fl.inv_fs[b], y = -0.5 * x * x;
+                    if (y > -746.0) {   // below, exp(y) = 0
+                        const double tb = exp(y);
+                        num[b] += tb * wn;
+                        nrm[b] += tb * wq;
                     }
                 }
             }
         }
-        __syncthreads();
+        __syncthreads();   // the next tiles' sums take the slots
     }
-
-    if constexpr (EPI == EPI_STORE) {
+    auto over_lambda = [](double v) {   // over the 16 lanes of a galaxy
+        v = dpp_add<0x128>(v);
+        v = dpp_add<0x124>(v);
+        v = dpp_add<0x122>(v);
+        return dpp_add<0x121>(v);
+    };
+    double *out = a.part + ((size_t)blockIdx.x * a.n + g) * 2 * a.n_band;
 #pragma unroll
-        for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-            for (int tj = 0; tj < 2; ++tj)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int m = tile_m + wm * 32 + ti * 16 + out_row(lk, r);
-                    const int n = tile_n + wn * 32 + tj * 16 + li;
-                    if (m < a.M && n < a.ldc) a.C[(size_t)m * a.ldc + n] = (float)acc[ti][tj][r];
-                }
-        return;
-    } else {
-        // ---- SED tile -> LDS, then one galaxy row per 4 threads
-        AccE (*sed)[BN + 1] = reinterpret_cast<AccE (*)[BN + 1]>(smem);
-#pragma unroll
-        for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-            for (int tj = 0; tj < 2; ++tj)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sed[wm * 32 + ti * 16 + out_row(lk, r)][wn * 32 + tj * 16 + li] = acc[ti][tj][r];
-        __syncthreads();
-        const int row = tid >> 2, sub = tid & 3, g = tile_m + row;
-        constexpr int NPB = (EPI == EPI_PHOT_DUST) ? 5 : 2;   // num, N [, dnum/dtauV, dnum/ddelta, dnum/dFfloor]
-        E acc_p[NB_MAX][NPB];
-#pragma unroll
-        for (int b = 0; b < NB_MAX; ++b)
-#pragma unroll
-            for (int q = 0; q < NPB; ++q) acc_p[b][q] = 0;
-        const int gg = g < a.M ? g : a.M - 1;
-        const E *prm = (const E *)a.params;
-        const E tauv = prm[(size_t)7 * a.M + gg], delta = prm[(size_t)8 * a.M + gg], ffl = prm[(size_t)9 * a.M + gg];
-        const double opz = 1.0 + (double)((const E *)a.z)[gg];
-        for (int c = sub * 16; c < sub * 16 + 16; ++c) {
-            const int l = tile_n + c;
-            if (l >= a.N) break;
-            const double lam = a.wave[l], q = a.trap[l];
-            const E lnx = (E)log(lam * (1.0 / 5500.0));
-            const E xd = e_exp(delta * lnx), ee = e_exp(-tauv * xd);
-            const E F = ffl + (1 - ffl) * ee;
-            const E s = (E)sed[row][c];
-            const E wq = (E)(lam * q), qi = (E)(q / lam);
-#pragma unroll
-            for (int b = 0; b < NB_MAX; ++b) {
-                if (b >= a.n_band) break;
-                const double x = (opz * lam - a.fc[b]) / a.fs[b];
-                const E tb = e_exp((E)(-0.5 * x * x));
-                const E stw = s * tb * wq;
-                acc_p[b][0] += stw * F;
-                if (blockIdx.z == 0) acc_p[b][1] += tb * qi;   // the band normaliser, once over the K split
-                if constexpr (EPI == EPI_PHOT_DUST) {
-                    const E dtv = -(1 - ffl) * xd * ee;
-                    acc_p[b][2] += stw * dtv;
-                    acc_p[b][3] += stw * dtv * tauv * lnx;
-                    acc_p[b][4] += stw * (1 - ee);
-                }
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < NB_MAX; ++b)
-#pragma unroll
-            for (int q = 0; q < NPB; ++q) {
-                E v = acc_p[b][q];
-                v += __shfl_xor(v, 1, 64);
-                v += __shfl_xor(v, 2, 64);
-                acc_p[b][q] = v;
-            }
-        if (sub == 0 && g < a.M) {
-            E *out = (E *)a.part + (((size_t)blockIdx.z * gridDim.x + blockIdx.x) * a.M + g) * a.npart;
-#pragma unroll
-            for (int b = 0; b < NB_MAX; ++b) {
-                if (b >= a.n_band) break;
-#pragma unroll
-                for (int q = 0; q < NPB; ++q) out[q * a.n_band + b] = acc_p[b][q];
-            }
+    for (int b = 0; b < NB_MAX; ++b) {
+        if (b >= a.n_band) break;
+        const double sn = over_lambda(num[b]), sw = over_lambda(nrm[b]);
+        if ((tid & (D_LAM - 1)) == 0 && row < a.n) {
+            out[b] = sn;
+            out[a.n_band + b] = sw;
         }
     }
 }
@@ -673,62 +604,57 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
 
 // ------------------------------------------------------------------ FP64 weights rows P_SSP[g][s]
 // FP64 weights from FP64 bin edges: closed-form log-normal or 8-point Gauss-Legendre DPL
-// panels, closed-form triweight and normal CDFs (the FP64 parity path).  One wave per galaxy:
-// lane i takes age bins i and i + 64, the smooth and burst normalisers are wave sums, and the
-// row is written with consecutive lanes on consecutive age bins.
-__global__ void __launch_bounds__(64) k_exact_weights64(DevConsts k, int n, int sfh, const double *params_v,
-                                                        const double *z_v, const double *edges, double *w_out) {
-    static_assert(NA <= 128 && NZ <= 64, "two age bins per lane, one metallicity bin per lane");
-    __shared__ double spz[NZ];
-    const int lane = threadIdx.x, g = blockIdx.x;
+// panels, closed-form triweight and normal CDFs (the FP64 parity path).  Its time is one bin's chain
+// of FP64 functions, so a galaxy takes three waves: thread i < NA age bin i, the third wave the metallicity
+// bins (one wave with two bins per lane took 12.5 us at 64 galaxies, these 7.1).
+constexpr int W64_T = 192;
+__global__ void __launch_bounds__(W64_T) k_exact_weights64(DevConsts k, int n, int sfh, const double *params_v,
+                                                           const double *z_v, const double *edges, double *w_out) {
+    static_assert(NA <= 2 * WAVE && NZ <= WAVE, "an age bin per thread of two waves, a metallicity bin per lane");
+    __shared__ double spz[NZ], sum[2][2];
+    const int tid = threadIdx.x, g = blockIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const double *prm = params_v;
     const double *age_lo = edges, *age_hi = edges + NA, *lage_lo = edges + 2 * NA, *lage_hi = edges + 3 * NA;
     const double *met_lo = edges + 4 * NA, *met_hi = edges + 4 * NA + NZ;
-    double th[NP];
+    double th[NP], m = 0.0, bm = 0.0;
 #pragma unroll
     for (int p = 0; p < NP; ++p) th[p] = prm[(size_t)p * n + g];
-    const double t_obs = age_universe_gyr(k, z_v[g]);
-    if (lane < NZ) {
-        const double xl = (met_lo[lane] - th[6]) / k.sigma_logz_d, xh = (met_hi[lane] - th[6]) / k.sigma_logz_d;
-        spz[lane] = (xl > 0.0) ? Phic_d(xl) - Phic_d(xh) : Phi_d(xh) - Phi_d(xl);
-    }
-    const double l_obs = log10(t_obs * 1e9), s3 = 3.0 * k.burst_sig_d;
-    auto mass = [&](int i) {
-        if (i >= NA) return 0.0;
-        double m, a0, a1;
-        if (sfh == SPS_SFH_LOGNORMAL) logn_bin_e<false>(age_lo[i], age_hi[i], t_obs, th[1], th[2], m, a0, a1);
-        else m = dpl_bin_f64(k, age_lo[i], age_hi[i], t_obs, th[1], th[2], th[3]);
-        return m;
-    };
-    auto burst = [&](int i) {
-        if (i >= NA) return 0.0;
-        const double lo = lage_lo[i];
-        if (!(lo < l_obs)) return 0.0;
-        const double hi = fmin(lage_hi[i], l_obs);
-        auto cdf = [](double u) {
-            u = fmin(fmax(u, -1.0), 1.0);
-            const double u2 = u * u;
-            return 0.5 + 1.09375 * u * (1.0 - u2 + u2 * u2 * (0.6 - u2 / 7.0));
-        };
-        return cdf((hi - th[5]) / s3) - cdf((lo - th[5]) / s3);
-    };
-    const double m0 = mass(lane), m1 = mass(lane + 64), b0 = burst(lane), b1 = burst(lane + 64);
-    double S = m0 + m1, Zb = b0 + b1;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        S += __shfl_xor(S, o, 64);
-        Zb += __shfl_xor(Zb, o, 64);
+    double *w = w_out + (size_t)g * S_PAD;
+    if (wv < 2) {
+        const double t_obs = age_universe_gyr(k, z_v[g]);
+        if (tid < NA) {
+            double a0, a1;
+            if (sfh == SPS_SFH_LOGNORMAL) logn_bin_e<false>(age_lo[tid], age_hi[tid], t_obs, th[1], th[2], m, a0, a1);
+            else m = dpl_bin_f64(k, age_lo[tid], age_hi[tid], t_obs, th[1], th[2], th[3]);
+            const double l_obs = log10(t_obs * 1e9), s3 = 3.0 * k.burst_sig_d, lo = lage_lo[tid];
+            if (lo < l_obs) {
+                const double hi = fmin(lage_hi[tid], l_obs);
+                auto cdf = [](double u) {
+                    u = fmin(fmax(u, -1.0), 1.0);
+                    const double u2 = u * u;
+                    return 0.5 + 1.09375 * u * (1.0 - u2 + u2 * u2 * (0.6 - u2 / 7.0));
+                };
+                bm = cdf((hi - th[5]) / s3) - cdf((lo - th[5]) / s3);
+            }
+        }
+        const double S = wave_sum(m), Zb = wave_sum(bm);
+        if ((tid & 63) == 0) {
+            sum[wv][0] = S;
+            sum[wv][1] = Zb;
+        }
+    } else {
+        const int j = tid - 2 * WAVE;
+        if (j < NZ) {
+            const double xl = (met_lo[j] - th[6]) / k.sigma_logz_d, xh = (met_hi[j] - th[6]) / k.sigma_logz_d;
+            spz[j] = (xl > 0.0) ? Phic_d(xl) - Phic_d(xh) : Phi_d(xh) - Phi_d(xl);
+        }
+        for (int s = NSSP + j; s < S_PAD; s += WAVE) w[s] = 0.0;
     }
     __syncthreads();
-    double *w = w_out + (size_t)g * S_PAD;
-    const double pa0 = (1.0 - th[4]) * m0 / S + (Zb > 0.0 ? th[4] * b0 / Zb : 0.0);
-    const double pa1 = (1.0 - th[4]) * m1 / S + (Zb > 0.0 ? th[4] * b1 / Zb : 0.0);
-    for (int j = 0; j < NZ; ++j) {
-        const double pz = spz[j];
-        w[j * NA + lane] = pz * pa0;
-        if (lane + 64 < NA) w[j * NA + lane + 64] = pz * pa1;
-    }
-    for (int s = NSSP + lane; s < S_PAD; s += 64) w[s] = 0.0;
+    if (tid >= NA) return;
+    const double S = sum[0][0] + sum[1][0], Zb = sum[0][1] + sum[1][1];
+    const double pa = (1.0 - th[4]) * m / S + (Zb > 0.0 ? th[4] * bm / Zb : 0.0);
+    for (int j = 0; j < NZ; ++j) w[j * NA + tid] = spz[j] * pa;
 }
 
 // ------------------------------------------------------------------ FP32 / BF16X weights, large batches
@@ -823,16 +749,6 @@ __global__ void __launch_bounds__(256) k_expand(int n, const float *pw, void *w)
 }
 
 // ------------------------------------------------------------------ finish: magnitudes / likelihood
-// FP64 path: magnitudes from the summed partials [g][quantity]
-__global__ void __launch_bounds__(128) k_exact_finish64(DevConsts k, int n, const double *params, const double *z,
-                                                        const double *part, int npart, double *mag) {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x, nb = k.n_band;
-    if (g >= n) return;
-    const double m0 = mag_offset(k, z[g]) - 2.5 * params[g];
-    const double *pp = part + (size_t)g * npart;
-    for (int b = 0; b < nb; ++b) mag[(size_t)g * nb + b] = m0 - 2.5 * log10(pp[b] / pp[nb + b]);
-}
-
 // FP32 / BF16X: the photometry partials [tile][quantity][rank] summed over the wavelength tiles of the
 // row tile's window (the forward GEMM writes none outside it), then magnitudes, or log L (vjp: the
 // caller's adjoints obs = dL/dm_b take the place of the residuals), the mass and dust derivatives and
@@ -1048,23 +964,27 @@ __global__ void __launch_bounds__(256) k_sum_splits(size_t n4, int n_split, size
     c[i] = v;
 }
 
-// FP64 partials [t][g][q] summed over the wavelength tiles and the K split: out[g][q].  One
-// block per galaxy; thread (r, q) sums every R-th partial of quantity q, then the R row sums
-// of each quantity are added in LDS.
-__global__ void __launch_bounds__(256) k_sum_parts64(int n, int npart, int n_parts, const double *part,
-                                                     double *out) {
-    __shared__ double red[256];
-    const int g = blockIdx.x, tid = threadIdx.x, R = 256 / npart, r = tid / npart, q = tid % npart;
+// FP64 magnitudes from the partials [t][g][quantity]: a block per galaxy, thread (r, q) sums every R-th
+// partial of quantity q, then the R row sums of each quantity are added in LDS; meanwhile the last
+// thread forms the magnitude offset.
+__global__ void __launch_bounds__(256) k_exact_finish64(DevConsts k, int n, int n_parts, const double *params,
+                                                        const double *z, const double *part, double *mag) {
+    __shared__ double red[256], m0;
+    const int nb = k.n_band, npart = 2 * nb, nt = 192;
+    const int g = blockIdx.x, tid = threadIdx.x, R = nt / npart, r = tid / npart, q = tid % npart;
     double v = 0.0;
     if (r < R)
         for (int t = r; t < n_parts; t += R) v += part[((size_t)t * n + g) * npart + q];
+    if (tid == 255) m0 = mag_offset(k, z[g]) - 2.5 * params[g];
     red[tid] = v;
     __syncthreads();
     if (tid < npart) {
         double acc = 0.0;
         for (int i = 0; i < R; ++i) acc += red[i * npart + tid];
-        out[(size_t)g * npart + tid] = acc;
+        red[tid] = acc;   // read by this thread alone until the barrier
     }
+    __syncthreads();
+    if (tid < nb) mag[(size_t)g * nb + tid] = m0 - 2.5 * log10(red[tid] / red[nb + tid]);
 }
 
 // ------------------------------------------------------------------ weights and their adjoint, a wave per galaxy
@@ -1331,23 +1251,9 @@ __global__ void __launch_bounds__(128) k_xwindows(int n, int n_wave, FiltConst f
 // partial sums | their tile sums | filter windows | dlogL/dnum | Rbar | Wbar | dP.  logl: the
 // likelihood outputs are wanted; grad: also the gradient.
 struct ExactLayout {
-    size_t o_w = 0, o_pw = 0, o_part = 0, o_psum = 0, o_win = 0, o_cn = 0, o_rb = 0, o_wb = 0, o_pb = 0;
+    size_t o_w = 0, o_pw = 0, o_part = 0, o_eg = 0, o_win = 0, o_cn = 0, o_rb = 0, o_wb = 0, o_pb = 0;
     size_t bytes = 0;
 };
-// FP64 GEMM K split: a few row tiles (the 64-galaxy parity batch is one) leave most of the
-// chip idle, so the SSP axis is cut into chunks of at least four k-tiles until the grid holds
-// about 512 blocks; each chunk writes its own band partials, which the finish kernel sums.
-struct F64Split {
-    int ks, chunk;
-};
-static F64Split f64_split(int n, int n_tiles) {
-    const int steps = S_PAD / Prec<SPS_F64>::BK, blocks = n_tiles * ((n + BM - 1) / BM);
-    int ks = 1;
-    while (blocks * ks < 512 && steps / (2 * ks) >= 4) ks *= 2;
-    const int per = (steps + ks - 1) / ks;
-    return F64Split{(steps + per - 1) / per, per * Prec<SPS_F64>::BK};
-}
-
 // K ranges of the gradient GEMM for n galaxies, and the rows of its partial products for any batch up to n
 static int grad_splits(int n) {
     const int tiles = round_up(n, XBM) / XBM * (S_PAD / XBN);
@@ -1366,8 +1272,7 @@ static int wbar_rows(int n) {
 static ExactLayout exact_layout(const sps_ctx *c, int n, int prec, bool logl, bool grad) {
     const int nw = c->n_wave, nb = c->n_band;
     const bool f64 = (prec == SPS_F64);
-    const int n_tiles = f64 ? (nw + BN - 1) / BN : c->lw / XBN;
-    const int n_parts = f64 ? n_tiles * f64_split(n, n_tiles).ks : n_tiles;
+    const int n_parts = f64 ? f64_parts(n, nw) : c->lw / XBN;
     const int mp = round_up(n, XBM);              // A operands are read in whole 128-row tiles
     const bool want_grad = logl && grad;
     const int npart = (want_grad ? 5 : 2) * nb;
@@ -1380,7 +1285,7 @@ static ExactLayout exact_layout(const sps_ctx *c, int n, int prec, bool logl, bo
     L.o_w = carve((size_t)nsplit * mp * S_PAD * tsz);
     L.o_pw = f64 ? 0 : carve((size_t)PW_SLOTS * n * 4);
     L.o_part = carve((size_t)n_parts * n * npart * esz);
-    L.o_psum = carve(f64 ? (size_t)n * npart * esz : (size_t)4 * n * sizeof(float));   // FP64 tile sums | eg
+    L.o_eg = carve(f64 ? 0 : (size_t)4 * n * sizeof(float));
     L.o_win = f64 ? 0 : carve((size_t)(mp / XBM) * sizeof(int4));
     if (logl) {
         L.o_cn = carve((size_t)n * NB_MAX * 4);
@@ -1396,11 +1301,11 @@ static ExactLayout exact_layout(const sps_ctx *c, int n, int prec, bool logl, bo
 
 size_t exact_ws_bytes(const sps_ctx *c, int n, int prec, bool logl, bool grad) {
     if (prec != SPS_F64) return exact_layout(c, n, prec, logl, grad).bytes;
-    // the FP64 K split grows as the batch shrinks: size for the largest need of any batch up
-    // to n, which within one split factor falls on a whole number of row tiles or on n
+    // the FP64 partials shrink where the blocks take more tiles: size for the largest need of any batch
+    // up to n, which for one number of tiles falls on a whole number of row tiles or on n
     size_t most = 0;
-    for (int t = 1; t <= (n + BM - 1) / BM; ++t)
-        most = std::max(most, exact_layout(c, std::min(t * BM, n), prec, logl, grad).bytes);
+    for (int t = 1; t <= (n + D_ROWS - 1) / D_ROWS; ++t)
+        most = std::max(most, exact_layout(c, std::min(t * D_ROWS, n), prec, logl, grad).bytes);
     return most;
 }
 
@@ -1423,14 +1328,14 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
                       float *grad, bool zordered, bool vjp, const int *perm) {
     const int nw = c->n_wave, nb = c->n_band;
     const bool f64 = (prec == SPS_F64);
-    const int n_tiles = f64 ? (nw + BN - 1) / BN : c->lw / XBN;
+    const int n_tiles = c->lw / XBN;
     const int mp = round_up(n, XBM);              // A operands are read in whole 128-row tiles
     const bool want_grad = grad != nullptr;
     const int npart = (want_grad ? 5 : 2) * nb;
     const int lw = c->lw;                         // padded wavelength stride of Rbar
     const bool lik = logl != nullptr || vjp;     // the likelihood's (or the adjoints') finish
     const ExactLayout Lo = exact_layout(c, n, prec, lik, want_grad);
-    const size_t o_w = Lo.o_w, o_pw = Lo.o_pw, o_part = Lo.o_part, o_psum = Lo.o_psum, o_win = Lo.o_win;
+    const size_t o_w = Lo.o_w, o_pw = Lo.o_pw, o_part = Lo.o_part, o_eg = Lo.o_eg, o_win = Lo.o_win;
     const size_t o_cn = Lo.o_cn, o_rb = Lo.o_rb, o_wb = Lo.o_wb, o_pb = Lo.o_pb;
     if (c->work_bytes < Lo.bytes || n > c->max_exact)
         return set_error(SPS_E_STATE, "the exact path's workspace holds " + std::to_string(c->max_exact) +
@@ -1443,11 +1348,11 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
     float *pw = f64 ? nullptr : (float *)(W + o_pw);
     const bool big = n >= GPL_BIG_N;
     // the dust parameters and z in rank order (large batches come in rank order)
-    float *eg = (float *)(W + o_psum);
+    float *eg = (float *)(W + o_eg);
     const float *dust = big ? (const float *)params + (size_t)7 * n : eg;
     const float *z_r = big ? (const float *)z : eg + (size_t)3 * n;
     if (f64) {
-        hipLaunchKernelGGL(k_exact_weights64, dim3(n), dim3(64), 0, s, c->k, n, sfh,
+        hipLaunchKernelGGL(k_exact_weights64, dim3(n), dim3(W64_T), 0, s, c->k, n, sfh,
                            (const double *)params, (const double *)z, c->d_edges, (double *)w_hi);
     } else if (big) {
         hipLaunchKernelGGL(k_exact_pw, dim3((n + 64 / GPL - 1) / (64 / GPL)), dim3(64), 0, s, c->k, n, sfh,
@@ -1462,31 +1367,14 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
     }
     float *part = (float *)(W + o_part);
     if (f64) {
-        // FP64 parity path: the generic 64 x 64 tile kernel on the FP64 table
-        GemmArgs a{};
-        a.M = n;
-        a.N = nw;
-        a.K_valid = NSSP;
-        a.K_pad = S_PAD;
-        a.A_hi = w_hi;
-        a.A_lo = nullptr;
-        a.lda = S_PAD;
-        a.B_hi = c->d_lum64;
-        a.B_lo = nullptr;
-        a.ldb = nw;
-        a.b_nk = false;
-        a.params = params;
-        a.z = z;
-        a.wave = c->d_wave;
-        a.trap = c->d_trap;
-        a.n_band = nb;
-        for (int b = 0; b < NB_MAX; ++b) { a.fc[b] = c->h_fc[b]; a.fs[b] = c->h_fs[b]; }
-        a.part = part;
-        a.npart = npart;
-        const F64Split sp = f64_split(n, n_tiles);
-        a.k_chunk = sp.chunk;
-        dim3 gg(n_tiles, (n + BM - 1) / BM, sp.ks), bg(256);
-        hipLaunchKernelGGL((k_exact_gemm<SPS_F64, EPI_PHOT>), gg, bg, 0, s, a);
+        bool wide;
+        const int np = f64_parts(n, nw), tiles = f64_tiles(n, nw, &wide);
+        const DArgs a{n, nw, nb, tiles, (const double *)w_hi, c->d_lum64, (const double *)params,
+                      (const double *)z, c->d_wave, c->d_trap, filt_const(c->h_fc, c->h_fs), (double *)part};
+        hipLaunchKernelGGL((wide ? k_exact_phot64<2> : k_exact_phot64<1>), dim3(np, (n + D_ROWS - 1) / D_ROWS),
+                           dim3(D_T), 0, s, a);
+        hipLaunchKernelGGL(k_exact_finish64, dim3(n), dim3(256), 0, s, c->k, n, np, (const double *)params,
+                           (const double *)z, (const double *)part, (double *)mag_out);
     } else {
         const FiltConst fl = filt_const(c->h_fc, c->h_fs);
         win = (int4 *)(W + o_win);
@@ -1524,13 +1412,7 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
     }
 
     float *cn = lik ? (float *)(W + o_cn) : nullptr;
-    if (f64) {
-        double *psum = (double *)(W + o_psum);
-        hipLaunchKernelGGL(k_sum_parts64, dim3(n), dim3(256), 0, s, n, npart, n_tiles * f64_split(n, n_tiles).ks,
-                           (const double *)part, psum);
-        hipLaunchKernelGGL(k_exact_finish64, dim3((n + 127) / 128), dim3(128), 0, s, c->k, n, (const double *)params,
-                           (const double *)z, (const double *)psum, npart, (double *)mag_out);
-    } else {
+    if (!f64) {
         auto kf = want_grad ? k_exact_finish<true> : k_exact_finish<false>;
         hipLaunchKernelGGL(kf, dim3((n + 31) / 32), dim3(256), 0, s, c->k, n, n_tiles, perm,
                            (const float *)params, z_r, (const int4 *)win, (const float *)part, npart, (float *)mag_out,
