@@ -190,6 +190,16 @@ int sps_loglike_grad(sps_ctx *ctx, void *stream, int n_gal, int sfh, int path, i
 int sps_phot_vjp(sps_ctx *ctx, void *stream, int n_gal, int sfh, int path, int prec,
                  const float *params, const float *z, const float *gbar, float *grad_out);
 
+/* The exact magnitudes and their vector-Jacobian product as one forward and backward pass (SPS_F32 or
+ * SPS_BF16X): sps_phot_exact_sums also stores the band sums [n_gal][5][n_band] FP32 (numerator,
+ * normaliser, the numerator's derivatives by tau_V, delta and F_floor) in the caller's array, and
+ * sps_phot_vjp_sums starts from them instead of repeating the forward contraction.  Same inputs for
+ * both calls; results, limits and errors as sps_phot_exact and sps_phot_vjp. */
+int sps_phot_exact_sums(sps_ctx *ctx, void *stream, int n_gal, int sfh, int prec, const float *params,
+                        const float *z, float *mag_out, float *band_sums);
+int sps_phot_vjp_sums(sps_ctx *ctx, void *stream, int n_gal, int sfh, int prec, const float *params,
+                      const float *z, const float *gbar, const float *band_sums, float *grad_out);
+
 /* Log posterior on the unbounded parameters x (App. C): theta_p = F_B(x_p) with
  * bounds[p] = (y_lo, y_hi, k, x0), plus the skew-normal log prior with
  * prior[p] = (xi, omega, s) on x_p; value logp_out [n_gal] and gradient

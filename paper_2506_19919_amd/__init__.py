@@ -31,7 +31,7 @@ ABI_FUNCTIONS = ("sps_create", "sps_reserve", "sps_reserve_exact", "sps_status",
                  "sps_phot_exact", "sps_loglike_grad", "sps_logpost_grad", "sps_hmc_run", "sps_hmc_state_bytes",
                  "sps_set_kernel_timing", "sps_kernel_times", "sps_nuts_run", "sps_reserve_nuts",
                  "sps_loglike_grad_static", "sps_get_launch", "sps_set_launch", "sps_autotune_exact",
-                 "sps_autotune_hmc", "sps_phot_vjp")
+                 "sps_autotune_hmc", "sps_phot_vjp", "sps_phot_exact_sums", "sps_phot_vjp_sums")
 
 
 class SpsError(RuntimeError):
@@ -98,6 +98,8 @@ def _load():
     lib.sps_weights.argtypes = [vp, vp, i, i, vp, vp, vp]
     lib.sps_phot_approx.argtypes = [vp, vp, i, i, vp, vp, vp]
     lib.sps_phot_exact.argtypes = [vp, vp, i, i, i, vp, vp, vp]
+    lib.sps_phot_exact_sums.argtypes = [vp, vp, i, i, i, vp, vp, vp, vp]
+    lib.sps_phot_vjp_sums.argtypes = [vp, vp, i, i, i, vp, vp, vp, vp, vp]
     lib.sps_loglike_grad.argtypes = [vp, vp, i, i, i, i, vp, vp, vp, vp, vp, vp, vp]
     lib.sps_logpost_grad.argtypes = [vp, vp, i, i, vp, vp, vp, vp, vp, vp, vp, vp, vp]
     lib.sps_hmc_run.argtypes = [vp, vp, C.POINTER(_HmcCfg), i, i, vp, vp, vp, vp, vp, vp, vp, vp,
@@ -335,6 +337,25 @@ class Context:
                                  _ptr(grad_out)))
         return grad_out
 
+    def _phot_exact_sums(self, sfh, params, z, prec):
+        """Exact magnitudes and the band sums their backward starts from ([n_gal][5][n_band])."""
+        n = self._gal(params, z)
+        mag = torch.empty((n, self.n_band), dtype=torch.float32, device=self.device)
+        sums = torch.empty((n, 5, self.n_band), dtype=torch.float32, device=self.device)
+        _check(_lib.sps_phot_exact_sums(self.h, _stream(None), n, sfh, prec, _ptr(params), _ptr(z), _ptr(mag),
+                                        _ptr(sums)))
+        return mag, sums
+
+    def _phot_vjp_sums(self, sfh, params, z, gbar, sums, prec):
+        """phot_vjp on the exact path from the forward's band sums."""
+        n = self._gal(params, z)
+        _dev(gbar, torch.float32, (n, self.n_band), "gbar", self.device)
+        _dev(sums, torch.float32, (n, 5, self.n_band), "band_sums", self.device)
+        grad = torch.empty((NPARAM, n), dtype=torch.float32, device=self.device)
+        _check(_lib.sps_phot_vjp_sums(self.h, _stream(None), n, sfh, prec, _ptr(params), _ptr(z), _ptr(gbar),
+                                      _ptr(sums), _ptr(grad)))
+        return grad
+
     def loglike_grad_static(self, sfh, params, z, obs, sigma, mask, grad=True, logl_out=None, grad_out=None,
                             stream=None):
         """loglike_grad on the approximate path through the entry point that allocates nothing
@@ -488,17 +509,25 @@ class PhotExact(torch.autograd.Function):
     vector-Jacobian product (the adjoint GEMM) of the band adjoints."""
 
     @staticmethod
-    def forward(ctx, params, z, sps_ctx, sfh, prec):
+    def forward(ctx, params, z, sps_ctx, sfh, prec, keep=False):
         p = params.detach().contiguous()
+        ctx.sps, ctx.sfh, ctx.prec, ctx.keep = sps_ctx, sfh, prec, keep
+        if keep:   # the band sums spare the backward the forward contraction: 5 n_band floats per galaxy
+            mag, sums = sps_ctx._phot_exact_sums(sfh, p, z, prec)
+            ctx.save_for_backward(p, z, sums)
+            return mag
         ctx.save_for_backward(p, z)
-        ctx.sps, ctx.sfh, ctx.prec = sps_ctx, sfh, prec
         return sps_ctx.phot_exact(sfh, p, z, prec=prec)
 
     @staticmethod
     def backward(ctx, gbar):
-        p, z = ctx.saved_tensors
-        g = ctx.sps.phot_vjp(ctx.sfh, p, z, gbar.contiguous().float(), path=SPS_PATH_EXACT, prec=ctx.prec)
-        return g, None, None, None, None
+        p, z, *sums = ctx.saved_tensors
+        gbar = gbar.contiguous().float()
+        if ctx.keep:
+            g = ctx.sps._phot_vjp_sums(ctx.sfh, p, z, gbar, sums[0], ctx.prec)
+        else:
+            g = ctx.sps.phot_vjp(ctx.sfh, p, z, gbar, path=SPS_PATH_EXACT, prec=ctx.prec)
+        return g, None, None, None, None, None
 
 
 def phot_approx(sps_ctx, params, z, sfh=SPS_SFH_DPL):
@@ -506,4 +535,5 @@ def phot_approx(sps_ctx, params, z, sfh=SPS_SFH_DPL):
 
 
 def phot_exact(sps_ctx, params, z, sfh=SPS_SFH_DPL, prec=SPS_F32):
-    return PhotExact.apply(params, z, sps_ctx, sfh, prec)
+    keep = prec != SPS_F64 and torch.is_grad_enabled() and params.requires_grad
+    return PhotExact.apply(params, z, sps_ctx, sfh, prec, keep)

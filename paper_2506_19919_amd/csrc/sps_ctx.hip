@@ -676,6 +676,20 @@ int sps_phot_exact(sps_ctx *c, void *stream, int n_gal, int sfh, int prec, const
                         nullptr, nullptr);
 }
 
+int sps_phot_exact_sums(sps_ctx *c, void *stream, int n_gal, int sfh, int prec, const float *params, const float *z,
+                        float *mag_out, float *band_sums) {
+    int rc = enter(c);
+    if (rc) return rc;
+    if ((rc = check_gal(c, n_gal, sfh))) return rc;
+    if (prec != SPS_F32 && prec != SPS_BF16X)
+        return set_error(SPS_E_INVAL, "band sums are kept in SPS_F32 or SPS_BF16X");
+    if (!(c->prec_mask & (1u << prec))) return set_error(SPS_E_STATE, "this precision's SSP table was not uploaded");
+    if (n_gal == 0) return SPS_OK;
+    if (!params || !z || !mag_out || !band_sums) return set_error(SPS_E_INVAL, "null array");
+    return launch_exact(c, (hipStream_t)stream, n_gal, sfh, prec, params, z, mag_out, nullptr, nullptr, nullptr,
+                        nullptr, nullptr, false, false, band_sums);
+}
+
 int sps_loglike_grad(sps_ctx *c, void *stream, int n_gal, int sfh, int path, int prec, const float *params,
                      const float *z, const float *obs, const float *sigma, const uint8_t *band_mask,
                      float *logl_out, float *grad_out) {
@@ -716,6 +730,20 @@ int sps_phot_vjp(sps_ctx *c, void *stream, int n_gal, int sfh, int path, int pre
     if (!(c->prec_mask & (1u << prec))) return set_error(SPS_E_STATE, "this precision's SSP table was not uploaded");
     return launch_exact(c, (hipStream_t)stream, n_gal, sfh, prec, params, z, nullptr, gbar, nullptr, nullptr,
                         nullptr, grad_out, false, true);
+}
+
+int sps_phot_vjp_sums(sps_ctx *c, void *stream, int n_gal, int sfh, int prec, const float *params, const float *z,
+                      const float *gbar, const float *band_sums, float *grad_out) {
+    int rc = enter(c);
+    if (rc) return rc;
+    if ((rc = check_gal(c, n_gal, sfh))) return rc;
+    if (prec != SPS_F32 && prec != SPS_BF16X)
+        return set_error(SPS_E_INVAL, "exact-path vector-Jacobian products run in SPS_F32 or SPS_BF16X");
+    if (!(c->prec_mask & (1u << prec))) return set_error(SPS_E_STATE, "this precision's SSP table was not uploaded");
+    if (n_gal == 0) return SPS_OK;
+    if (!params || !z || !gbar || !band_sums || !grad_out) return set_error(SPS_E_INVAL, "null array");
+    return launch_exact(c, (hipStream_t)stream, n_gal, sfh, prec, params, z, nullptr, gbar, nullptr, nullptr,
+                        nullptr, grad_out, false, true, const_cast<float *>(band_sums));   // read only with vjp
 }
 
 int sps_logpost_grad(sps_ctx *c, void *stream, int n_gal, int sfh, const float *x, const float *z,

@@ -8,7 +8,7 @@
 // The GEMM runs on MFMA (FP64 16x16x4, or BF16 16x16x32 accumulated in FP32: SPS_F32 splits
 // both operands into three BF16 parts, which hold all 24 bits, and takes six products;
 // SPS_BF16X into two, W = W_hi + W_lo, L = L_hi + L_lo, and takes three).  The attenuation, filter and quadrature weights are
-// generated in the epilogue and reduced over each wavelength tile (64 wide on the
+// generated in the epilogue and reduced over each wavelength tile (16 wide on the
 // FP64 path, 128 on the FP32 / BF16X paths) into per-tile partial sums; small
 // kernels finish the sums per galaxy.  The FP32 / BF16X paths skip the wavelength
 // tiles outside every band's 8-sigma support for a 128-galaxy row tile.
@@ -753,14 +753,17 @@ __global__ void __launch_bounds__(256) k_expand(int n, const float *pw, void *w)
 // row tile's window (the forward GEMM writes none outside it), then magnitudes, or log L (vjp: the
 // caller's adjoints obs = dL/dm_b take the place of the residuals), the mass and dust derivatives and
 // dlogL/dnum.  Eight lanes per galaxy, a band each; perm: the caller's index of a rank (null: the same).
-// A block's 32 galaxies share a row tile.  One thread per galaxy and a pass of its own for the tile sums
-// took 28 + 9 us at 4096 galaxies.
+// sums, with mag: the tile sums [g][5][n_band] of the numerator, the normaliser and the numerator's dust
+// derivatives are kept for a later backward, which passes them with vjp in place of the partials; sperm:
+// the caller's index of a rank for them.  A block's 32 galaxies share a row tile.  One thread per galaxy
+// and a pass of its own for the tile sums took 28 + 9 us at 4096 galaxies.
 template <bool GRAD>
 __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_tiles, const int *perm,
                                                       const float *params, const float *z, const int4 *win,
                                                       const float *part, int npart, float *mag, const float *obs,
                                                       const float *sigma, const uint8_t *mask, float *logl,
-                                                      float *grad, float *cnum, int vjp) {
+                                                      float *grad, float *cnum, int vjp, float *sums,
+                                                      const int *sperm) {
     static_assert(NB_MAX == 8, "a lane per band");
     const int r = blockIdx.x * 32 + (threadIdx.x >> 3), b = threadIdx.x & 7, nb = k.n_band;
     const bool valid = r < n, act = b < nb;
@@ -769,13 +772,19 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
     const int4 w = win[blockIdx.x * 32 / XBM];
     constexpr int NQ = GRAD ? 5 : 2;
     float v[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    const float *pp = part + (size_t)bb * n + rr;
-    const size_t qs = (size_t)nb * n, ts = (size_t)npart * n;
-    const int t_end = min(w.y, n_tiles);
-#pragma unroll 4
-    for (int t = w.x; t < t_end; ++t) {
+    const size_t so = (size_t)(sperm ? sperm[rr] : g) * 5 * nb + bb;
+    if (GRAD && vjp && sums) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) v[q] += pp[t * ts + q * qs];
+        for (int q = 0; q < NQ; ++q) v[q] = sums[so + q * nb];
+    } else {
+        const float *pp = part + (size_t)bb * n + rr;
+        const size_t qs = (size_t)nb * n, ts = (size_t)npart * n;
+        const int t_end = min(w.y, n_tiles);
+#pragma unroll 4
+        for (int t = w.x; t < t_end; ++t) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) v[q] += pp[t * ts + q * qs];
+        }
     }
     // the distance integral's nodes split over the eight lanes (mag_offset)
     const double zf = (double)z[rr];
@@ -794,6 +803,9 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
     const double num = v[0], m = m0 - 2.5 * log10(num / (double)v[1]);
     if (mag) {
         if (valid && act) mag[(size_t)g * nb + b] = (float)m;
+        if (GRAD && sums && valid && act)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) sums[so + q * nb] = v[q];
         return;
     }
     const uint32_t mk = (vjp || !mask) ? 0xffffffffu : mask[g];
@@ -1068,7 +1080,7 @@ __device__ inline void wave_params(const float *params, int n, int g, int lane, 
     for (int p = 0; p < NP; ++p) th[p] = lane_value(v, p);
 }
 
-// P_age, P_Z -> pw (slots as above), the weights row -> w, and the epilogue's inputs tau_V, delta,
+// P_age, P_Z -> pw (slots as above), the weights row -> w (unless null), and the epilogue's inputs tau_V, delta,
 // F_floor, z in rank order -> eg [4][n]
 template <int P>
 __global__ void __launch_bounds__(XWG * WAVE) k_exact_weights(DevConsts k, int n, int sfh, const int *perm,
@@ -1091,7 +1103,7 @@ __global__ void __launch_bounds__(XWG * WAVE) k_exact_weights(DevConsts k, int n
         const int row = e / XWG, t = e % XWG;
         if (r0 + t < n) pw[(size_t)(row < NA ? row : PW_PZ + (row - NA)) * n + r0 + t] = sp[t][row];
     }
-    if (r0 + wv >= n) return;
+    if (r0 + wv >= n || !w) return;
     for (int e = lane; e < S_PAD / 2; e += WAVE) expand_pair<P>(sp[wv], 2 * e, (size_t)r, w);
 }
 
@@ -1249,7 +1261,7 @@ __global__ void __launch_bounds__(128) k_xwindows(int n, int n_wave, FiltConst f
 // ------------------------------------------------------------------ launcher
 // Byte offsets of the exact path's workspace for n rows: weights rows | per-galaxy weights |
 // partial sums | their tile sums | filter windows | dlogL/dnum | Rbar | Wbar | dP.  logl: the
-// likelihood outputs are wanted; grad: also the gradient.
+// likelihood outputs are wanted; grad: also the gradient; dust: magnitudes with the dust derivatives' sums.
 struct ExactLayout {
     size_t o_w = 0, o_pw = 0, o_part = 0, o_eg = 0, o_win = 0, o_cn = 0, o_rb = 0, o_wb = 0, o_pb = 0;
     size_t bytes = 0;
@@ -1269,13 +1281,13 @@ static int wbar_rows(int n) {
     }
 }
 
-static ExactLayout exact_layout(const sps_ctx *c, int n, int prec, bool logl, bool grad) {
+static ExactLayout exact_layout(const sps_ctx *c, int n, int prec, bool logl, bool grad, bool dust = false) {
     const int nw = c->n_wave, nb = c->n_band;
     const bool f64 = (prec == SPS_F64);
     const int n_parts = f64 ? f64_parts(n, nw) : c->lw / XBN;
     const int mp = round_up(n, XBM);              // A operands are read in whole 128-row tiles
     const bool want_grad = logl && grad;
-    const int npart = (want_grad ? 5 : 2) * nb;
+    const int npart = (want_grad || dust ? 5 : 2) * nb;
     const int esz = f64 ? 8 : 4;
     const int tsz = f64 ? 8 : 2;   // a GEMM operand's element: FP64, or BF16 parts
     const int nsplit = f64 ? 1 : (prec == SPS_F32 ? 3 : 2);
@@ -1322,19 +1334,21 @@ static void tile_order(const sps_ctx *c, XArgs &a) {
 }
 
 // perm: the caller's index of each rank, or null where the arrays come in rank order (always from
-// GPL_BIG_N galaxies on)
+// GPL_BIG_N galaxies on).  sums: with mag_out, the band sums that a backward starts from, to be kept; with vjp,
+// those of an earlier call on the same inputs, whose forward GEMM is then not repeated; sperm: the caller's
+// indices of the ranks for them.
 static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const void *params, const void *z,
                       void *mag_out, const float *obs, const float *sigma, const uint8_t *mask, float *logl,
-                      float *grad, bool zordered, bool vjp, const int *perm) {
+                      float *grad, bool zordered, bool vjp, const int *perm, float *sums, const int *sperm) {
     const int nw = c->n_wave, nb = c->n_band;
     const bool f64 = (prec == SPS_F64);
     const int n_tiles = c->lw / XBN;
     const int mp = round_up(n, XBM);              // A operands are read in whole 128-row tiles
-    const bool want_grad = grad != nullptr;
-    const int npart = (want_grad ? 5 : 2) * nb;
+    const bool want_grad = grad != nullptr, dust5 = want_grad || sums, given = vjp && sums;
+    const int npart = (dust5 ? 5 : 2) * nb;
     const int lw = c->lw;                         // padded wavelength stride of Rbar
     const bool lik = logl != nullptr || vjp;     // the likelihood's (or the adjoints') finish
-    const ExactLayout Lo = exact_layout(c, n, prec, lik, want_grad);
+    const ExactLayout Lo = exact_layout(c, n, prec, lik, want_grad, dust5);
     const size_t o_w = Lo.o_w, o_pw = Lo.o_pw, o_part = Lo.o_part, o_eg = Lo.o_eg, o_win = Lo.o_win;
     const size_t o_cn = Lo.o_cn, o_rb = Lo.o_rb, o_wb = Lo.o_wb, o_pb = Lo.o_pb;
     if (c->work_bytes < Lo.bytes || n > c->max_exact)
@@ -1358,12 +1372,13 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
         hipLaunchKernelGGL(k_exact_pw, dim3((n + 64 / GPL - 1) / (64 / GPL)), dim3(64), 0, s, c->k, n, sfh,
                            (const float *)params, (const float *)z, pw);
         const dim3 ge((n + XG - 1) / XG), be(256);
-        if (prec == SPS_F32) hipLaunchKernelGGL(k_expand<SPS_F32>, ge, be, 0, s, n, (const float *)pw, w_hi);
+        if (given) {   // no weights rows
+        } else if (prec == SPS_F32) hipLaunchKernelGGL(k_expand<SPS_F32>, ge, be, 0, s, n, (const float *)pw, w_hi);
         else hipLaunchKernelGGL(k_expand<SPS_BF16X>, ge, be, 0, s, n, (const float *)pw, w_hi);
     } else {
         auto kw = prec == SPS_F32 ? k_exact_weights<SPS_F32> : k_exact_weights<SPS_BF16X>;
         hipLaunchKernelGGL(kw, dim3((n + XWG - 1) / XWG), dim3(XWG * WAVE), 0, s, c->k, n, sfh, perm,
-                           (const float *)params, (const float *)z, pw, eg, w_hi);
+                           (const float *)params, (const float *)z, pw, eg, given ? nullptr : w_hi);
     }
     float *part = (float *)(W + o_part);
     if (f64) {
@@ -1403,20 +1418,21 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
         tile_order(c, a);
         const dim3 gx(a.n_mt * a.n_nt), bx(256);
         const bool ring = c->launch.exact_ring != 0;
-        if (prec == SPS_F32 && !want_grad) hipLaunchKernelGGL((k_xgemm<SPS_F32, EPI_PHOT, false>), gx, bx, 0, s, a);
+        if (given) {   // the sums are the caller's
+        } else if (prec == SPS_F32 && !dust5) hipLaunchKernelGGL((k_xgemm<SPS_F32, EPI_PHOT, false>), gx, bx, 0, s, a);
         else if (prec == SPS_F32) hipLaunchKernelGGL((k_xgemm<SPS_F32, EPI_PHOT_DUST, false>), gx, bx, 0, s, a);
-        else if (!want_grad && ring) hipLaunchKernelGGL((k_xgemm<SPS_BF16X, EPI_PHOT, true>), gx, bx, 0, s, a);
-        else if (!want_grad) hipLaunchKernelGGL((k_xgemm<SPS_BF16X, EPI_PHOT, false>), gx, bx, 0, s, a);
+        else if (!dust5 && ring) hipLaunchKernelGGL((k_xgemm<SPS_BF16X, EPI_PHOT, true>), gx, bx, 0, s, a);
+        else if (!dust5) hipLaunchKernelGGL((k_xgemm<SPS_BF16X, EPI_PHOT, false>), gx, bx, 0, s, a);
         else if (ring) hipLaunchKernelGGL((k_xgemm<SPS_BF16X, EPI_PHOT_DUST, true>), gx, bx, 0, s, a);
         else hipLaunchKernelGGL((k_xgemm<SPS_BF16X, EPI_PHOT_DUST, false>), gx, bx, 0, s, a);
     }
 
     float *cn = lik ? (float *)(W + o_cn) : nullptr;
     if (!f64) {
-        auto kf = want_grad ? k_exact_finish<true> : k_exact_finish<false>;
+        auto kf = dust5 ? k_exact_finish<true> : k_exact_finish<false>;
         hipLaunchKernelGGL(kf, dim3((n + 31) / 32), dim3(256), 0, s, c->k, n, n_tiles, perm,
                            (const float *)params, z_r, (const int4 *)win, (const float *)part, npart, (float *)mag_out,
-                           obs, sigma, mask, logl, grad, cn, vjp ? 1 : 0);
+                           obs, sigma, mask, logl, grad, cn, vjp ? 1 : 0, sums, sperm);
     }
     if (want_grad) {
         void *r_hi = W + o_rb;   // Rbar rows: BF16 parts interleaved [mp][3 or 2 lw]
@@ -1603,10 +1619,10 @@ size_t exact_xsort_bytes(const sps_ctx *c, int n) { return n >= XSORT_MIN ? xsor
 
 int launch_exact(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const void *params, const void *z,
                  void *mag_out, const float *obs, const float *sigma, const uint8_t *mask, float *logl,
-                 float *grad, bool ordered, bool vjp) {
+                 float *grad, bool ordered, bool vjp, float *sums) {
     if (prec == SPS_F64 || ordered)
         return exact_core(c, s, n, sfh, prec, params, z, mag_out, obs, sigma, mask, logl, grad,
-                          ordered && prec != SPS_F64, vjp, nullptr);
+                          ordered && prec != SPS_F64, vjp, nullptr, sums, nullptr);
     const DevConsts grid = z_sort_grid(c);
     if (n < XSORT_MIN) {
         const bool rank = n > XBM;
@@ -1615,7 +1631,7 @@ int launch_exact(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const void
             SPS_HIP(hipGetLastError());
         }
         return exact_core(c, s, n, sfh, prec, params, z, mag_out, obs, sigma, mask, logl, grad, rank, vjp,
-                          rank ? c->d_perm : nullptr);
+                          rank ? c->d_perm : nullptr, sums, nullptr);
     }
     const int nb = c->n_band;
     const XsortLayout xl = xsort_layout(c, n);
@@ -1636,7 +1652,7 @@ int launch_exact(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const void
                        (const float *)z, obs, sigma, mask, par_s, z_s, obs_s, sig_s, msk_s);
     rc = exact_core(c, s, n, sfh, prec, par_s, z_s, mag_out ? mag_s : nullptr, obs ? obs_s : nullptr,
                     sigma ? sig_s : nullptr, mask ? msk_s : nullptr, logl ? ll_s : nullptr, grad ? gr_s : nullptr,
-                    true, vjp, nullptr);
+                    true, vjp, nullptr, sums, c->d_perm);
     if (rc) return rc;
     hipLaunchKernelGGL(k_exact_order_out, g1, b1, 0, s, n, nb, (const int *)c->d_perm, mag_s, ll_s, gr_s,
                        (float *)mag_out, logl, grad);

@@ -202,10 +202,11 @@ int launch_approx(sps_ctx *c, hipStream_t s, int n_gal, int sfh, int mode, const
 // ordered: the galaxies already come in z order (the exact-path HMC ranks its chains); else the
 // FP32 / BF16X paths rank them by z internally and return the outputs in the caller's order.
 // vjp: obs holds the magnitudes' adjoints (sigma, mask and logl null) and grad receives their
-// vector-Jacobian product
+// vector-Jacobian product.  sums: the band sums a backward starts from, written with mag_out, read with vjp
 int launch_exact(sps_ctx *c, hipStream_t s, int n_gal, int sfh, int prec, const void *params,
                  const void *z, void *mag_out, const float *obs, const float *sigma,
-                 const uint8_t *mask, float *logl, float *grad, bool ordered = false, bool vjp = false);
+                 const uint8_t *mask, float *logl, float *grad, bool ordered = false, bool vjp = false,
+                 float *sums = nullptr);
 int launch_hmc(sps_ctx *c, hipStream_t s, const sps_hmc_cfg *cfg, int n_gal, int sfh, const float *z,
                const float *obs, const float *sigma, const uint8_t *mask, const float *bounds,
                const float *prior, const float *theta0, float *samples, float *post_mean,
