@@ -659,12 +659,14 @@ __global__ void __launch_bounds__(W64_T) k_exact_weights64(DevConsts k, int n, i
 
 // ------------------------------------------------------------------ FP32 / BF16X weights, large batches
 // From GPL_BIG_N galaxies on, GPL adjacent lanes share a galaxy (and its LDS column) and split its age
-// bins; below, a wave takes each galaxy (k_exact_weights).
+// bins; below, a wave takes each galaxy (k_exact_weights).  Four lanes: the chain of a lane's bins is the
+// time of the weights and of their adjoint, us with two / four lanes: 16,384 galaxies 29 + 38 / 23 + 30,
+// 20,011 32 + 43 / 25 + 33, 65,536 43 + 65 / 43 + 53.
 // Per-galaxy results, SoA [slot][n]: slots 0..93 P_age, 96..107 P_Z, 108/109 the FP64 total
 // smooth mass (low/high words), 110 the burst normaliser, 111 log10 t_obs, 112 the first
 // burst bin (int bits).
 constexpr int PW_SLOTS = 128, PW_PZ = 96, PW_S = 108, PW_ZB = 110, PW_LOBS = 111, PW_I0 = 112;
-constexpr int GPL_BIG_N = 16384, GPL = 2;
+constexpr int GPL_BIG_N = 16384, GPL = 4;
 
 __global__ void __launch_bounds__(64) k_exact_pw(DevConsts k, int n, int sfh, const float *params, const float *z,
                                                  float *pw) {
