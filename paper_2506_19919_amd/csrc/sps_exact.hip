@@ -48,12 +48,14 @@ constexpr float LOG2E_F = 1.4426950408889634f;
 struct FiltConst {
     double fc[NB_MAX], inv_fs[NB_MAX];   // band centres and 1 / widths (FP64, as in the forward epilogue)
     double lo8[NB_MAX], hi8[NB_MAX];     // c - 8 sigma, c + 8 sigma: the support the kernels keep
+    double gk[NB_MAX];                   // sqrt(log2(e) / 2) / sigma
 };
 inline FiltConst filt_const(const double *fc, const double *fs) {
     FiltConst f;
     for (int b = 0; b < NB_MAX; ++b) {
         f.fc[b] = fc[b];
         f.inv_fs[b] = fs[b] > 0.0 ? 1.0 / fs[b] : 0.0;
+        f.gk[b] = f.inv_fs[b] * GAUSS_K2;
         f.lo8[b] = fc[b] - 8.0 * fs[b];
         f.hi8[b] = fc[b] + 8.0 * fs[b];
     }
@@ -841,12 +843,14 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
 // Rbar[g][l] = sum_b (d logL / d num_b) F_att(l) T_b((1+z) l) l q_l  (zero beyond n_wave);
 // bands more than 8 sigma from the redshifted wavelength contribute below FP32 resolution.
 // One block takes G consecutive galaxies (rows of one 128-row tile, so one filter-support
-// window) and walks their rows in chunks of 256 wavelengths: the galaxies' constants are loaded
+// window, all that the gradient GEMM reads) and walks their rows from the window's first k-tile to its
+// last, two wavelengths per thread: the galaxies' constants are loaded
 // together once, and each batch of wavelength constants serves all of the block's galaxies.
-// With a block per galaxy, each block's short life went mostly to waiting on those two loads
-// (a block per chunk had been worse still); G = 4 pays once the batch leaves at least 8192
-// blocks to fill the chip, and below that G = 1 keeps more blocks in flight.
-constexpr int RBAR_G_BIG = 4, RBAR_BIG_MIN_GAL = 32768;
+// G = 4 spares those loads, G = 1 keeps more blocks in flight: us with 1 / 4 galaxies, 6 bands, BF16X, 500
+// x 2000 5.3 / 9.6, 4096 13.5 / 15.8, 20,011 41.7 / 39.2, 65,536 149 / 128.  Bound by instructions (an
+// exponential per band in reach and two for the dust); one wavelength per thread in whole chunks of 256
+// around the window, a 2-byte store per part, took 63 us at 20,011 and 195 at 65,536.
+constexpr int RBAR_G_BIG = 4, RBAR_BIG_MIN_GAL = 16384;
 static_assert(XBM % RBAR_G_BIG == 0, "a block's galaxies share one row tile");
 template <int P, int RBAR_G>
 __global__ void __launch_bounds__(256) k_exact_rbar(int n, int n_wave, int ld, int nb, FiltConst fl,
@@ -854,14 +858,8 @@ __global__ void __launch_bounds__(256) k_exact_rbar(int n, int n_wave, int ld, i
                                                     const float *cnum, const int4 *win, void *rb) {
     const int g0 = blockIdx.x * RBAR_G, tid = threadIdx.x;
     const int ng = min(RBAR_G, n - g0);   // galaxies of this block (>= 1)
-    // the gradient GEMM reads only the k-tiles inside its row tile's filter-support window:
-    // chunks wholly outside it are never read and are not written
-    int c_lo = 0, c_hi = (ld + 255) / 256;
-    if (win) {
-        const int4 w = win[g0 / XBM];
-        c_lo = (w.z * XBK) / 256;
-        c_hi = min(c_hi, (w.w * XBK + 255) / 256);
-    }
+    const int4 wn = win[g0 / XBM];
+    const int lo = wn.z * XBK, hi = min(ld, wn.w * XBK);
     double opz[RBAR_G];
     float cb[RBAR_G][NB_MAX], ffl[RBAR_G], delta2[RBAR_G], tauv2[RBAR_G];
 #pragma unroll
@@ -877,54 +875,46 @@ __global__ void __launch_bounds__(256) k_exact_rbar(int n, int n_wave, int ld, i
     }
     float tc[NB_MAX];   // filter offsets as in the forward epilogue
 #pragma unroll
-    for (int b = 0; b < NB_MAX; ++b) tc[b] = (float)(-fl.fc[b] * fl.inv_fs[b] * GAUSS_K2);
-    // RU chunks per step, their wavelength constants loaded together: each chunk's work is a
-    // few dozen instructions, so a step that waited out its own load before computing left the
-    // block latency-bound.  Bands are tested per element (a wave's 64 wavelengths lie within a
-    // fraction of a filter width of each other, so the test rarely diverges).
-    constexpr int RU = 4;
-    for (int ch0 = c_lo; ch0 < c_hi; ch0 += RU) {
-        v4f w[RU];
+    for (int b = 0; b < NB_MAX; ++b) tc[b] = (float)(-fl.fc[b] * fl.gk[b]);
+    // bands are tested per pair (a wave's 128 wavelengths lie within a filter's reach of each other, so the
+    // test rarely diverges)
+    for (int l = lo + 2 * tid; l < hi; l += 512) {
+        v4f w[2];
 #pragma unroll
-        for (int u = 0; u < RU; ++u) {
-            const int l = (ch0 + u) * 256 + tid, lc = min(l, n_wave - 1);
-            w[u] = *(const v4f *)(wc + 4 * (size_t)lc);   // ln x, l q, q / l, l
-        }
+        for (int e = 0; e < 2; ++e) w[e] = *(const v4f *)(wc + 4 * (size_t)min(l + e, n_wave - 1));   // ln x, l q, q / l, l
 #pragma unroll
         for (int j = 0; j < RBAR_G; ++j) {
             if (j >= ng) break;
             const int g = g0 + j;
-            float ta[NB_MAX];
+            float v[2], sum[2] = {0.0f, 0.0f};
 #pragma unroll
-            for (int b = 0; b < NB_MAX; ++b) ta[b] = (float)(opz[j] * fl.inv_fs[b] * GAUSS_K2);
-#pragma unroll
-            for (int u = 0; u < RU; ++u) {
-                const int l = (ch0 + u) * 256 + tid;
-                if (ch0 + u >= c_hi || l >= ld) break;
-                float v = 0.0f;
-                if (l < n_wave) {
-                    float sum = 0.0f;
-#pragma unroll
-                    for (int b = 0; b < NB_MAX; ++b) {
-                        if (b >= nb) break;
-                        const float t = fmaf(w[u][3], ta[b], tc[b]);
-                        if (fabsf(t) < 8.0f * GAUSS_K2) sum = fmaf(cb[j][b], __builtin_amdgcn_exp2f(-t * t), sum);
-                    }
-                    if (sum != 0.0f) {
-                        const float F = ffl[j] + (1.0f - ffl[j]) * __builtin_amdgcn_exp2f(
-                                                                    tauv2[j] * __builtin_amdgcn_exp2f(delta2[j] * w[u][0]));
-                        v = sum * F * w[u][1];
-                    }
+            for (int b = 0; b < NB_MAX; ++b) {
+                if (b >= nb) break;
+                const float ta = (float)(opz[j] * fl.gk[b]), t0 = fmaf(w[0][3], ta, tc[b]), t1 = fmaf(w[1][3], ta, tc[b]);
+                if (fminf(fabsf(t0), fabsf(t1)) < 8.0f * GAUSS_K2) {
+                    sum[0] = fmaf(cb[j][b], __builtin_amdgcn_exp2f(-t0 * t0), sum[0]);
+                    sum[1] = fmaf(cb[j][b], __builtin_amdgcn_exp2f(-t1 * t1), sum[1]);
                 }
-                if (P == SPS_F32) {
-                    uint16_t *o = (uint16_t *)rb + bf3_at(g, ld, l);
-                    split3(v, o[0], o[32], o[64]);
-                } else {
-                    const uint16_t h = f2bf(v);
-                    const size_t o = bfx_at(g, ld, l);   // interleaved hi / lo rows
-                    ((uint16_t *)rb)[o] = h;
-                    ((uint16_t *)rb)[o + 32] = f2bf(v - bf2f(h));
-                }
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const float F = ffl[j] + (1.0f - ffl[j]) * __builtin_amdgcn_exp2f(
+                                                            tauv2[j] * __builtin_amdgcn_exp2f(delta2[j] * w[e][0]));
+                v[e] = (l + e < n_wave && sum[e] != 0.0f) ? sum[e] * F * w[e][1] : 0.0f;
+            }
+            if (P == SPS_F32) {
+                uint16_t *o = (uint16_t *)rb + bf3_at(g, ld, l);   // l is even
+                uint16_t h[2], m[2], q[2];
+                split3(v[0], h[0], m[0], q[0]);
+                split3(v[1], h[1], m[1], q[1]);
+                *(uint32_t *)o = h[0] | ((uint32_t)h[1] << 16);
+                *(uint32_t *)(o + 32) = m[0] | ((uint32_t)m[1] << 16);
+                *(uint32_t *)(o + 64) = q[0] | ((uint32_t)q[1] << 16);
+            } else {
+                uint16_t *o = (uint16_t *)rb + bfx_at(g, ld, l);   // interleaved hi / lo rows
+                const uint16_t h0 = f2bf(v[0]), h1 = f2bf(v[1]);
+                *(uint32_t *)o = h0 | ((uint32_t)h1 << 16);
+                *(uint32_t *)(o + 32) = f2bf(v[0] - bf2f(h0)) | ((uint32_t)f2bf(v[1] - bf2f(h1)) << 16);
             }
         }
     }
