@@ -922,17 +922,14 @@ __global__ void __launch_bounds__(256) k_exact_rbar(int n, int n_wave, int ld, i
 
 // dP_age and dP_Z from Wbar = dlogL/dP_SSP (stored [s][ld], galaxies contiguous):
 //   dP_age(i) = sum_j P_Z(j) Wbar[j NA + i],  dP_Z(j) = sum_i P_age(i) Wbar[j NA + i]
-// Thread per (galaxy, group of WB_AGES ages): each Wbar element is read once; the group's
-// dP_age are complete, its dP_Z are partial sums written SoA pb[NA + grp NZ + j][n] and added
-// by the weights adjoint.  Written SoA pb[r][n] (r < NA: dP_age).
-// Below GPL_BIG_N galaxies the grid is small: blocks of one wave (four times the blocks to
-// spread over the CUs) and two ages' loads in flight per thread; above it, blocks of 256 with
-// one age at a time were faster.
-constexpr int WB_GROUPS = 4, WB_AGES = (NA + WB_GROUPS - 1) / WB_GROUPS;
-template <int WB_T>
-__global__ void __launch_bounds__(WB_T) k_wbar_reduce(int n, const float *pw, const float *wbar, int ld,
-                                                     float *pb) {
-    const int g = blockIdx.x * WB_T + threadIdx.x, grp = blockIdx.y;
+// over the n_split partial products of the gradient GEMM's K ranges (split elements apart).  Each Wbar
+// element is read once; a group of ages' dP_age are complete, its dP_Z are partial sums written SoA
+// pb[NA + grp NZ + j][n] and added by the weights adjoint.  Written SoA pb[r][n] (r < NA: dP_age).
+// From GPL_BIG_N galaxies on (one partial product) a thread takes a galaxy and a group of 24 ages.
+constexpr int WB_BIG = 4, WB_SMALL = 6;   // groups of ages
+__global__ void __launch_bounds__(256) k_wbar_reduce(int n, const float *pw, const float *wbar, int ld, float *pb) {
+    constexpr int AGES = (NA + WB_BIG - 1) / WB_BIG;
+    const int g = blockIdx.x * 256 + threadIdx.x, grp = blockIdx.y;
     if (g >= n) return;
     float pz[NZ], dz[NZ];
 #pragma unroll
@@ -940,9 +937,9 @@ __global__ void __launch_bounds__(WB_T) k_wbar_reduce(int n, const float *pw, co
         pz[j] = pw[(size_t)(PW_PZ + j) * n + g];
         dz[j] = 0.0f;
     }
-    const int i1 = min(NA, (grp + 1) * WB_AGES);
-#pragma unroll(WB_T == 64 ? 2 : 1)
-    for (int i = grp * WB_AGES; i < i1; ++i) {
+    const int i1 = min(NA, (grp + 1) * AGES);
+#pragma unroll 1
+    for (int i = grp * AGES; i < i1; ++i) {
         float w[NZ];
 #pragma unroll
         for (int j = 0; j < NZ; ++j) w[j] = wbar[(size_t)(j * NA + i) * ld + g];
@@ -959,14 +956,51 @@ __global__ void __launch_bounds__(WB_T) k_wbar_reduce(int n, const float *pw, co
     for (int j = 0; j < NZ; ++j) pb[(size_t)(NA + grp * NZ + j) * n + g] = dz[j];
 }
 
-// sum of the K-range partial products into the first one (float4 per thread)
-__global__ void __launch_bounds__(256) k_sum_splits(size_t n4, int n_split, size_t split4, v4f *c) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n4) return;
-    v4f v = c[i];
-    for (int q = 1; q < n_split; ++q) v += c[q * split4 + i];
-    c[i] = v;
+// Below GPL_BIG_N the chain of loads is the time, so each of a block's waves takes one age of its group
+// for 64 galaxies, two partial products' loads in flight, and the group's dP_Z are summed in LDS.  us at 100 /
+// 1500 / 4096 / 9600 galaxies (8 / 6 / 2 / 1 products): 7.8 / 9.2 / 8.5 / 11.5; a thread per group of 24
+// ages, after a pass of its own for the partial products, 16.2 / 19.1 / 20.9 / 13.0.
+constexpr int WB_AGES = (NA + WB_SMALL - 1) / WB_SMALL, WB_Q = 2;
+__global__ void __launch_bounds__(WB_AGES * WAVE) k_wbar_reduce_wave(int n, const float *pw, const float *wbar, int ld,
+                                                                    int n_split, size_t split, float *pb) {
+    __shared__ float dz[WB_AGES][NZ][WAVE];
+    const int lane = threadIdx.x & (WAVE - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = blockIdx.y, i = grp * WB_AGES + wv, g = blockIdx.x * WAVE + lane, gg = min(g, n - 1);
+    if (i < NA) {
+        float w[NZ];
+#pragma unroll
+        for (int j = 0; j < NZ; ++j) w[j] = 0.0f;
+        for (int q0 = 0; q0 < n_split; q0 += WB_Q) {   // WB_Q products' loads in flight
+            float v[WB_Q][NZ];
+#pragma unroll
+            for (int u = 0; u < WB_Q; ++u)
+#pragma unroll
+                for (int j = 0; j < NZ; ++j)
+                    v[u][j] = wbar[min(q0 + u, n_split - 1) * split + (size_t)(j * NA + i) * ld + gg];
+#pragma unroll
+            for (int u = 0; u < WB_Q; ++u)
+#pragma unroll
+                for (int j = 0; j < NZ; ++j)
+                    if (q0 + u < n_split) w[j] += v[u][j];
+        }
+        const float pa = pw[(size_t)i * n + gg];
+        float da = 0.0f;
+#pragma unroll
+        for (int j = 0; j < NZ; ++j) {
+            da = fmaf(pw[(size_t)(PW_PZ + j) * n + gg], w[j], da);
+            dz[wv][j][lane] = pa * w[j];
+        }
+        if (g < n) pb[(size_t)i * n + g] = da;
+    }
+    __syncthreads();
+    const int ages = min(WB_AGES, NA - grp * WB_AGES);
+    for (int j = wv; j < NZ; j += WB_AGES) {
+        float v = 0.0f;
+        for (int t = 0; t < ages; ++t) v += dz[t][j][lane];
+        if (g < n) pb[(size_t)(NA + grp * NZ + j) * n + g] = v;
+    }
 }
+static_assert((WB_SMALL - 1) * WB_AGES < NA, "no group without ages");
 
 // FP64 magnitudes from the partials [t][g][quantity]: a block per galaxy, thread (r, q) sums every R-th
 // partial of quantity q, then the R row sums of each quantity are added in LDS; meanwhile the last
@@ -1103,7 +1137,7 @@ __global__ void __launch_bounds__(XWG * WAVE) k_exact_weights(DevConsts k, int n
 __global__ void __launch_bounds__(XWG * WAVE) k_exact_adjoint_wave(DevConsts k, int n, int sfh, const int *perm,
                                                                    const float *params, const float *z,
                                                                    const float *pb, float *grad) {
-    constexpr int ROWS = NA + WB_GROUPS * NZ;
+    constexpr int ROWS = NA + WB_SMALL * NZ;
     __shared__ float sp[XWG][ROWS];
     const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & (WAVE - 1);
     const int r0 = blockIdx.x * XWG, r = min(r0 + wv, n - 1), g = perm ? perm[r] : r;
@@ -1148,7 +1182,7 @@ __global__ void __launch_bounds__(XWG * WAVE) k_exact_adjoint_wave(DevConsts k, 
     if (lane < NZ) {
         float s = 0.0f;
 #pragma unroll
-        for (int q = 0; q < WB_GROUPS; ++q) s += sp[wv][NA + q * NZ + lane];
+        for (int q = 0; q < WB_SMALL; ++q) s += sp[wv][NA + q * NZ + lane];
         v[11] = s * ww.dpz;
     }
 #pragma unroll
@@ -1193,7 +1227,7 @@ __global__ void __launch_bounds__(64) k_exact_adjoint(DevConsts k, int n, int sf
 #pragma unroll
     for (int j = 0; j < NZ; ++j) {
         float v = 0.0f;
-        for (int q = 0; q < WB_GROUPS; ++q) v += pb[(size_t)(NA + q * NZ + j) * n + gg];
+        for (int q = 0; q < WB_BIG; ++q) v += pb[(size_t)(NA + q * NZ + j) * n + gg];
         pzbar[j] = v;
     }
     float gr[NP];
@@ -1296,7 +1330,7 @@ static ExactLayout exact_layout(const sps_ctx *c, int n, int prec, bool logl, bo
         if (want_grad) {
             L.o_rb = carve((size_t)nsplit * mp * c->lw * tsz);
             L.o_wb = carve((size_t)wbar_rows(n) * S_PAD * 4);
-            L.o_pb = carve((size_t)(NA + WB_GROUPS * NZ) * n * 4);
+            L.o_pb = carve((size_t)(NA + std::max(WB_BIG, WB_SMALL) * NZ) * n * 4);
         }
     }
     L.bytes = off;
@@ -1456,19 +1490,15 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
         else if (c->launch.exact_ring) hipLaunchKernelGGL((k_xgemm<SPS_BF16X, EPI_STORE, true>), g2, b2, 0, s, b);
         else hipLaunchKernelGGL((k_xgemm<SPS_BF16X, EPI_STORE, false>), g2, b2, 0, s, b);
         float *pb = (float *)(W + o_pb);
-        if (b.k_splits > 1) {
-            const size_t n4 = b.c_split / 4;
-            hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, n4, b.k_splits, n4,
-                               (v4f *)b.C);
-        }
         if (big) {
-            hipLaunchKernelGGL(k_wbar_reduce<256>, dim3((n + 255) / 256, WB_GROUPS), dim3(256), 0, s, n,
+            static_assert(XSPLIT_BLOCKS < GPL_BIG_N / XBM * (S_PAD / XBN), "one partial product");
+            hipLaunchKernelGGL(k_wbar_reduce, dim3((n + 255) / 256, WB_BIG), dim3(256), 0, s, n,
                                (const float *)pw, (const float *)b.C, mp, pb);
             hipLaunchKernelGGL(k_exact_adjoint, dim3((n + 64 / GPL - 1) / (64 / GPL)), dim3(64), 0, s, c->k, n, sfh,
                                (const float *)params, (const float *)z, (const float *)pw, (const float *)pb, grad);
         } else {
-            hipLaunchKernelGGL(k_wbar_reduce<64>, dim3((n + 63) / 64, WB_GROUPS), dim3(64), 0, s, n,
-                               (const float *)pw, (const float *)b.C, mp, pb);
+            hipLaunchKernelGGL(k_wbar_reduce_wave, dim3((n + WAVE - 1) / WAVE, WB_SMALL), dim3(WB_AGES * WAVE), 0, s, n,
+                               (const float *)pw, (const float *)b.C, mp, b.k_splits, b.c_split, pb);
             hipLaunchKernelGGL(k_exact_adjoint_wave, dim3((n + XWG - 1) / XWG), dim3(XWG * WAVE), 0, s, c->k, n, sfh,
                                perm, (const float *)params, (const float *)z, (const float *)pb, grad);
         }
