@@ -313,9 +313,9 @@ def bench_exact(dev, n=4096, steps=5, warmup=2, cpu=False, budget_s=10.0):
     # band's filter support (about a third of this grid), so rates computed from it are
     # effective rates; the executed matrix-core utilisation is the rocprofv3 busy counter
     gemm_flop = 2.0 * n * 1128 * 5000
-    # dense matrix-core peaks of MI355X: FP32 157.3 TFLOP/s; BF16 2.5 PFLOP/s, of which the
-    # hi/lo split spends three products per algorithmic one
-    peaks = {"f32": (157.3, 1), "bf16x": (2500.0, 3)}
+    # dense BF16 matrix-core peak of MI355X, 2.5 PFLOP/s: FP32 runs as three BF16 parts per operand,
+    # six products per algorithmic one, the hi/lo split spends three
+    peaks = {"f32": (2500.0, 6), "bf16x": (2500.0, 3)}
     for name, prec in (("f32", sps.SPS_F32), ("bf16x", sps.SPS_BF16X)):
         # the tile order the autotuner picks for this shape (results do not depend on it)
         chosen, tune_ms = ctx.autotune_exact(synth.SFH_DPL, params, zt, obs, sigma, mask, prec=prec)
