@@ -21,7 +21,6 @@
 
 namespace sps {
 
-typedef float f4v __attribute__((ext_vector_type(4)));
 typedef double d4v __attribute__((ext_vector_type(4)));
 
 constexpr int NSSP = NZ * NA;
@@ -39,8 +38,6 @@ __device__ inline void split3(float v, uint16_t &h, uint16_t &m, uint16_t &l) {
     l = f2bf(r - bf2f(m));
 }
 
-__device__ inline float e_exp(float x) { return expf(x); }
-__device__ inline double e_exp(double x) { return exp(x); }
 
 constexpr double GAUSS_K2 = 0.84932180028801904272;   // sqrt(log2(e) / 2): exp(-x^2 / 2) = exp2(-(K x)^2)
 constexpr float LOG2E_F = 1.4426950408889634f;
