@@ -482,6 +482,7 @@ int sps_create(sps_ctx **out, int device, const sps_ssp_desc *ssp, const sps_fil
     for (int l = 0; l < nw; ++l) {
         double lo = ssp->wave_A[l == 0 ? 0 : l - 1], hi = ssp->wave_A[l == nw - 1 ? nw - 1 : l + 1];
         c->h_trap[l] = 0.5 * (hi - lo);
+        if (l > 0) c->h_step = std::max(c->h_step, ssp->wave_A[l] / ssp->wave_A[l - 1]);
     }
     // keep filter descriptors in double for the table builds
     const size_t S = (size_t)NZ * NA, nl = S * nw;

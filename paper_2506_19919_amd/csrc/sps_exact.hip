@@ -249,8 +249,12 @@ struct XArgs {
     // 32-wide) inside some band's 8-sigma filter support for some galaxy of the tile; null: all
     const int4 *win;
     // rows in z order: the forward epilogue skips, per wave, the bands farther than 8 sigma
-    // from all of its wavelengths (a wave's galaxies then share nearly one redshift)
+    // from all of its wavelengths (a wave's galaxies then share nearly one redshift), unless a band's 8 sigma
+    // hold no wavelength of the grid at all for a galaxy of the wave: all its terms are then out there, and
+    // their ratio is its magnitude.  dense: bit b set if they hold one wherever band b lies inside the grid
     int band_skip;
+    double lam_first, lam_last;
+    unsigned dense;
     // tile order: 1 M fastest, 2 N fastest, 3 bands of XBAND row tiles; xcd: one contiguous run of
     // tiles per XCD (1) or dispatch order (0).  Every order computes the same tiles the same way.
     int order, xcd;
@@ -516,6 +520,17 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
             tc[bb] = (float)(-a.fc[bb] * a.inv_fs[bb] * GAUSS_K2);
         }
         const float delta2 = delta * LOG2E_F, tauv2 = -tauv * LOG2E_F;
+        unsigned keep = 0;   // bands never skipped
+        if (a.band_skip) {
+#pragma unroll
+            for (int bb = 0; bb < NB_MAX; ++bb) {
+                if (bb >= a.n_band) break;
+                const double xf = (opz * a.lam_first - a.fc[bb]) * a.inv_fs[bb];
+                const double xl = (opz * a.lam_last - a.fc[bb]) * a.inv_fs[bb];
+                const bool empty = xf > -8.0 ? xf >= 8.0 : (xl <= -8.0 || !((a.dense >> bb) & 1u));
+                if (__ballot(empty) != 0) keep |= 1u << bb;
+            }
+        }
         // (beyond the grid the constants are zero, and so are the SED columns: those columns
         // add exact zeros)
         if (tid < XBN) swc[tid] = *(const v4f *)(a.wc + 4 * (size_t)(tile_n + tid));
@@ -539,7 +554,7 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
         if (a.band_skip) {
             const int l0 = tile_n + pp * PW + half * (PW / 2), l1 = min(l0 + PW / 2 - 1, a.n_wave - 1);
             const double u0 = opz * a.wave[min(l0, a.n_wave - 1)], u1 = opz * a.wave[l1];
-            act = 0;
+            act = keep;
 #pragma unroll
             for (int bb = 0; bb < NB_MAX; ++bb) {
                 if (bb >= a.n_band) break;
@@ -1436,6 +1451,11 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
         a.n_wave = nw;
         a.n_band = nb;
         for (int b = 0; b < NB_MAX; ++b) { a.fc[b] = c->h_fc[b]; a.inv_fs[b] = 1.0 / c->h_fs[b]; }
+        a.lam_first = c->h_wave.front();
+        a.lam_last = c->h_wave.back();
+        // the wavelength after one at or below (c - 8 s) / (1 + z) lies at most h_step times higher
+        for (int b = 0; b < nb; ++b)
+            if ((c->h_fc[b] - 8.0 * c->h_fs[b]) * c->h_step < c->h_fc[b] + 8.0 * c->h_fs[b]) a.dense |= 1u << b;
         a.part = part;
         a.npart = npart;
         tile_order(c, a);

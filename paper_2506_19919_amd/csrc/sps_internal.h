@@ -75,6 +75,7 @@ struct sps_ctx {
     unsigned prec_mask = 0;
     sps::DevConsts k{};
     std::vector<double> h_wave, h_trap;
+    double h_step = 1.0;           // largest ratio of consecutive wavelengths
     double h_fc[SPS_MAX_BAND] = {0}, h_fs[SPS_MAX_BAND] = {0};   // filter constants (FP64)
     // device tables
     double *d_lum64 = nullptr;     // [S][n_wave]

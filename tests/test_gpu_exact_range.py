@@ -1,0 +1,36 @@
+"""Exact-path calls at the ends of what they accept: a grid that ends short of a band."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from gpu_common import dev, gal_inputs, soa
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("prec_name", ["SPS_F32", "SPS_BF16X"])
+@pytest.mark.parametrize("n", [129, 400, 16384])     # ranked by one block, and by passes of their own
+def test_band_past_the_end_of_the_grid(filt6, n, prec_name):
+    # a grid from 3000 A: at z > 1.3 the bluest band lies more than 8 widths below its first wavelength, to
+    # 13 widths its sums are still FP32 numbers.  Batches in z order leave bands out of a wave's reach out;
+    # the same 100 galaxies in one row tile, never in z order, keep every term.  Where the band does reach
+    # the grid the terms left out are below exp(-32) of it; where it does not, none may be.  The same sums in
+    # the same order within a tile of 128 wavelengths, the tiles' added in order: FP32 rounding of a
+    # magnitude up to 128, 4e-6 each, of the sums, 1e-6 mag
+    import paper_2506_19919_amd as sps
+    prec = getattr(sps, prec_name)
+    g = synth.ssp_grid(1500)
+    k = g["wave_A"] >= 3000.0
+    cut = dict(g, wave_A=g["wave_A"][k].copy(), lum=np.ascontiguousarray(g["lum"][..., k]))
+    ctx = sps.Context(cut, filt6, precisions=(prec,), max_gal=n, max_exact=n)
+    sfh, th, z = gal_inputs("dpl", 100, 861)
+    at = np.arange(n) % 100
+    few = ctx.phot_exact(sfh, soa(th), dev(z), prec=prec).cpu().numpy()
+    many = ctx.phot_exact(sfh, soa(th[at]), dev(z[at]), prec=prec).cpu().numpy()
+    ctx.close()
+    blue = (3000.0 * (1 + z) - synth.filters()["center_A"][0]) / synth.filters()["sigma_A"][0]
+    assert ((blue > 8) & (blue < 12)).sum() >= 5 and np.isfinite(few[blue < 12]).all()
+    assert np.array_equal(np.isfinite(many), np.isfinite(few[at]))
+    ok = np.isfinite(many)
+    assert np.abs(many - few[at])[ok].max() <= 1e-5
