@@ -514,10 +514,14 @@ int sps_create(sps_ctx **out, int device, const sps_ssp_desc *ssp, const sps_fil
     c->lw = lw;
     const size_t np = (size_t)S_PAD * lw;
     if (prec_mask & (1u << SPS_F32)) {
+        double most = 0.0;
+        for (size_t i = 0; i < nl; ++i)
+            if (std::isfinite(ssp->lum[i])) most = std::max(most, std::fabs(ssp->lum[i]));
+        if (most > 0.0 && most < 0.5) c->lum32_exp = -std::ilogb(most) - 1;   // largest to 0.5 .. 1
         std::vector<uint16_t> ls(3 * np, 0), lt(3 * np, 0);
         for (size_t s = 0; s < S; ++s)
             for (int l = 0; l < nw; ++l) {
-                const float f = (float)ssp->lum[s * nw + l];
+                const float f = (float)std::ldexp(ssp->lum[s * nw + l], c->lum32_exp);
                 const uint16_t h = bf16_rne(f);
                 const float r = std::isfinite(f) ? f - bf16_to_f(h) : 0.0f;
                 const uint16_t m = bf16_rne(r), lo = bf16_rne(r - bf16_to_f(m));

@@ -15,6 +15,7 @@
 // Gradient (FP32 / BF16X): dlogL/dnum -> Rbar[g][l] -> second GEMM
 // Wbar = Rbar . L^T -> dP_age, dP_Z -> the weights adjoint shared with the
 // approximate path; dust derivatives come from extra epilogue partials.
+#include <cmath>
 #include <type_traits>
 
 #include "sps_pair.h"
@@ -771,7 +772,8 @@ __global__ void __launch_bounds__(256) k_expand(int n, const float *pw, void *w)
 // dlogL/dnum.  Eight lanes per galaxy, a band each; perm: the caller's index of a rank (null: the same).
 // sums, with mag: the tile sums [g][5][n_band] of the numerator, the normaliser and the numerator's dust
 // derivatives are kept for a later backward, which passes them with vjp in place of the partials; sperm:
-// the caller's index of a rank for them.  A block's 32 galaxies share a row tile.  One thread per galaxy
+// the caller's index of a rank for them.  lum_unit: what the table's unit is worth (sps_ctx::lum32_exp); only the
+// magnitude sees it, dlogL/dnum and the table of the gradient GEMM share it.  A block's 32 galaxies share a row tile.  One thread per galaxy
 // and a pass of its own for the tile sums took 28 + 9 us at 4096 galaxies.
 template <bool GRAD>
 __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_tiles, const int *perm,
@@ -779,7 +781,7 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
                                                       const float *part, int npart, float *mag, const float *obs,
                                                       const float *sigma, const uint8_t *mask, float *logl,
                                                       float *grad, float *cnum, int vjp, float *sums,
-                                                      const int *sperm) {
+                                                      const int *sperm, double lum_unit) {
     static_assert(NB_MAX == 8, "a lane per band");
     const int r = blockIdx.x * 32 + (threadIdx.x >> 3), b = threadIdx.x & 7, nb = k.n_band;
     const bool valid = r < n, act = b < nb;
@@ -816,7 +818,7 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
     chi = group_sum<8>(chi);
     const double dl = (1.0 + zf) * k.dh_cm * h * chi;
     const double m0 = -2.5 * log10((1.0 + zf) * k.kfac) + 5.0 * log10(dl) - 2.5 * (double)params[g];
-    const double num = v[0], m = m0 - 2.5 * log10(num / (double)v[1]);
+    const double num = v[0], m = m0 - 2.5 * log10(num * lum_unit / (double)v[1]);
     if (mag) {
         if (valid && act) mag[(size_t)g * nb + b] = (float)m;
         if (GRAD && sums && valid && act)
@@ -1475,7 +1477,8 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
         auto kf = dust5 ? k_exact_finish<true> : k_exact_finish<false>;
         hipLaunchKernelGGL(kf, dim3((n + 31) / 32), dim3(256), 0, s, c->k, n, n_tiles, perm,
                            (const float *)params, z_r, (const int4 *)win, (const float *)part, npart, (float *)mag_out,
-                           obs, sigma, mask, logl, grad, cn, vjp ? 1 : 0, sums, sperm);
+                           obs, sigma, mask, logl, grad, cn, vjp ? 1 : 0, sums, sperm,
+                           prec == SPS_F32 ? std::ldexp(1.0, -c->lum32_exp) : 1.0);
     }
     if (want_grad) {
         void *r_hi = W + o_rb;   // Rbar rows: BF16 parts interleaved [mp][3 or 2 lw]

@@ -84,6 +84,9 @@ struct sps_ctx {
     //   ls: [S_PAD][LW]  (B of the gradient GEMM, k = wavelength)
     //   lt: [LW][S_PAD]  (B of the forward GEMM, k = SSP)
     int lw = 0;
+    // (the FP32 ones hold 2^lum32_exp x the luminosities: the third part lies 16 bits below the first, so a table
+    // in small units would lose it below 2^-126; 0 where the largest is 1/2 or more)
+    int lum32_exp = 0;
     uint16_t *d_ls_b3 = nullptr, *d_lt_b3 = nullptr;   // FP32 as BF16 hi + mid + lo, interleaved (bf3_at)
     uint16_t *d_ls_bx = nullptr, *d_lt_bx = nullptr;   // BF16 hi + lo, interleaved (bfx_at)
     float *d_wc = nullptr;         // per wavelength [LW][4]: ln(l / 5500 A), l q_l, q_l / l, 0

@@ -34,3 +34,28 @@ def test_band_past_the_end_of_the_grid(filt6, n, prec_name):
     assert np.array_equal(np.isfinite(many), np.isfinite(few[at]))
     ok = np.isfinite(many)
     assert np.abs(many - few[at])[ok].max() <= 1e-5
+
+
+@pytest.mark.parametrize("e", [-124, -118, -110, -40, 90])
+def test_f32_keeps_its_precision_at_any_scale_of_the_grid(filt6, e):
+    # SPS_F32 carries its operands as three BF16 parts, the last 16 bits below the first: a grid in small units
+    # keeps all of them.  Magnitudes to the FP32 path's 1e-4 of the FP64 path on the same grid, and the
+    # gradient, which no scale changes, to 1e-6 of the unscaled grid's largest component
+    import paper_2506_19919_amd as sps
+    n = 150
+    sfh, th, z = gal_inputs("dpl", n, 871)
+    gbar = dev(np.random.default_rng(872).normal(size=(n, 6)))
+    base = synth.ssp_grid(500)
+    grads = []
+    for lum in (base["lum"], np.ldexp(base["lum"], e)):
+        ctx = sps.Context(dict(base, lum=lum), filt6, precisions=(sps.SPS_F64, sps.SPS_F32), max_gal=n, max_exact=n)
+        ref = ctx.phot_exact(sfh, soa(th, torch.float64), dev(z, torch.float64), prec=sps.SPS_F64)
+        par = soa(th).requires_grad_()
+        mag = sps.phot_exact(ctx, par, dev(z), sfh=sfh, prec=sps.SPS_F32)
+        assert (mag.detach() - ref).abs().max() <= 1e-4
+        grads.append(ctx.phot_vjp(sfh, soa(th), dev(z), gbar, path=sps.SPS_PATH_EXACT, prec=sps.SPS_F32))
+        again, = torch.autograd.grad(mag, par, gbar)       # through the kept band sums
+        assert (again - grads[-1]).abs().max() <= 1e-6 * grads[-1].abs().max()
+        ctx.close()
+    bar = 1e-6 * grads[0].abs().max(dim=0, keepdim=True).values
+    assert ((grads[1] - grads[0]).abs() <= bar).all()
