@@ -228,6 +228,10 @@ template <int P> constexpr int x_stage() { return 2 * x_parts<P>() * XSUB; }    
 constexpr int XSPLIT_MAX = 8, XSPLIT_BLOCKS = 640;
 constexpr int XBAND = 8;                                     // row tiles per band (tile order 3)
 
+// a row tile's window (k_xwindows) packs the bands that the forward epilogue must not skip over its first tile
+__device__ inline int win_x(int4 w) { return w.x & 0xffffff; }
+__device__ inline unsigned win_keep(int4 w) { return (unsigned)w.x >> 24; }
+
 struct XArgs {
     int M, N, K;
     const void *A;             // BF16 parts interleaved, [M][3 lda] (bf3_at) or [M][2 lda] (bfx_at)
@@ -246,16 +250,13 @@ struct XArgs {
     double fc[NB_MAX], inv_fs[NB_MAX];
     float *part;               // [n_nt][npart][M] (quantity-major: the finish reads it coalesced)
     int npart;
-    // per 128-galaxy row tile: the wavelength tiles (x, y: 128-wide, [x, y)) and k-tiles (z, w:
+    // per 128-galaxy row tile: the wavelength tiles (win_x, y: 128-wide, [win_x, y)) and k-tiles (z, w:
     // 32-wide) inside some band's 8-sigma filter support for some galaxy of the tile; null: all
     const int4 *win;
     // rows in z order: the forward epilogue skips, per wave, the bands farther than 8 sigma
-    // from all of its wavelengths (a wave's galaxies then share nearly one redshift), unless a band's 8 sigma
-    // hold no wavelength of the grid at all for a galaxy of the wave: all its terms are then out there, and
-    // their ratio is its magnitude.  dense: bit b set if they hold one wherever band b lies inside the grid
+    // from all of its wavelengths (a wave's galaxies then share nearly one redshift), but for the row tile's
+    // win_keep
     int band_skip;
-    double lam_first, lam_last;
-    unsigned dense;
     // tile order: 1 M fastest, 2 N fastest, 3 bands of XBAND row tiles; xcd: one contiguous run of
     // tiles per XCD (1) or dispatch order (0).  Every order computes the same tiles the same way.
     int order, xcd;
@@ -362,6 +363,7 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
         tile_n = (nfast ? t % a.n_nt : t / a.n_mt) * XBN;
     }
     int klen = a.K, kbeg = 0;
+    [[maybe_unused]] unsigned keep = 0;
     if (a.win) {
         // wavelengths outside every band's support for all of this tile's galaxies: the
         // forward tile's band sums are below exp(-32) of the band's: the tile is not computed
@@ -372,8 +374,9 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
             const int nk_w = max(w.w - w.z, 0), k0 = w.z + nk_w * sp / nsp, k1 = w.z + nk_w * (sp + 1) / nsp;
             kbeg = k0 * XBK;
             klen = (k1 - k0) * XBK;
-        } else if (tile_n / XBN < w.x || tile_n / XBN >= w.y) {
-            return;   // k_exact_finish reads only the tiles inside the window
+        } else {
+            if (tile_n / XBN < win_x(w) || tile_n / XBN >= w.y) return;   // k_exact_finish reads only the tiles inside
+            keep = win_keep(w);
         }
     }
 
@@ -521,17 +524,6 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
             tc[bb] = (float)(-a.fc[bb] * a.inv_fs[bb] * GAUSS_K2);
         }
         const float delta2 = delta * LOG2E_F, tauv2 = -tauv * LOG2E_F;
-        unsigned keep = 0;   // bands never skipped
-        if (a.band_skip) {
-#pragma unroll
-            for (int bb = 0; bb < NB_MAX; ++bb) {
-                if (bb >= a.n_band) break;
-                const double xf = (opz * a.lam_first - a.fc[bb]) * a.inv_fs[bb];
-                const double xl = (opz * a.lam_last - a.fc[bb]) * a.inv_fs[bb];
-                const bool empty = xf > -8.0 ? xf >= 8.0 : (xl <= -8.0 || !((a.dense >> bb) & 1u));
-                if (__ballot(empty) != 0) keep |= 1u << bb;
-            }
-        }
         // (beyond the grid the constants are zero, and so are the SED columns: those columns
         // add exact zeros)
         if (tid < XBN) swc[tid] = *(const v4f *)(a.wc + 4 * (size_t)(tile_n + tid));
@@ -772,8 +764,8 @@ __global__ void __launch_bounds__(256) k_expand(int n, const float *pw, void *w)
 // dlogL/dnum.  Eight lanes per galaxy, a band each; perm: the caller's index of a rank (null: the same).
 // sums, with mag: the tile sums [g][5][n_band] of the numerator, the normaliser and the numerator's dust
 // derivatives are kept for a later backward, which passes them with vjp in place of the partials; sperm:
-// the caller's index of a rank for them.  lum_unit: what the table's unit is worth (sps_ctx::lum32_exp); only the
-// magnitude sees it, dlogL/dnum and the table of the gradient GEMM share it.  A block's 32 galaxies share a row tile.  One thread per galaxy
+// the caller's index of a rank for them.  k.kfac takes in the table's unit (sps_ctx::lum32_exp): only
+// the magnitude sees it, dlogL/dnum and the table of the gradient GEMM share it.  A block's 32 galaxies share a row tile.  One thread per galaxy
 // and a pass of its own for the tile sums took 28 + 9 us at 4096 galaxies.
 template <bool GRAD>
 __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_tiles, const int *perm,
@@ -781,7 +773,7 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
                                                       const float *part, int npart, float *mag, const float *obs,
                                                       const float *sigma, const uint8_t *mask, float *logl,
                                                       float *grad, float *cnum, int vjp, float *sums,
-                                                      const int *sperm, double lum_unit) {
+                                                      const int *sperm) {
     static_assert(NB_MAX == 8, "a lane per band");
     const int r = blockIdx.x * 32 + (threadIdx.x >> 3), b = threadIdx.x & 7, nb = k.n_band;
     const bool valid = r < n, act = b < nb;
@@ -799,7 +791,7 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
         const size_t qs = (size_t)nb * n, ts = (size_t)npart * n;
         const int t_end = min(w.y, n_tiles);
 #pragma unroll 4
-        for (int t = w.x; t < t_end; ++t) {
+        for (int t = win_x(w); t < t_end; ++t) {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) v[q] += pp[t * ts + q * qs];
         }
@@ -818,7 +810,7 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
     chi = group_sum<8>(chi);
     const double dl = (1.0 + zf) * k.dh_cm * h * chi;
     const double m0 = -2.5 * log10((1.0 + zf) * k.kfac) + 5.0 * log10(dl) - 2.5 * (double)params[g];
-    const double num = v[0], m = m0 - 2.5 * log10(num * lum_unit / (double)v[1]);
+    const double num = v[0], m = m0 - 2.5 * log10(num / (double)v[1]);
     if (mag) {
         if (valid && act) mag[(size_t)g * nb + b] = (float)m;
         if (GRAD && sums && valid && act)
@@ -1257,9 +1249,10 @@ __global__ void __launch_bounds__(64) k_exact_adjoint(DevConsts k, int n, int sf
 // Per 128-galaxy row tile: the rest-frame wavelengths any band reaches within 8 sigma for any
 // of the tile's galaxies, [min_b (c_b - 8 s_b) / (1 + z_max), max_b (c_b + 8 s_b) / (1 + z_min)],
 // as 128-wide wavelength tiles and 32-wide k-tiles of the padded grid, one index of margin on
-// each side.  One block per row tile.
+// each side; and the bands that the forward epilogue must not skip.  One block per row tile.
 __global__ void __launch_bounds__(128) k_xwindows(int n, int n_wave, FiltConst fl, int nb, const float *z,
-                                                  const double *wave, int4 *win) {
+                                                  const double *wave, double lam_first, double lam_last,
+                                                  unsigned dense, int4 *win) {
     __shared__ float zlo[2], zhi[2];
     const int tid = threadIdx.x, g = min((int)blockIdx.x * XBM + tid, n - 1);
     float mn = z[g], mx = mn;
@@ -1273,10 +1266,22 @@ __global__ void __launch_bounds__(128) k_xwindows(int n, int n_wave, FiltConst f
     }
     __syncthreads();
     const double z0 = fmin(zlo[0], zlo[1]), z1 = fmax(zhi[0], zhi[1]);
+    // far_bands: the bands that come no nearer than 5 sigma to a wavelength of the grid for some galaxy of the tile: past
+    // either end of it at the tile's largest or smallest z, or in a grid too coarse for them (bit clear in dense:
+    // the wavelength after one at or below (c - 5 s) / (1 + z) may lie above (c + 5 s) / (1 + z)).  Such a band's
+    // magnitude is made of far terms, so the epilogue must skip none; of a nearer one's sum, the terms beyond 8
+    // sigma are at most exp(-(64 - 25) / 2) = 3e-9.
+    unsigned far_bands = ~dense;
     double lo = 1e300, hi = 0.0;
-    for (int b = 0; b < nb; ++b) {
-        lo = fmin(lo, fl.lo8[b] / (1.0 + z1));
-        hi = fmax(hi, fl.hi8[b] / (1.0 + z0));
+#pragma unroll
+    for (int b = 0; b < NB_MAX; ++b) {   // unrolled: the bands' limits are read together
+        const double l8 = fl.lo8[b], h8 = fl.hi8[b];
+        if (b >= nb) continue;
+        lo = fmin(lo, l8 / (1.0 + z1));
+        hi = fmax(hi, h8 / (1.0 + z0));
+        // c - 5 s and c + 5 s
+        if ((1.0 + z1) * lam_first >= 0.8125 * h8 + 0.1875 * l8 || (1.0 + z0) * lam_last <= 0.8125 * l8 + 0.1875 * h8)
+            far_bands |= 1u << b;
     }
     // the number of wavelengths below lo (wave 0) and up to hi (wave 1) on the ascending grid: 64 probes at
     // a time (a serial binary search waited out 26 loads, 7.6 us)
@@ -1295,7 +1300,7 @@ __global__ void __launch_bounds__(128) k_xwindows(int n, int n_wave, FiltConst f
     if (tid != 0) return;
     const int l0 = max(found[0] - 1, 0);
     const int l1 = min(found[1], n_wave - 1);   // one past the last index <= hi, as margin
-    win[blockIdx.x] = make_int4(l0 / XBN, l1 / XBN + 1, l0 / XBK, l1 / XBK + 1);
+    win[blockIdx.x] = make_int4((int)((unsigned)(l0 / XBN) | far_bands << 24), l1 / XBN + 1, l0 / XBK, l1 / XBK + 1);
 }
 
 // ------------------------------------------------------------------ launcher
@@ -1433,7 +1438,11 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
     } else {
         const FiltConst fl = filt_const(c->h_fc, c->h_fs);
         win = (int4 *)(W + o_win);
-        hipLaunchKernelGGL(k_xwindows, dim3(mp / XBM), dim3(128), 0, s, n, nw, fl, nb, z_r, c->d_wave, win);
+        unsigned dense = 0;
+        for (int b = 0; b < nb; ++b)
+            if ((c->h_fc[b] - 5.0 * c->h_fs[b]) * c->h_step < c->h_fc[b] + 5.0 * c->h_fs[b]) dense |= 1u << b;
+        hipLaunchKernelGGL(k_xwindows, dim3(mp / XBM), dim3(128), 0, s, n, nw, fl, nb, z_r, c->d_wave,
+                           c->h_wave.front(), c->h_wave.back(), dense, win);
         XArgs a{};
         a.win = win;
         a.band_skip = zordered ? 1 : 0;
@@ -1453,11 +1462,6 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
         a.n_wave = nw;
         a.n_band = nb;
         for (int b = 0; b < NB_MAX; ++b) { a.fc[b] = c->h_fc[b]; a.inv_fs[b] = 1.0 / c->h_fs[b]; }
-        a.lam_first = c->h_wave.front();
-        a.lam_last = c->h_wave.back();
-        // the wavelength after one at or below (c - 8 s) / (1 + z) lies at most h_step times higher
-        for (int b = 0; b < nb; ++b)
-            if ((c->h_fc[b] - 8.0 * c->h_fs[b]) * c->h_step < c->h_fc[b] + 8.0 * c->h_fs[b]) a.dense |= 1u << b;
         a.part = part;
         a.npart = npart;
         tile_order(c, a);
@@ -1475,10 +1479,11 @@ static int exact_core(sps_ctx *c, hipStream_t s, int n, int sfh, int prec, const
     float *cn = lik ? (float *)(W + o_cn) : nullptr;
     if (!f64) {
         auto kf = dust5 ? k_exact_finish<true> : k_exact_finish<false>;
-        hipLaunchKernelGGL(kf, dim3((n + 31) / 32), dim3(256), 0, s, c->k, n, n_tiles, perm,
+        DevConsts k = c->k;
+        if (prec == SPS_F32) k.kfac = std::ldexp(k.kfac, -c->lum32_exp);
+        hipLaunchKernelGGL(kf, dim3((n + 31) / 32), dim3(256), 0, s, k, n, n_tiles, perm,
                            (const float *)params, z_r, (const int4 *)win, (const float *)part, npart, (float *)mag_out,
-                           obs, sigma, mask, logl, grad, cn, vjp ? 1 : 0, sums, sperm,
-                           prec == SPS_F32 ? std::ldexp(1.0, -c->lum32_exp) : 1.0);
+                           obs, sigma, mask, logl, grad, cn, vjp ? 1 : 0, sums, sperm);
     }
     if (want_grad) {
         void *r_hi = W + o_rb;   // Rbar rows: BF16 parts interleaved [mp][3 or 2 lw]

@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 def test_band_past_the_end_of_the_grid(filt6, n, prec_name):
     # a grid from 3000 A: at z > 1.3 the bluest band lies more than 8 widths below its first wavelength, to
     # 13 widths its sums are still FP32 numbers.  Batches in z order leave bands out of a wave's reach out;
-    # the same 100 galaxies in one row tile, never in z order, keep every term.  Where the band does reach
-    # the grid the terms left out are below exp(-32) of it; where it does not, none may be.  The same sums in
+    # the same 100 galaxies in one row tile, never in z order, keep every term.  Where the band comes near
+    # the grid the terms left out are at most 3e-9 of it; where it does not, none may be.  The same sums in
     # the same order within a tile of 128 wavelengths, the tiles' added in order: FP32 rounding of a
     # magnitude up to 128, 4e-6 each, of the sums, 1e-6 mag
     import paper_2506_19919_amd as sps
