@@ -1643,11 +1643,14 @@ static int launch_hmc_exact(sps_ctx *c, hipStream_t s, const sps_hmc_cfg *cfg, i
     return SPS_OK;
 }
 
-// Up to HMC_PAIR_MAX chains a pair of waves takes each chain (k_hmc_pair), above it a pair of lanes
-// (k_hmc), whose waves span ever fewer redshift buckets as the batch grows.  Pair of waves / lanes, us
-// per leapfrog step: 13 / 101 at 512 chains, 28 / 84 at 2048, 46 / 80 at 4096, 84 / 90 at 8192, 103 / 91
-// at 10,240.
-constexpr int HMC_PAIR_MAX = 8192;
+// Up to this many chains a pair of waves takes each chain (k_hmc_pair), above it a pair of lanes (k_hmc).
+// A pair of waves costs the same whatever the bands and redshifts; the lanes' waves span ever fewer redshift
+// buckets as the batch grows, none but one where the galaxies share a redshift, and cost less with fewer bands.
+// So the lines are where the lanes at their best, one band and one redshift, break even.  us per leapfrog step (30 of
+// them and the start), pairs / lanes, one band at one redshift and six bands at redshifts 0.1 to 3: double power law
+// 4096 chains 41 / 62 and 47 / 87, 6144 57 / 62 and 69 / 91, 7168 65 / 62 and 79 / 92, 8192 75 / 62 and 88 / 92;
+// log-normal, whose lanes go through more rules, 6144 54 / 70 and 63 / 100, 8192 70 / 70 and 83 / 99.
+static int hmc_pair_max(int sfh) { return sfh == SPS_SFH_DPL ? 6144 : 8192; }
 
 int launch_hmc(sps_ctx *c, hipStream_t s, const sps_hmc_cfg *cfg, int n_gal, int sfh, const float *z,
                const float *obs, const float *sigma, const uint8_t *mask, const float *bounds, const float *prior,
@@ -1667,7 +1670,7 @@ int launch_hmc(sps_ctx *c, hipStream_t s, const sps_hmc_cfg *cfg, int n_gal, int
     const int it0 = cfg->it_begin, it1 = cfg->it_end > 0 ? cfg->it_end : nit;
     if (c->hstate_bytes < hmc_state_bytes(nslot))
         return set_error(SPS_E_STATE, "the HMC chain state needs n_gal * n_chain reserved galaxies (call sps_reserve)");
-    const bool pair = nslot <= HMC_PAIR_MAX;   // those kernels keep the caller's order: no sort
+    const bool pair = nslot <= hmc_pair_max(sfh);   // those kernels keep the caller's order: no sort
     int rc = pair ? SPS_OK : launch_bucket_sort(c, s, n_gal, z);
     if (rc) return rc;
     const int *perm = pair ? nullptr : c->d_perm;
