@@ -228,9 +228,9 @@ template <int P> constexpr int x_stage() { return 2 * x_parts<P>() * XSUB; }    
 constexpr int XSPLIT_MAX = 8, XSPLIT_BLOCKS = 640;
 constexpr int XBAND = 8;                                     // row tiles per band (tile order 3)
 
-// a row tile's window (k_xwindows) packs the bands that the forward epilogue must not skip over its first tile
-__device__ inline int win_x(int4 w) { return w.x & 0xffffff; }
-__device__ inline unsigned win_keep(int4 w) { return (unsigned)w.x >> 24; }
+// a row tile's window (k_xwindows) packs the bands that the forward epilogue must not skip over its first k-tile
+__device__ inline int win_z(int4 w) { return w.z & 0xffffff; }
+__device__ inline unsigned win_keep(int4 w) { return (unsigned)w.z >> 24; }
 
 struct XArgs {
     int M, N, K;
@@ -250,7 +250,7 @@ struct XArgs {
     double fc[NB_MAX], inv_fs[NB_MAX];
     float *part;               // [n_nt][npart][M] (quantity-major: the finish reads it coalesced)
     int npart;
-    // per 128-galaxy row tile: the wavelength tiles (win_x, y: 128-wide, [win_x, y)) and k-tiles (z, w:
+    // per 128-galaxy row tile: the wavelength tiles (x, y: 128-wide, [x, y)) and k-tiles (win_z, w:
     // 32-wide) inside some band's 8-sigma filter support for some galaxy of the tile; null: all
     const int4 *win;
     // rows in z order: the forward epilogue skips, per wave, the bands farther than 8 sigma
@@ -371,11 +371,11 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
         // there, so its K range is the window's
         const int4 w = a.win[tile_m / XBM];
         if constexpr (EPI == EPI_STORE) {
-            const int nk_w = max(w.w - w.z, 0), k0 = w.z + nk_w * sp / nsp, k1 = w.z + nk_w * (sp + 1) / nsp;
+            const int nk_w = max(w.w - win_z(w), 0), k0 = win_z(w) + nk_w * sp / nsp, k1 = win_z(w) + nk_w * (sp + 1) / nsp;
             kbeg = k0 * XBK;
             klen = (k1 - k0) * XBK;
         } else {
-            if (tile_n / XBN < win_x(w) || tile_n / XBN >= w.y) return;   // k_exact_finish reads only the tiles inside
+            if (tile_n / XBN < w.x || tile_n / XBN >= w.y) return;   // k_exact_finish reads only the tiles inside
             keep = win_keep(w);
         }
     }
@@ -791,7 +791,7 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
         const size_t qs = (size_t)nb * n, ts = (size_t)npart * n;
         const int t_end = min(w.y, n_tiles);
 #pragma unroll 4
-        for (int t = win_x(w); t < t_end; ++t) {
+        for (int t = w.x; t < t_end; ++t) {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) v[q] += pp[t * ts + q * qs];
         }
@@ -865,7 +865,7 @@ __global__ void __launch_bounds__(256) k_exact_rbar(int n, int n_wave, int ld, i
     const int g0 = blockIdx.x * RBAR_G, tid = threadIdx.x;
     const int ng = min(RBAR_G, n - g0);   // galaxies of this block (>= 1)
     const int4 wn = win[g0 / XBM];
-    const int lo = wn.z * XBK, hi = min(ld, wn.w * XBK);
+    const int lo = win_z(wn) * XBK, hi = min(ld, wn.w * XBK);
     double opz[RBAR_G];
     float cb[RBAR_G][NB_MAX], ffl[RBAR_G], delta2[RBAR_G], tauv2[RBAR_G];
 #pragma unroll
@@ -1300,7 +1300,7 @@ __global__ void __launch_bounds__(128) k_xwindows(int n, int n_wave, FiltConst f
     if (tid != 0) return;
     const int l0 = max(found[0] - 1, 0);
     const int l1 = min(found[1], n_wave - 1);   // one past the last index <= hi, as margin
-    win[blockIdx.x] = make_int4((int)((unsigned)(l0 / XBN) | far_bands << 24), l1 / XBN + 1, l0 / XBK, l1 / XBK + 1);
+    win[blockIdx.x] = make_int4(l0 / XBN, l1 / XBN + 1, (int)((unsigned)(l0 / XBK) | far_bands << 24), l1 / XBK + 1);
 }
 
 // ------------------------------------------------------------------ launcher
