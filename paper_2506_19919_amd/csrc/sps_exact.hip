@@ -1611,11 +1611,11 @@ __global__ void __launch_bounds__(RANK_T) k_exact_rank(DevConsts k, int n, const
             const unsigned long long m = __ballot(on);
             same &= on ? m : ~m;
         }
-        if (bk[t] >= 0) {
-            const int before = __popcll(same & ((1ull << lane) - 1ull)), c = cnt[wv][bk[t]];
-            at[t] = c + before;
-            if (before == 0) cnt[wv][bk[t]] = (uint16_t)(c + __popcll(same));
-        }
+        const int before = __popcll(same & ((1ull << lane) - 1ull)), c = bk[t] >= 0 ? cnt[wv][bk[t]] : 0;
+        wave_sync();   // every lane has read its bucket's count before the bucket's first lane advances it
+        at[t] = c + before;
+        if (bk[t] >= 0 && before == 0) cnt[wv][bk[t]] = (uint16_t)(c + __popcll(same));
+        wave_sync();
     }
     __syncthreads();
     // bucket tid: its waves' counts to offsets, and the exclusive scan of the totals

@@ -53,6 +53,15 @@ __device__ inline T wave_sum(T v) {
     return lane_value(v, 63);
 }
 
+// Between LDS writes of some lanes of a wave and reads of the same words by others (all 64 lanes must
+// call it).  A wave's LDS operations are done in order, so it emits nothing: it keeps the compiler from moving them
+// past each other.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ------------------------------------------------------------------ per-workgroup state
 // factors of the adjoint's sums over bins (see pair_sums)
 enum { PX_NGBAR, PX_PSBAR, PX_BURST, PX_ONE, PX_INVS3, PX_COUNT };
@@ -351,6 +360,7 @@ __device__ __forceinline__ void pair_eval(const DevConsts &k, const PairBin &bin
                     S.by[3][lane] = f9;
                 }
             }
+            wave_sync();
             // sums over the bands in the batched order: bands q, q + PG, ... for each q < PG, then those
             // added (the entries past the bands are zero)
             logl = 0.0;
