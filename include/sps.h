@@ -297,8 +297,9 @@ int sps_set_launch(sps_ctx *ctx, const sps_launch_cfg *cfg);   /* SPS_E_INVAL fo
  * inputs (a few repetitions each, the median kept), sets the fastest in the context and writes
  * it to *chosen (may be NULL); *timed_ms (may be NULL) receives the chosen candidate's time, or
  * 0 if the choice came from the cache.  If the environment variable SPS_AUTOTUNE_CACHE names a
- * file, choices are looked up there first (key: the call kind, device name and CU count, and
- * the shape of the call) and new ones are added to it (a JSON object, one entry per line).
+ * file, choices are looked up there first (key: the call kind, device name and CU count, a
+ * number that this library raises with its kernels, and the shape of the call) and new ones are
+ * added to it (a JSON object, one entry per line; entries of other numbers stay in it unused).
  *  sps_autotune_exact: exact_order x exact_xcd (x exact_ring for SPS_BF16X) on
  *    sps_loglike_grad(path = SPS_PATH_EXACT) of
  *    these inputs (obs, sigma, band_mask may be NULL: sps_phot_exact is timed instead).

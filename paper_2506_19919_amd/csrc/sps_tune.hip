@@ -82,11 +82,16 @@ void cache_write(const std::string &path, const Cache &c) {
     std::rename(tmp.c_str(), path.c_str());
 }
 
+// Part of every key: raised whenever the kernels behind a choice, or what a choice means, change, so
+// that a file's earlier entries are timed anew instead of being applied to kernels they were not timed on.  1: entries
+// without the field.  2: FP32 on BF16 parts, bands as the built-in order, the single-stage GEMM, a pair of waves per chain.
+constexpr int KERNELS = 2;
+
 std::string device_key(int device) {
     hipDeviceProp_t p{};
-    if (hipGetDeviceProperties(&p, device) != hipSuccess) return "unknown";
+    if (hipGetDeviceProperties(&p, device) != hipSuccess) return "unknown|kernels=" + std::to_string(KERNELS);
     std::ostringstream o;
-    o << p.gcnArchName << "/" << p.multiProcessorCount << "cu";
+    o << p.gcnArchName << "/" << p.multiProcessorCount << "cu|kernels=" << KERNELS;
     std::string s = o.str();
     for (char &ch : s)
         if (ch == '"' || ch == '\\' || ch == ':') ch = '_';
