@@ -251,7 +251,7 @@ struct XArgs {
     float *part;               // [n_nt][npart][M] (quantity-major: the finish reads it coalesced)
     int npart;
     // per 128-galaxy row tile: the wavelength tiles (x, y: 128-wide, [x, y)) and k-tiles (win_z, w:
-    // 32-wide) inside some band's 8-sigma filter support for some galaxy of the tile; null: all
+    // 32-wide) inside some band's 8-sigma filter support for some galaxy of the tile
     const int4 *win;
     // rows in z order: the forward epilogue skips, per wave, the bands farther than 8 sigma
     // from all of its wavelengths (a wave's galaxies then share nearly one redshift), but for the row tile's
@@ -337,17 +337,14 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
     const int T = a.n_mt * a.n_nt, nsp = (EPI == EPI_STORE) ? a.k_splits : 1, total = T * nsp, b = blockIdx.x;
     int t = b;
     if (a.xcd && total % 8 == 0) t = (b % 8) * (total / 8) + b / 8;
-    // the K range: slowest, or between M and N where windows clip it (every XCD's run of tiles
+    // the K range: between M and N, as the windows clip it (every XCD's run of tiles
     // then holds all ranges, so the mostly skipped last ones do not gather on a few XCDs, and
     // consecutive tiles still share their B rows and K range in L2)
-    int sp;
-    if (EPI == EPI_STORE && a.win != nullptr) {
+    [[maybe_unused]] int sp = 0;
+    if constexpr (EPI == EPI_STORE) {
         const int m_ = t % a.n_mt, rest = t / a.n_mt;
         sp = rest % nsp;
         t = (rest / nsp) * a.n_mt + m_;
-    } else {
-        sp = t / T;
-        t -= sp * T;
     }
     const bool nfast = a.order == 2;
     int tile_m, tile_n;
@@ -364,7 +361,7 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
     }
     int klen = a.K, kbeg = 0;
     [[maybe_unused]] unsigned keep = 0;
-    if (a.win) {
+    {
         // wavelengths outside every band's support for all of this tile's galaxies: the
         // forward tile's band sums are below exp(-32) of the band's: the tile is not computed
         // and the tile sum (k_exact_finish) skips it; the gradient GEMM's Rbar is exactly zero
@@ -388,23 +385,18 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
 
     const int nk = klen / XBK;
     if constexpr (RING) {
-        // prologue: k-tiles 0..2 in flight
+        // prologue: k-tile 0 in flight
+        static_assert(RSTAGES == 2, "the next k-tile loads while this one's products issue");
         const XRing ring = x_ring_setup(a, tile_m, tile_n, wave, lane);
-        for (int kt = 0; kt < RSTAGES - 1 && kt < nk; ++kt) x_ring_issue(ring, smem + kt * RSTAGE, kbeg + kt * XBK, wave);
+        if (nk > 0) x_ring_issue(ring, smem, kbeg, wave);
         for (int kt = 0; kt < nk; ++kt) {
-            // this wave's loads of k-tile kt are done once at most those of the later k-tiles
-            // in flight (8 per k-tile) remain; the barrier then covers every wave's loads, and
-            // every wave's reads of the stage that k-tile kt + RSTAGES - 1 refills (k-tile
-            // kt - 1's)
-            const int ahead = min(nk - 1, kt + RSTAGES - 2) - kt;
+            // this wave's loads of k-tile kt are done; the barrier then covers every wave's loads, and
+            // every wave's reads of the stage that k-tile kt + 1 refills (k-tile kt - 1's)
             asm volatile("" ::: "memory");
-            if (ahead >= 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));
-            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
-            if (kt + RSTAGES - 1 < nk)
-                x_ring_issue(ring, smem + ((kt + RSTAGES - 1) % RSTAGES) * RSTAGE, kbeg + (kt + RSTAGES - 1) * XBK,
-                             wave);
+            if (kt + 1 < nk) x_ring_issue(ring, smem + ((kt + 1) % RSTAGES) * RSTAGE, kbeg + (kt + 1) * XBK, wave);
             const char *As = smem + (kt % RSTAGES) * RSTAGE, *Bs = As + XBM * 128;
             b8v ah[4], al[4], bh[4], bl[4];
 #pragma unroll
@@ -493,10 +485,10 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
             }
         return;
     } else {
-        // SED tile [128 galaxies][128 wavelengths] -> LDS in NPASS passes of PW columns (row
+        // SED tile [128 galaxies][128 wavelengths] -> LDS in two passes of PW columns (row
         // stride PW + 1; one stage holds half the tile), two threads per galaxy reducing PW / 2
         // wavelengths each per pass into the band sums
-        constexpr int NPASS = (x_smem<P, RING>() >= XBM * (XBN + 1) * 4 + XBN * 16) ? 1 : 2, PW = XBN / NPASS;
+        constexpr int NPASS = 2, PW = XBN / NPASS;
         float(*sed)[PW + 1] = reinterpret_cast<float(*)[PW + 1]>(smem);
         // the tile's wavelength constants (ln x, l q, q / l, l) in LDS after the SED columns:
         // read once per tile instead of one dependent global load per column and thread
@@ -530,14 +522,13 @@ __global__ void __launch_bounds__(256, (x_blocks<P, RING>())) k_xgemm(XArgs a) {
 #pragma unroll
         for (int pp = 0; pp < NPASS; ++pp) {
         if (pp > 0) __syncthreads();   // the previous pass's reads are done
-        if (NPASS == 1 || wn == pp) {
-            const int c0 = (NPASS == 1) ? wn * 64 : 0;
+        if (wn == pp) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) sed[wm * 64 + i * 16 + 4 * lk + q][c0 + j * 16 + li] = acc[i][j][q];
+                    for (int q = 0; q < 4; ++q) sed[wm * 64 + i * 16 + 4 * lk + q][j * 16 + li] = acc[i][j][q];
         }
         __syncthreads();
         // bands within 8 sigma of some redshifted wavelength of some thread of the wave: a
