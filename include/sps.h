@@ -90,8 +90,8 @@ typedef struct {
 
 typedef struct sps_ctx sps_ctx;
 
-/* Create a context on `device`: uploads the SSP grid (FP64 always; FP32 if
- * prec_mask has bit 1<<SPS_F32; BF16 hi+lo pair if bit 1<<SPS_BF16X), the
+/* Create a context on `device`: uploads the SSP grid (FP64 always; FP32 in three BF16
+ * parts if prec_mask has bit 1<<SPS_F32; BF16 hi+lo pair if bit 1<<SPS_BF16X), the
  * wavelength quadrature weights and the filter constants, and reserves
  * workspace for up to max_gal galaxies.  Supported SSP grid: n_age = 94,
  * n_met = 12 (compile-time register tiles); n_band <= 8.  On error *out is NULL. */
@@ -106,8 +106,9 @@ int sps_reserve(sps_ctx *ctx, int max_gal);
 
 /* Size the exact path's workspace for calls of up to max_rows galaxies (or exact-path HMC
  * chains, n_gal * n_chain), for every precision uploaded at create, with the gradient:
- * the weights rows, partial band sums, Rbar and Wbar of the two GEMMs (about 34 KB per
- * row at 2000 wavelengths and 50 KB at 5000), the z-order buffer from 16,384 rows on, and
+ * the weights rows, partial band sums, Rbar and Wbar of the two GEMMs (6 bands, large batches:
+ * about 27 KB per row at 2000 wavelengths and 48 KB at 5000 with SPS_F32, 21 and 36 KB with SPS_BF16X
+ * alone), the z-order buffer from 16,384 rows on, and
  * the exact-path HMC's chain state (~0.6 KB per chain).  Also grows
  * sps_reserve's galaxy count to max_rows.  Synchronises the device; never shrinks. */
 int sps_reserve_exact(sps_ctx *ctx, int max_rows);
@@ -151,20 +152,27 @@ int sps_weights(sps_ctx *ctx, void *stream, int n_gal, int sfh, const float *par
 
 /* Approximate AB magnitudes (Eq. photo_integral_approx; attenuation evaluated at
  * the rest-frame effective wavelength, table interpolated linearly in z, in
- * flux).  Needs a z table.  mag_out [n_gal][n_band] FP32. */
+ * flux).  Needs a z table.  mag_out [n_gal][n_band] FP32.  The approximate path's
+ * magnitudes and log L do not depend on the batch that a galaxy comes in.  Its gradients add the age
+ * bins in one order for up to 8192 and for more than 65,536 galaxies and in two others for
+ * 8193..32,768 and 32,769..65,536, so the same galaxy in batches of two of these ranges differs by
+ * FP32 rounding, up to 1e-5 of its largest component; within a range it does not. */
 int sps_phot_approx(sps_ctx *ctx, void *stream, int n_gal, int sfh, const float *params,
                     const float *z, float *mag_out);
 
 /* Exact AB magnitudes (Eq. photo_integral_exact): dense (galaxies x SSPs) x
  * (SSPs x wavelengths) contraction on MFMA with the attenuation x redshifted
  * filter x quadrature weight applied in the epilogue.  prec = SPS_F64:
- * params/z/mag_out are double; SPS_F32 and SPS_BF16X (split hi+lo BF16 with
- * FP32 accumulation): float.  The requested precision's table must have been
- * uploaded at create.  The FP32 / BF16X paths skip wavelengths farther than 8 filter
- * sigmas from every band for all galaxies of a 128-galaxy tile (their contribution is below
- * exp(-32) of the band's), and from 16,384 galaxies on they process the galaxies in z order
- * internally (outputs are still in the caller's order).  n_gal <= the rows reserved by
- * sps_reserve_exact, else SPS_E_STATE. */
+ * params/z/mag_out are double; SPS_F32 and SPS_BF16X: float.  SPS_F32 multiplies FP32 operands, each
+ * as three BF16 parts that hold its 24 bits, in six products accumulated in FP32 (error against
+ * SPS_F64 no larger than with FP32 products; the table is scaled so that a grid in small units keeps its
+ * bits, an intermediate below 2^-110 keeps fewer); SPS_BF16X splits hi+lo (16 bits) and takes three.
+ * The requested precision's table must have been uploaded at create.  The FP32 / BF16X paths skip
+ * wavelengths farther than 8 filter sigmas from every band for all galaxies of a 128-galaxy
+ * tile, and process batches of more than 128 galaxies in z order internally (outputs are still in the
+ * caller's order), where a band is also skipped on its own beyond 8 sigmas (what is left out is at
+ * most 3e-9 of the band's sum; a band that comes no nearer than 5 sigmas to the grid is summed whole).  n_gal
+ * <= the rows reserved by sps_reserve_exact, else SPS_E_STATE. */
 int sps_phot_exact(sps_ctx *ctx, void *stream, int n_gal, int sfh, int prec, const void *params,
                    const void *z, void *mag_out);
 
@@ -192,9 +200,12 @@ int sps_phot_vjp(sps_ctx *ctx, void *stream, int n_gal, int sfh, int path, int p
 
 /* The exact magnitudes and their vector-Jacobian product as one forward and backward pass (SPS_F32 or
  * SPS_BF16X): sps_phot_exact_sums also stores the band sums [n_gal][5][n_band] FP32 (numerator,
- * normaliser, the numerator's derivatives by tau_V, delta and F_floor) in the caller's array, and
- * sps_phot_vjp_sums starts from them instead of repeating the forward contraction.  Same inputs for
- * both calls; results, limits and errors as sps_phot_exact and sps_phot_vjp. */
+ * normaliser, the numerator's derivatives by tau_V, delta and F_floor; the numerator's unit is the
+ * context's own) in the caller's array, and sps_phot_vjp_sums starts from them instead of repeating the
+ * forward contraction.  Same context and inputs for both calls; results, limits and errors as
+ * sps_phot_exact and sps_phot_vjp.  The sums make the forward 7 to 10 us dearer than sps_phot_exact up to 4096
+ * galaxies (4 to 13 %), about 6 % at 20,000, and spare the backward nearly a whole forward: a caller
+ * that will not differentiate should call sps_phot_exact. */
 int sps_phot_exact_sums(sps_ctx *ctx, void *stream, int n_gal, int sfh, int prec, const float *params,
                         const float *z, float *mag_out, float *band_sums);
 int sps_phot_vjp_sums(sps_ctx *ctx, void *stream, int n_gal, int sfh, int prec, const float *params,

@@ -506,7 +506,8 @@ class PhotApprox(torch.autograd.Function):
 
 class PhotExact(torch.autograd.Function):
     """Exact magnitudes [n_gal][n_band] in SPS_F32 or SPS_BF16X; backward: the exact path's
-    vector-Jacobian product (the adjoint GEMM) of the band adjoints."""
+    vector-Jacobian product (the adjoint GEMM) of the band adjoints.  With keep the forward saves its
+    band sums for the backward (see phot_exact)."""
 
     @staticmethod
     def forward(ctx, params, z, sps_ctx, sfh, prec, keep=False):
@@ -535,5 +536,9 @@ def phot_approx(sps_ctx, params, z, sfh=SPS_SFH_DPL):
 
 
 def phot_exact(sps_ctx, params, z, sfh=SPS_SFH_DPL, prec=SPS_F32):
+    """Exact magnitudes, differentiable by params.  Where params wants a gradient the forward also keeps 5
+    n_band floats per galaxy until the backward, which then need not repeat the forward contraction;
+    that makes the forward itself 4 to 13 % dearer, so call it under torch.no_grad() (or on
+    params.detach()) where no backward follows."""
     keep = prec != SPS_F64 and torch.is_grad_enabled() and params.requires_grad
     return PhotExact.apply(params, z, sps_ctx, sfh, prec, keep)

@@ -482,8 +482,7 @@ __device__ __forceinline__ void approx_eval(const DevConsts &k, const float *led
     static_assert(!VJP || MODE == MODE_LOGL_GRAD, "the vector-Jacobian product is the gradient pass");
     // bins the walks take at a time where a wave's lanes agree: bin by bin 981 us, two 913, four 905,
     // value+gradient of a million DPL galaxies in 6 bands.  The samplers (PK = false) go bin by bin: the
-    // chains of a wave agree less and their loop already exceeds the instruction cache (102 us per
-    // evaluation of 65,536 chains with one, two or four).
+    // chains of a wave agree less (102 us per evaluation of 65,536 chains with one, two or four).
     constexpr int WALK = PK ? 4 : 1;
     const int nb = k.n_band;
     const int lane = opaque((int)threadIdx.x & (WAVE - 1));

@@ -29,7 +29,8 @@ constexpr int EPI_PHOT = 0, EPI_PHOT_DUST = 1, EPI_STORE = 2;
 
 __device__ inline uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }   // nearest even
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-// FP32 as three BF16 values hi + mid + lo: exact (8 + 8 + 8 bits) down to the range of the last; an
+// FP32 as three BF16 values hi + mid + lo: exact (8 + 8 + 8 bits) down to 2^-110, below which the last runs out of
+// range (the weights' parts that small do not reach FP32 sums, the table is scaled, Rbar carries l q); an
 // infinity or NaN is carried by hi alone
 __device__ inline void split3(float v, uint16_t &h, uint16_t &m, uint16_t &l) {
     h = f2bf(v);
@@ -77,8 +78,8 @@ constexpr int D_K = S_PAD / D_WAVES, D_G = D_K / 8, D_BATCH = 3;   // SSPs, grou
 static_assert(S_PAD % (8 * D_WAVES) == 0 && D_G % D_BATCH == 0 && D_ROWS * D_LAM == D_T, "FP64 tile");
 // wavelength tiles per block, and whether it takes them two at a time, each weight fragment then feeding
 // two products (a CU holds one block at a time: from a block per CU on, fewer loads count for more than more
-// blocks).  us per call at 2000 wavelengths, 6 bands, one at a time / two: 64 galaxies 36.9 / 40.0, 65
-// 47.3 / 40.8, 500 148 / 106, 4096 917 / 600 (192, 883 on the tiles above).
+// blocks).  us per call at 2000 wavelengths, 6 bands, one at a time / two: 64 galaxies 29.9 / 33.4, 65
+// 39.8 / 33.3, 500 136 / 94, 4096 998 / 605 (500 and 4096 galaxies on the tiles above: 192, 883).
 constexpr int D_WIDE = 256;
 static int f64_tiles(int n, int n_wave, bool *wide) {
     const int blocks = (n + D_ROWS - 1) / D_ROWS * ((n_wave + D_LAM - 1) / D_LAM);
@@ -211,7 +212,8 @@ __global__ void __launch_bounds__(D_T, 2) k_exact_phot64(DArgs a) {
 // products issue).  Both precisions run on v_mfma_f32_16x16x32_bf16, lane l supplying k =
 // 8 (l / 16) .. + 7, with FP32 accumulation, the operands split into XP BF16 parts that lie
 // side by side per 32-element k chunk (bfx_at, bf3_at), so a k-tile of a row is XP 64-byte runs:
-//   FP32:  hi + mid + lo, which hold all 24 bits; six products lo.hi + hi.lo + mid.mid + mid.hi +
+//   FP32:  hi + mid + lo, which hold all 24 bits (of values down to 2^-110, see split3 and
+//          sps_ctx::lum32_exp); six products lo.hi + hi.lo + mid.mid + mid.hi +
 //          hi.mid + hi.hi per tile pair (the three dropped ones are below 2^-26 of the product).
 //          v_mfma_f32_16x16x4f32 takes 32 cycles for 4 k, these six 96 for 32: the GEMMs at 4096 x
 //          5000 took 378 (forward) and 373 us (gradient) on the former.
@@ -265,7 +267,9 @@ struct XArgs {
 // LDS stages, filled by direct global-to-LDS loads (no staging registers): one stage with three blocks
 // per CU, whose products cover each other's loads; or for BF16X (RING = true, a launch choice) a ring
 // of two stages with two blocks per CU.  The two BF16X forms multiply the same tiles in the same order
-// (the same bits); which is faster depends on the shape (sps_autotune_exact).
+// (the same bits); which is faster depends on the shape (sps_autotune_exact): value+gradient, us, one stage /
+// ring, 2000 wavelengths, 200 galaxies 105 / 99, 1000 121 / 117, 4096 171 / 175, 65,536 1224 / 1294; 5000
+// wavelengths, 1000 141 / 134, 4096 257 / 278.
 constexpr int RSTAGES = 2;
 constexpr int RSTAGE = 2 * XBM * 128;   // A then B rows, 128 bytes (the k-tile's 32 hi + 32 lo) each
 // the single stage is at least the epilogue's half SED tile with the wavelength constants

@@ -12,7 +12,8 @@
 //   values in FP32, the running total mass in FP64.  Against the exact integrals this
 //   keeps the total mass within ~4e-6 and the tau, alpha, beta derivatives within ~8e-5
 //   over tau 0.1-14 Gyr, alpha, beta 0.1-8, z 0.1-3.
-//   log-normal SFH: Gauss-Legendre quadrature of the normal density over each bin in FP32
+//   log-normal SFH: Gauss-Legendre quadrature of the normal density over each bin in FP32, the
+//   difference of the normal tails in bins wider than the density's local scale
 //   (closed-form normal-CDF differences in FP64 on the FP64 exact path).
 // Burst (Eq. triweight): closed-form triweight CDF differences in log age.
 // Metallicity (App. A.2): normal-CDF differences on the midpoint bins.
@@ -348,7 +349,7 @@ __device__ inline void logn_bin_e(double a_lo, double a_hi, double t_obs, double
 // difference of the tails at the bin's ends.  (Panels throughout took up to 256 of them in the
 // old bins of a narrow log-normal, and a wave its largest lane's number: 1470 nodes per galaxy
 // over a batch of widths 0.2 to 1.5, where its own lanes need 320.  Magnitudes of 100,000 galaxies in 6
-// bands, us per call: 117 then, 87 now; of a million 632 and 474.)  Against FP64 normal-CDF differences over t_p
+// bands, us per call: 117 then, 85 now; of a million 632 and 465.)  Against FP64 normal-CDF differences over t_p
 // 0.5-13 Gyr, w 0.15-2, t_obs 2-12 Gyr: bin masses within 1e-5 relative, where FP32 x itself
 // limits far tails, and the derivatives within 5e-7 of their sum over the bins; over t_p 1-12, w 0.2-1.5
 // the weights' summed error is 2.31e-7 on average (2.32e-7 with panels alone), 1.85e-6 at most.  The oldest

@@ -1,8 +1,9 @@
 // One galaxy (or chain) per workgroup of two waves: the approximate-path model for batches too
 // small to fill the chip with a lane or two per galaxy.
 //
-// Same model, rules, operand rounding and summation order as approx_eval, so the results are the
-// batched kernels'; only the FP64 total of the smooth mass is summed in another order.  A thread
+// Same model, rules, operand rounding and FP32 summation order as approx_eval with one lane per galaxy (the
+// samplers': with two), so the results are that kernel's; only the FP64 sums (the total of the smooth mass, the
+// log-normal derivatives) are taken in another order.  A thread
 // owns one age bin (its mass, derivatives and burst share stay in registers between the forward and
 // the adjoint pass), and wave w takes every second block of 16 table rows (ages) of the contraction:
 // the fragments of both z nodes are loaded into registers ahead of their use, the forward ones during
@@ -11,8 +12,8 @@
 // sum per lane.  Nothing is shared between galaxies: no z sort, no record, no pass per z bucket.
 //
 // What bounds it: the serial chain of one evaluation (bins -> total -> contraction -> bands ->
-// adjoint contraction -> sums) while the chip has free wave slots, then the wave slots and the 66 KB
-// of table that each wave reads from L2.
+// adjoint contraction -> sums) while the chip has free wave slots, then the wave slots and the table that
+// each wave reads from L2, 36 KB per contraction.
 #pragma once
 #include "sps_eval.h"
 
@@ -101,8 +102,8 @@ __device__ inline float pair_edge(const PairBin &b, int e) {
 
 // wave w's fragments (qf or qa of sps_internal.h) of nodes kb and kb + 1: blocks 2 t + w, BF16 hi and
 // lo.  The first PAIR_KRES k-steps are loaded ahead, the rest inside the contraction: one leaves 128
-// registers, four waves per SIMD (value+gradient at 4096 galaxies, us: 41; two ahead, three waves, 43;
-// all three ahead, two waves, 50; at one galaxy the same within 1 us).
+// registers, four waves per SIMD (value+gradient, us at 4096 / 8192 galaxies: 38 / 63; two ahead, three waves, 41 / 69;
+// all three ahead, two waves, 44 / 75; at one galaxy the same).
 constexpr int PAIR_KRES = 1;
 struct PairTab {
     b8v h[PAIR_KRES][2][PAIR_NB], l[PAIR_KRES][2][PAIR_NB];
