@@ -170,9 +170,10 @@ int sps_phot_approx(sps_ctx *ctx, void *stream, int n_gal, int sfh, const float 
  * The requested precision's table must have been uploaded at create.  The FP32 / BF16X paths skip
  * wavelengths farther than 8 filter sigmas from every band for all galaxies of a 128-galaxy
  * tile, and process batches of more than 128 galaxies in z order internally (outputs are still in the
- * caller's order), where a band is also skipped on its own beyond 8 sigmas (what is left out is at
- * most 3e-9 of the band's sum; a band that comes no nearer than 5 sigmas to the grid is summed whole).  n_gal
- * <= the rows reserved by sps_reserve_exact, else SPS_E_STATE. */
+ * caller's order), where a band is also skipped on its own beyond 8 sigmas.  What is left out is at most 3e-9
+ * of the transmission, less than 5e-7 of the band for tau_V <= 4, delta >= -1.5; a band that comes no
+ * nearer than 5 sigmas to the grid, or whose attenuation has no floor and rises so steeply that farther terms
+ * count, is summed whole.  n_gal <= the rows reserved by sps_reserve_exact, else SPS_E_STATE. */
 int sps_phot_exact(sps_ctx *ctx, void *stream, int n_gal, int sfh, int prec, const void *params,
                    const void *z, void *mag_out);
 
