@@ -831,6 +831,8 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
         g8 = cb * (double)v[3];
         g9 = cb * (double)v[4];
     }
+    // a kept band (k_xwindows) whose sum is 0, or too small for 1 / sum, has no share
+    if (((win_keep(w) >> b) & 1u) && (num == 0.0 || fabs(cb) > 3.4e38)) cb = 0.0;
     if (valid && cnum) cnum[(size_t)r * NB_MAX + b] = (float)cb;
     ll = group_sum<8>(ll);
     if (logl && valid && b == 0) logl[g] = (float)ll;
@@ -843,7 +845,10 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
 }
 
 // Rbar[g][l] = sum_b (d logL / d num_b) F_att(l) T_b((1+z) l) l q_l  (zero beyond n_wave);
-// bands more than 8 sigma from the redshifted wavelength contribute below FP32 resolution.
+// bands more than 8 sigma from the redshifted wavelength contribute below FP32 resolution, but in a row
+// tile with a win_keep, whose magnitudes are made of such terms: there none is left out.  (One limit for
+// all bands, and seven waves on a SIMD: with a limit per band and 79 registers the gradient of 20,011 galaxies, 503
+// us, took 514.)
 // One block takes G consecutive galaxies (rows of one 128-row tile, so one filter-support
 // window, all that the gradient GEMM reads) and walks their rows from the window's first k-tile to its
 // last, two wavelengths per thread: the galaxies' constants are loaded
@@ -855,13 +860,14 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
 constexpr int RBAR_G_BIG = 4, RBAR_BIG_MIN_GAL = 16384;
 static_assert(XBM % RBAR_G_BIG == 0, "a block's galaxies share one row tile");
 template <int P, int RBAR_G>
-__global__ void __launch_bounds__(256) k_exact_rbar(int n, int n_wave, int ld, int nb, FiltConst fl,
+__global__ void __launch_bounds__(256, P == SPS_F32 ? 6 : 7) k_exact_rbar(int n, int n_wave, int ld, int nb, FiltConst fl,
                                                     const float *dust, const float *z, const float *wc,
                                                     const float *cnum, const int4 *win, void *rb) {
     const int g0 = blockIdx.x * RBAR_G, tid = threadIdx.x;
     const int ng = min(RBAR_G, n - g0);   // galaxies of this block (>= 1)
     const int4 wn = win[g0 / XBM];
     const int lo = win_z(wn) * XBK, hi = min(ld, wn.w * XBK);
+    const float cut = win_keep(wn) ? INFINITY : 8.0f * GAUSS_K2;
     double opz[RBAR_G];
     float cb[RBAR_G][NB_MAX], ffl[RBAR_G], delta2[RBAR_G], tauv2[RBAR_G];
 #pragma unroll
@@ -893,7 +899,7 @@ __global__ void __launch_bounds__(256) k_exact_rbar(int n, int n_wave, int ld, i
             for (int b = 0; b < NB_MAX; ++b) {
                 if (b >= nb) break;
                 const float ta = (float)(opz[j] * fl.gk[b]), t0 = fmaf(w[0][3], ta, tc[b]), t1 = fmaf(w[1][3], ta, tc[b]);
-                if (fminf(fabsf(t0), fabsf(t1)) < 8.0f * GAUSS_K2) {
+                if (fminf(fabsf(t0), fabsf(t1)) < cut) {
                     sum[0] = fmaf(cb[j][b], __builtin_amdgcn_exp2f(-t0 * t0), sum[0]);
                     sum[1] = fmaf(cb[j][b], __builtin_amdgcn_exp2f(-t1 * t1), sum[1]);
                 }
@@ -1305,18 +1311,19 @@ __global__ void __launch_bounds__(128) k_xwindows(int n, int n_wave, FiltConst f
     // magnitude is made of far terms, so the epilogue must skip none; of a nearer one's sum, the terms beyond 8
     // sigma are at most exp(-(64 - 25) / 2) = 3e-9.
     const unsigned steep_any = steep[0] | steep[1];
-    unsigned far_bands = ~dense | steep_any;
+    unsigned far_bands = (~dense & ((1u << nb) - 1u)) | steep_any;
     double lo = 1e300, hi = 0.0;
 #pragma unroll
     for (int b = 0; b < NB_MAX; ++b) {   // unrolled: the bands' limits are read together
         const double l8 = fl.lo8[b], h8 = fl.hi8[b];
         if (b >= nb) continue;
-        // with steep galaxies 14.5 sigma, where T is below the smallest FP32 number
-        lo = fmin(lo, (steep_any ? 1.40625 * l8 - 0.40625 * h8 : l8) / (1.0 + z1));
-        hi = fmax(hi, (steep_any ? 1.40625 * h8 - 0.40625 * l8 : h8) / (1.0 + z0));
         // c - 5 s and c + 5 s
         if ((1.0 + z1) * lam_first >= 0.8125 * h8 + 0.1875 * l8 || (1.0 + z0) * lam_last <= 0.8125 * l8 + 0.1875 * h8)
             far_bands |= 1u << b;
+        // of these, and with steep galaxies, 14.5 sigma, where T is below the smallest FP32 number
+        const bool wide = steep_any || ((far_bands >> b) & 1u);
+        lo = fmin(lo, (wide ? 1.40625 * l8 - 0.40625 * h8 : l8) / (1.0 + z1));
+        hi = fmax(hi, (wide ? 1.40625 * h8 - 0.40625 * l8 : h8) / (1.0 + z0));
     }
     // the number of wavelengths below lo (wave 0) and up to hi (wave 1) on the ascending grid: 64 probes at
     // a time (a serial binary search waited out 26 loads, 7.6 us)

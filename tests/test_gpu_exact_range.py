@@ -84,3 +84,34 @@ def test_steep_attenuation_without_a_floor(ssp2000, n_band, n, prec_name):
     assert np.array_equal(np.isfinite(many), np.isfinite(few[at]))
     ok = np.isfinite(many) & (few[at] < 256)
     assert ok.mean() > 0.9 and np.abs(many[ok] - few[at][ok]).max() <= 5e-5
+
+
+@pytest.mark.parametrize("prec_name", ["SPS_F32", "SPS_BF16X"])
+@pytest.mark.parametrize("grid,n_band,n", [("end", 6, 100), ("end", 1, 400), ("end", 6, 16384), ("gap", 6, 400)])
+def test_gradient_of_a_band_past_the_end_of_the_grid(filt6, grid, n_band, n, prec_name):
+    # bands of which the grid, from 3000 A or without 2500 .. 6000 A, holds only terms from 5 to 12 widths away: the
+    # gradient with respect to the star formation and metallicity slots is made of the same terms as the magnitude.
+    # Against the oracle's Jacobian to 1e-3, the bar of a gradient, of the sum of the bands' shares; galaxies whose
+    # bands all lie within 12 widths, beyond which sums leave the FP32 range
+    import paper_2506_19919_amd as sps
+    from oracle import Oracle
+    prec = getattr(sps, prec_name)
+    g = synth.ssp_grid(1500)
+    w = g["wave_A"]
+    k = w >= 3000.0 if grid == "end" else (w < 2500.0) | (w >= 6000.0)
+    cut = dict(g, wave_A=w[k].copy(), lum=np.ascontiguousarray(g["lum"][..., k]))
+    filt = dict(center_A=filt6["center_A"][:n_band].copy(), sigma_A=filt6["sigma_A"][:n_band].copy())
+    sfh, th, z = gal_inputs("dpl", 100, 891)
+    gbar = np.random.default_rng(892).normal(size=(100, n_band))
+    _, jac = Oracle(cut, filt).mags_jacobian(sfh, th.astype(np.float32), z.astype(np.float32), path=1)
+    ref = np.einsum("gb,gbp->gp", gbar.astype(np.float32), jac)
+    share = np.einsum("gb,gbp->gp", np.abs(gbar), np.abs(jac))[:, 1:7].max(1, keepdims=True)
+    rest = (1 + z)[:, None, None] * w[k]
+    width = np.abs((rest - filt["center_A"][:, None]) / filt["sigma_A"][:, None]).min(2).max(1)
+    assert ((width > 8.2) & (width < 12)).sum() >= (5 if grid == "end" else 1) and ((width > 5) & (width < 8)).sum() >= 5
+    ctx = sps.Context(cut, filt, precisions=(prec,), max_gal=n, max_exact=n)
+    at = np.arange(n) % 100
+    grad = ctx.phot_vjp(sfh, soa(th[at]), dev(z[at]), dev(gbar[at]), path=sps.SPS_PATH_EXACT, prec=prec).T.cpu().numpy()
+    ctx.close()
+    err = (np.abs(grad - ref[at]) / share[at])[:, 1:7].max(1)
+    assert err[width[at] < 12].max() <= 1e-3
