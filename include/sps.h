@@ -173,7 +173,7 @@ int sps_phot_approx(sps_ctx *ctx, void *stream, int n_gal, int sfh, const float 
  * caller's order), where a band is also skipped on its own beyond 8 sigmas.  What is left out is at most 3e-9
  * of the transmission, less than 5e-7 of the band for tau_V <= 4, delta >= -1.5; a band that comes no
  * nearer than 5 sigmas to the grid, or whose attenuation has no floor and rises so steeply that farther terms
- * count, is summed whole.  n_gal <= the rows reserved by sps_reserve_exact, else SPS_E_STATE. */
+ * count, is summed whole, and so is its share of a gradient.  n_gal <= the rows reserved by sps_reserve_exact, else SPS_E_STATE. */
 int sps_phot_exact(sps_ctx *ctx, void *stream, int n_gal, int sfh, int prec, const void *params,
                    const void *z, void *mag_out);
 

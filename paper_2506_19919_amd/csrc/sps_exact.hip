@@ -231,7 +231,7 @@ template <int P> constexpr int x_stage() { return 2 * x_parts<P>() * XSUB; }    
 constexpr int XSPLIT_MAX = 8, XSPLIT_BLOCKS = 640;
 constexpr int XBAND = 8;                                     // row tiles per band (tile order 3)
 
-// a row tile's window (k_xwindows) packs the bands that the forward epilogue must not skip over its first k-tile
+// a row tile's window (k_xwindows) packs the bands that the forward epilogue and Rbar must not skip over its first k-tile
 __device__ inline int win_z(int4 w) { return w.z & 0xffffff; }
 __device__ inline unsigned win_keep(int4 w) { return (unsigned)w.z >> 24; }
 
@@ -1251,7 +1251,8 @@ __global__ void __launch_bounds__(64) k_exact_adjoint(DevConsts k, int n, int sf
 // Per 128-galaxy row tile: the rest-frame wavelengths any band reaches within 8 sigma for any
 // of the tile's galaxies, [min_b (c_b - 8 s_b) / (1 + z_max), max_b (c_b + 8 s_b) / (1 + z_min)],
 // as 128-wide wavelength tiles and 32-wide k-tiles of the padded grid, one index of margin on
-// each side; and the bands that the forward epilogue must not skip.  One block per row tile.
+// each side (14.5 sigma, beyond which T is below the smallest FP32 number, for the bands that come no nearer than
+// 5 sigma to the grid); and the bands that the forward epilogue and Rbar must not skip.  One block per row tile.
 //
 // 8 sigma leave out less than 5e-7 of a band over 0 <= tau_V <= 4, delta >= -1.5 at z <= 3.  Without a floor a steeper
 // attenuation can outweigh the transmission (delta = -3: magnitudes up to 1.6 off): steep_bands' bit b is set for a
@@ -1320,7 +1321,7 @@ __global__ void __launch_bounds__(128) k_xwindows(int n, int n_wave, FiltConst f
         // c - 5 s and c + 5 s
         if ((1.0 + z1) * lam_first >= 0.8125 * h8 + 0.1875 * l8 || (1.0 + z0) * lam_last <= 0.8125 * l8 + 0.1875 * h8)
             far_bands |= 1u << b;
-        // of these, and with steep galaxies, 14.5 sigma, where T is below the smallest FP32 number
+        // of these, and with steep galaxies, 14.5 sigma
         const bool wide = steep_any || ((far_bands >> b) & 1u);
         lo = fmin(lo, (wide ? 1.40625 * l8 - 0.40625 * h8 : l8) / (1.0 + z1));
         hi = fmax(hi, (wide ? 1.40625 * h8 - 0.40625 * l8 : h8) / (1.0 + z0));
