@@ -854,7 +854,7 @@ __global__ void __launch_bounds__(256) k_exact_finish(DevConsts k, int n, int n_
 // last, two wavelengths per thread: the galaxies' constants are loaded
 // together once, and each batch of wavelength constants serves all of the block's galaxies.
 // G = 4 spares those loads, G = 1 keeps more blocks in flight: us with 1 / 4 galaxies, 6 bands, BF16X, 500
-// x 2000 5.3 / 9.6, 4096 13.5 / 15.8, 20,011 41.7 / 39.2, 65,536 149 / 128.  Bound by instructions (an
+// x 2000 5.2 / 9.7, 4096 12.8 / 14.6, 15,900 31.8 / 30.1, 20,011 39.0 / 36.0, 65,536 122 / 99.  Bound by instructions (an
 // exponential per band in reach and two for the dust); one wavelength per thread in whole chunks of 256
 // around the window, a 2-byte store per part, took 63 us at 20,011 and 195 at 65,536.
 constexpr int RBAR_G_BIG = 4, RBAR_BIG_MIN_GAL = 16384;
